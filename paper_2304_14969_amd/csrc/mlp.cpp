@@ -35,29 +35,35 @@ int merr(hipError_t e, const char* what) {
   return mfail(QS_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Scratch for `rows` rows: X, y, z, H1, H2, D3, D2, D1, L.
+// Device scratch: X and, with labels, y of `rows` rows; `parts` partial
+// gradients and losses of the workgroups; scores.
 struct Scratch {
-  float *X = nullptr, *y = nullptr, *z = nullptr, *H1 = nullptr, *H2 = nullptr, *D3 = nullptr,
-        *D2 = nullptr, *D1 = nullptr, *L = nullptr;
+  float *X = nullptr, *y = nullptr, *part = nullptr, *scores = nullptr;
+  double* loss = nullptr;
   void* block = nullptr;
-  bool alloc(uint64_t rows) {
-    const size_t f = rows * (QS_MLP_INPUTS + 1 + 1 + 64 + 64 + 1 + 64 + 64 + 1);
-    block = qs::device_alloc(f * sizeof(float));
+  bool alloc(uint64_t rows, bool labels, uint64_t parts, bool grads, bool want_scores) {
+    const size_t np = size_t(qs::mlp_param_count());
+    const size_t f = rows * QS_MLP_INPUTS + (labels ? rows : 0) + (want_scores ? rows : 0) +
+                     (grads ? parts * np : 0);
+    block = qs::device_alloc(parts * sizeof(double) + f * sizeof(float));
     if (!block) return false;
-    float* p = static_cast<float*>(block);
+    loss = static_cast<double*>(block);
+    float* p = reinterpret_cast<float*>(loss + parts);
     X = p; p += rows * QS_MLP_INPUTS;
-    y = p; p += rows;
-    z = p; p += rows;
-    H1 = p; p += rows * 64;
-    H2 = p; p += rows * 64;
-    D3 = p; p += rows;
-    D2 = p; p += rows * 64;
-    D1 = p; p += rows * 64;
-    L = p;
+    if (labels) { y = p; p += rows; }
+    if (want_scores) { scores = p; p += rows; }
+    if (grads) part = p;
     return true;
   }
   ~Scratch() { qs::device_free(block); }
 };
+
+// The mean of the rows' losses from the workgroups' sums (in order).
+double mean_loss(const double* sums, int n, uint64_t rows) {
+  double t = 0.0;
+  for (int i = 0; i < n; ++i) t += sums[i];
+  return t / double(rows);
+}
 
 }  // namespace
 
@@ -79,18 +85,14 @@ int mlp_scores(qs_mlp* net, const float* X, uint64_t rows, float* scores) {
     return QS_OK;
   }
   Scratch s;
-  if (!s.alloc(rows)) return mfail(QS_E_NOMEM, "network scratch");
+  if (!s.alloc(rows, false, 0, false, true)) return mfail(QS_E_NOMEM, "network scratch");
   hipError_t e = hipMemcpyAsync(s.X, X, rows * QS_MLP_INPUTS * sizeof(float), hipMemcpyHostToDevice,
                                 net->stream);
+  if (e == hipSuccess) e = launch_mlp_scores(net->P, s.X, int(rows), s.scores, net->stream);
   if (e == hipSuccess)
-    e = launch_mlp_forward(net->P, s.X, int(rows), s.z, nullptr, nullptr, net->stream);
-  std::vector<float> z(rows);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(z.data(), s.z, rows * sizeof(float), hipMemcpyDeviceToHost, net->stream);
+    e = hipMemcpyAsync(scores, s.scores, rows * sizeof(float), hipMemcpyDeviceToHost, net->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(net->stream);
-  if (int rc = merr(e, "network forward")) return rc;
-  for (uint64_t r = 0; r < rows; ++r) scores[r] = 1.0f / (1.0f + std::exp(-z[r]));
-  return QS_OK;
+  return merr(e, "network forward");
 }
 
 }  // namespace qs
@@ -176,23 +178,20 @@ int qs_mlp_grad(qs_mlp* n, const float* X, const float* y, uint64_t rows, float*
   if (!n || !X || !y || !grad) return mfail(QS_E_INVAL, "NULL argument");
   if (rows == 0 || rows > (uint64_t(1) << 24)) return mfail(QS_E_INVAL, "rows = %llu", (unsigned long long)rows);
   Scratch s;
-  if (!s.alloc(rows)) return mfail(QS_E_NOMEM, "network scratch");
+  const int groups = qs::mlp_groups(int(rows));
+  if (!s.alloc(rows, true, groups, true, false)) return mfail(QS_E_NOMEM, "network scratch");
   hipError_t e = hipMemcpyAsync(s.X, X, rows * QS_MLP_INPUTS * sizeof(float), hipMemcpyHostToDevice, n->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(s.y, y, rows * sizeof(float), hipMemcpyHostToDevice, n->stream);
-  if (e == hipSuccess) e = qs::launch_mlp_forward(n->P, s.X, int(rows), s.z, s.H1, s.H2, n->stream);
   if (e == hipSuccess)
-    e = qs::launch_mlp_backward(n->P, s.X, s.y, int(rows), s.z, s.H1, s.H2, s.D3, s.D2, s.D1, s.L, n->G, n->stream);
-  std::vector<float> L(rows);
+    e = qs::launch_mlp_grad(n->P, s.X, s.y, int(rows), s.part, s.loss, n->G, n->stream);
+  double sums[qs::kMlpGroups];
   if (e == hipSuccess)
     e = hipMemcpyAsync(grad, n->G, QS_MLP_PARAMS * sizeof(float), hipMemcpyDeviceToHost, n->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(L.data(), s.L, rows * sizeof(float), hipMemcpyDeviceToHost, n->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(sums, s.loss, groups * sizeof(double), hipMemcpyDeviceToHost, n->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(n->stream);
   if (int rc = merr(e, "network gradient")) return rc;
-  if (loss) {
-    double t = 0.0;
-    for (float v : L) t += v;
-    *loss = t / double(rows);
-  }
+  if (loss) *loss = mean_loss(sums, groups, rows);
   return QS_OK;
 }
 
@@ -205,8 +204,9 @@ int qs_mlp_train(qs_mlp* n, const float* X, const float* y, uint64_t rows, const
   if (!(cfg->lr > 0) || !(cfg->beta1 >= 0 && cfg->beta1 < 1) || !(cfg->beta2 >= 0 && cfg->beta2 < 1))
     return mfail(QS_E_INVAL, "bad optimizer settings");
   // the whole data set on the device, minibatches are consecutive rows
-  Scratch data, mb;
-  if (!data.alloc(rows) || !mb.alloc(B)) return mfail(QS_E_NOMEM, "training buffers");
+  Scratch data;
+  const int groups = qs::mlp_groups(int(rows));  // at least those of a minibatch
+  if (!data.alloc(rows, true, groups, true, false)) return mfail(QS_E_NOMEM, "training buffers");
   hipError_t e = hipMemcpyAsync(data.X, X, rows * QS_MLP_INPUTS * sizeof(float), hipMemcpyHostToDevice, n->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(data.y, y, rows * sizeof(float), hipMemcpyHostToDevice, n->stream);
   // fresh optimizer moments
@@ -219,27 +219,20 @@ int qs_mlp_train(qs_mlp* n, const float* X, const float* y, uint64_t rows, const
     const float* Xb = data.X + cursor * QS_MLP_INPUTS;
     const float* yb = data.y + cursor;
     cursor += B;
-    e = qs::launch_mlp_forward(n->P, Xb, int(B), mb.z, mb.H1, mb.H2, n->stream);
-    if (e == hipSuccess)
-      e = qs::launch_mlp_backward(n->P, Xb, yb, int(B), mb.z, mb.H1, mb.H2, mb.D3, mb.D2, mb.D1, mb.L, n->G, n->stream);
     b1t *= cfg->beta1;
     b2t *= cfg->beta2;
-    if (e == hipSuccess)
-      e = qs::launch_mlp_adam(n->P, n->M, n->V, n->G, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps,
-                              float(1.0 / (1.0 - b1t)), float(1.0 / (1.0 - b2t)), n->stream);
+    e = qs::launch_mlp_step(n->P, n->M, n->V, Xb, yb, int(B), data.part, data.loss, cfg->lr,
+                            cfg->beta1, cfg->beta2, cfg->eps, float(1.0 / (1.0 - b1t)),
+                            float(1.0 / (1.0 - b2t)), n->stream);
   }
   if (e == hipSuccess && final_loss) {
     // mean loss over the whole data set with the trained parameters
-    e = qs::launch_mlp_forward(n->P, data.X, int(rows), data.z, data.H1, data.H2, n->stream);
+    double sums[qs::kMlpGroups];
+    e = qs::launch_mlp_loss(n->P, data.X, data.y, int(rows), data.loss, n->stream);
     if (e == hipSuccess)
-      e = qs::launch_mlp_backward(n->P, data.X, data.y, int(rows), data.z, data.H1, data.H2, data.D3,
-                                  data.D2, data.D1, data.L, n->G, n->stream);
-    std::vector<float> L(rows);
-    if (e == hipSuccess) e = hipMemcpyAsync(L.data(), data.L, rows * sizeof(float), hipMemcpyDeviceToHost, n->stream);
+      e = hipMemcpyAsync(sums, data.loss, groups * sizeof(double), hipMemcpyDeviceToHost, n->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(n->stream);
-    double t = 0.0;
-    for (float v : L) t += v;
-    *final_loss = t / double(rows);
+    if (e == hipSuccess) *final_loss = mean_loss(sums, groups, rows);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(n->stream);
   return merr(e, "network training");
