@@ -190,10 +190,8 @@ std::vector<Block> fuse(const std::vector<Gate>& gates, int n, int kmax) {
 
 namespace {
 
-// The gates of `sel` (indices into `qb`, the qubit lists) taken in rounds of
-// the dependence order: each call returns the gates of one group whose
-// qubits, together with `fixed`, need at most `budget` extra qubits; `done`
-// marks the gates already taken. Qubits in `fixed` are free.
+// The gates of a list (`qb`: the qubits of each) in the dependence order:
+// front() are those whose earlier gates on the same qubits are taken.
 struct DagCursor {
   const std::vector<std::vector<int>>* qb = nullptr;
   std::vector<std::vector<int>> per_qubit;  // gate positions (into sel) per qubit
@@ -230,21 +228,17 @@ struct DagCursor {
   }
 };
 
-// Greedy group: front gates (circuit order) whose qubits outside `fixed`
-// fit, with the qubits already chosen, in `budget`; `eligible` filters.
-template <typename Eligible>
-std::vector<int> take_group(DagCursor& dag, const std::vector<char>& fixed, int budget,
-                            std::vector<int>* chosen, Eligible eligible) {
+// Greedy group: front gates (circuit order) whose qubits, with those already
+// chosen, fit in `budget`.
+std::vector<int> take_group(DagCursor& dag, int budget, std::vector<int>* chosen) {
   std::vector<int> out;
   bool progress = true;
   while (progress) {
     progress = false;
     for (int i : dag.front()) {
-      if (!eligible(i)) continue;
       std::vector<int> need;
       for (int x : (*dag.qb)[i])
-        if (!fixed[x] && std::find(chosen->begin(), chosen->end(), x) == chosen->end())
-          need.push_back(x);
+        if (std::find(chosen->begin(), chosen->end(), x) == chosen->end()) need.push_back(x);
       if (int(chosen->size() + need.size()) > budget) continue;
       chosen->insert(chosen->end(), need.begin(), need.end());
       dag.take(i);
@@ -257,7 +251,163 @@ std::vector<int> take_group(DagCursor& dag, const std::vector<char>& fixed, int 
 
 }  // namespace
 
-TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, bool dense) {
+namespace {
+
+// The gate list with its one-qubit gates multiplied into wider neighbours
+// (float64): into the last gate on their qubit if it has two or more qubits,
+// else, collected, into the next one; a gate on the same qubits as the gate
+// before it on each of them is multiplied into that one. What stays are gates
+// of two or more qubits and one product per qubit that only has one-qubit
+// gates. The order keeps every qubit's gates in order.
+std::vector<Gate> merge_gates(const std::vector<Gate>& gates, int n) {
+  std::vector<Gate> out;
+  std::vector<int> last(n, -1);  // per qubit: its last gate in out
+  std::vector<std::vector<cd>> pend(n);
+  auto at = [](const Gate& g, int q) { return int(std::find(g.q, g.q + g.k, q) - g.q); };
+  for (const Gate& g : gates) {
+    if (g.k == 1) {
+      const int q = g.q[0], zero = 0;
+      if (last[q] >= 0) {
+        const int b = at(out[last[q]], q);
+        left_apply(out[last[q]].m, out[last[q]].k, g.m, 1, &b);
+      } else {
+        if (pend[q].empty()) pend[q] = eye(1);
+        left_apply(pend[q], 1, g.m, 1, &zero);
+      }
+      continue;
+    }
+    int prev = last[g.q[0]];
+    for (int j = 1; j < g.k; ++j)
+      if (last[g.q[j]] != prev) prev = -1;
+    if (prev >= 0 && out[prev].k == g.k) {
+      int lp[QS_MAX_FUSED];
+      for (int j = 0; j < g.k; ++j) lp[j] = at(out[prev], g.q[j]);
+      left_apply(out[prev].m, g.k, g.m, g.k, lp);
+      continue;
+    }
+    Gate w = g;
+    bool any = false;
+    for (int j = 0; j < g.k; ++j) any |= !pend[g.q[j]].empty();
+    if (any) {
+      w.m = eye(g.k);
+      for (int j = 0; j < g.k; ++j)
+        if (!pend[g.q[j]].empty()) left_apply(w.m, g.k, pend[g.q[j]], 1, &j);
+      int lp[QS_MAX_FUSED];
+      for (int j = 0; j < g.k; ++j) lp[j] = j;
+      left_apply(w.m, g.k, g.m, g.k, lp);
+      for (int j = 0; j < g.k; ++j) pend[g.q[j]].clear();
+    }
+    for (int j = 0; j < g.k; ++j) last[g.q[j]] = int(out.size());
+    out.push_back(std::move(w));
+  }
+  for (int q = 0; q < n; ++q)
+    if (!pend[q].empty()) {
+      Gate w;
+      w.k = 1;
+      w.q[0] = q;
+      w.m = std::move(pend[q]);
+      out.push_back(std::move(w));
+    }
+  return out;
+}
+
+// Which gates a pass takes. A pass on a set of qubits runs every gate that
+// the dependence order lets it run inside the set; the set is the low bits
+// plus at most H qubits, grown by the ready gate that lets the most gates run
+// per qubit it adds. (Taking front gates in circuit order while they fit,
+// the rule before, needed 24.2 passes for 10 layers at 28 qubits where this
+// one needs 16.8, and 11.4 against 7.6 for 8 layers at 20.)
+struct PassPicker {
+  const std::vector<Gate>& g;
+  int n, max_k;
+  std::vector<uint64_t> mask;             // qubits of each gate
+  std::vector<std::vector<int>> per;      // gates of each qubit, in order
+  std::vector<uint32_t> next;             // per qubit: its first gate not taken yet
+  size_t left;
+
+  PassPicker(const std::vector<Gate>& gates, int nq, int mk)
+      : g(gates), n(nq), max_k(mk), mask(gates.size(), 0), per(nq), next(nq, 0), left(gates.size()) {
+    for (size_t i = 0; i < gates.size(); ++i)
+      for (int j = 0; j < gates[i].k; ++j) {
+        mask[i] |= uint64_t(1) << gates[i].q[j];
+        per[gates[i].q[j]].push_back(int(i));
+      }
+  }
+  int front(const std::vector<uint32_t>& nx, int q) const {
+    return nx[q] < per[q].size() ? per[q][nx[q]] : -1;
+  }
+  bool ready(const std::vector<uint32_t>& nx, int i) const {
+    for (int j = 0; j < g[i].k; ++j)
+      if (front(nx, g[i].q[j]) != i) return false;
+    return true;
+  }
+  // runs all it can inside `set`, starting with the gates on `from`
+  int run(uint64_t set, uint64_t from, std::vector<uint32_t>* nx, std::vector<int>* out) const {
+    int count = 0;
+    uint64_t look = from;
+    while (look) {
+      const int q = __builtin_ctzll(look);
+      look &= look - 1;
+      for (;;) {
+        const int i = front(*nx, q);
+        if (i < 0 || g[i].k > max_k || (mask[i] & ~set) || !ready(*nx, i)) break;
+        for (int j = 0; j < g[i].k; ++j) ++(*nx)[g[i].q[j]];
+        ++count;
+        if (out) out->push_back(i);
+        look |= mask[i];
+      }
+    }
+    return count;
+  }
+  // The next pass: its gates (ascending) and the qubits chosen beyond `low`.
+  std::vector<int> take(uint64_t low, int H, std::vector<int>* chosen) {
+    uint64_t set = low;
+    std::vector<uint32_t> base = next, trial;
+    std::vector<int> out;
+    run(set, set, &base, &out);
+    for (int room = H; room > 0;) {
+      double best = 0;
+      uint64_t pick = 0;
+      int first = -1;  // ties go to the earliest gate
+      for (int q = 0; q < n; ++q) {
+        const int i = front(base, q);
+        if (i < 0 || g[i].k > max_k || (mask[i] & ((uint64_t(1) << q) - 1))) continue;
+        const uint64_t add = mask[i] & ~set;
+        const int cost = __builtin_popcountll(add);
+        if (cost < 1 || cost > room || !ready(base, i)) continue;
+        trial = base;
+        const double gain = double(run(set | add, mask[i], &trial, nullptr)) / cost;
+        if (gain > best || (gain == best && i < first)) best = gain, pick = add, first = i;
+      }
+      if (!pick) break;
+      set |= pick;
+      room -= __builtin_popcountll(pick);
+      run(set, set, &base, &out);
+    }
+    std::sort(out.begin(), out.end());
+    next = base;
+    left -= out.size();
+    for (int q = 0; q < n; ++q)
+      if (((set & ~low) >> q) & 1) chosen->push_back(q);
+    return out;
+  }
+  // The first ready gate (in order), taken: a gate too wide for a pass.
+  int take_wide() {
+    int i = -1;
+    for (int q = 0; q < n; ++q) {
+      const int f = front(next, q);
+      if (f >= 0 && (i < 0 || f < i) && ready(next, f)) i = f;
+    }
+    for (int j = 0; j < g[i].k; ++j) ++next[g[i].q[j]];
+    --left;
+    return i;
+  }
+};
+
+}  // namespace
+
+TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W, bool dense) {
+  const std::vector<Gate> gates = merge_gates(circuit, n);
   TilePlan plan;
   plan.C = C;
   plan.H = H;
@@ -265,18 +415,14 @@ TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, 
   plan.dense = dense;
   std::vector<std::vector<int>> qb(gates.size());
   for (size_t i = 0; i < gates.size(); ++i) qb[i].assign(gates[i].q, gates[i].q + gates[i].k);
-  DagCursor dag(qb, n);
-  std::vector<char> low(n, 0);
-  for (int q = 0; q < C && q < n; ++q) low[q] = 1;
-  const int max_k = dense ? W : 2;
-  auto small = [&](int i) { return gates[i].k <= max_k; };
-  while (dag.remaining) {
+  PassPicker picker(gates, n, dense ? W : 2);
+  const uint64_t low = (uint64_t(1) << (C < n ? C : n)) - 1;
+  while (picker.left) {
     std::vector<int> hi;
-    const std::vector<int> pass = take_group(dag, low, H, &hi, small);
+    const std::vector<int> pass = picker.take(low, H, &hi);
     if (pass.empty()) {
-      // only gates on more than two qubits at the front: the first one as a block
-      const int i = dag.front().front();
-      dag.take(i);
+      // only gates too wide for a round are ready: the first one as a block
+      const int i = picker.take_wide();
       TileStep st;
       st.block = true;
       st.ngates = 1;
@@ -313,10 +459,9 @@ TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, 
     for (size_t i = 0; i < pass.size(); ++i)
       for (int x : qb[pass[i]]) tq[i].push_back(tbit[x]);
     DagCursor rd(tq, C + H);
-    const std::vector<char> none(C + H, 0);
     while (rd.remaining) {
       std::vector<int> rb;
-      const std::vector<int> grp = take_group(rd, none, W, &rb, [](int) { return true; });
+      const std::vector<int> grp = take_group(rd, W, &rb);
       for (int b = 0; b < C + H && int(rb.size()) < W; ++b)
         if (std::find(rb.begin(), rb.end(), b) == rb.end()) rb.push_back(b);
       std::sort(rb.begin(), rb.end());

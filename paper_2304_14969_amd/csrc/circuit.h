@@ -75,13 +75,13 @@ struct TilePlan {
 };
 
 // Plans `gates` (on physical bits, in circuit order) into tile passes for a
-// state of n >= C + H qubits. Greedy over the gate dependence order: a pass
-// takes every gate at the front whose qubits fit in the low bits plus at
-// most H other bits, in circuit order, until none fits. Rounds are formed
-// the same way within a pass with W bits each. Sparse rounds (dense =
-// false) hold gates of one or two qubits; dense rounds hold any gate of at
-// most W qubits and carry the product of their gates. Larger gates run as
-// dense blocks between passes.
+// state of n >= C + H qubits. One-qubit gates are first multiplied into wider
+// neighbours. A pass takes every gate the dependence order lets it run inside
+// the low bits plus at most H other bits, which are chosen to let many gates
+// run (PassPicker in circuit.cpp). Rounds are formed greedily within a pass,
+// W bits each. Sparse rounds (dense =
+// false) hold gates of one or two qubits; dense rounds hold any gate of at most W qubits and carry the product of their
+// gates. Larger gates run as dense blocks between passes.
 TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, bool dense);
 
 // The device tables of a plan, as one byte image: per round an int4 {bits
