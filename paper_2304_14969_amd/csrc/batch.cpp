@@ -44,6 +44,7 @@ struct Launch {
   uint64_t tiles;
   int k;             // block launches: block width
   bool tile = false; // a batched tile pass (items in the tile-item table)
+  qs::TileMode mode = qs::TileMode::kDense;  // of a tile pass
 };
 
 }  // namespace
@@ -67,8 +68,8 @@ struct qs_batch {
   std::vector<std::pair<const qs_circuit*, uint64_t>> built_from;
   int built_kmax = 0;
   bool built_tiles = false;
-  void* d_tdata = nullptr;            // round table, then the embedded round matrices
-  size_t tmats_off = 0;               // byte offset of the matrices in d_tdata
+  void* d_tdata = nullptr;            // round table, dense operands, pair matrices
+  size_t temb_off = 0, tmats_off = 0; // byte offsets of the operands and matrices in d_tdata
   std::vector<Launch> launches;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -96,8 +97,9 @@ void drop_run(qs_batch* b) {
   b->built_from.clear();
 }
 
-// Tile passes for the kets that take them: one launch per pass index over
-// every ket that has that pass. Fills use_tile; false if nothing to do.
+// Tile passes for the kets that take them: one launch per pass index and kind
+// of rounds over every ket that has that pass. Fills use_tile; false if
+// nothing to do.
 int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_tile) {
   use_tile->assign(b->count, 0);
   if (!b->tiles || b->dtype != QS_C64) return QS_OK;
@@ -108,7 +110,7 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
     qs_circuit* c = circs[i];
     if (b->n[i] < C + H || c->gates.empty()) continue;
     if (!c->bplan_ok || c->bplan.C != C) {
-      c->bplan = qs::plan_tiles(c->gates, b->n[i], C, H, 4, true);
+      c->bplan = qs::plan_tiles(c->gates, b->n[i], C, H, 4, qs::matrix_tile_mode(c->gates));
       c->bplan_ok = true;
     }
     plans[i] = &c->bplan;
@@ -121,49 +123,68 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
   if (!maxp) return QS_OK;
   // rounds of every ket, in ket order; round_base[i] = first round of ket i
   std::vector<int32_t> rtab;
-  std::vector<float> emb;
+  std::vector<float> emb, mats;
   std::vector<int> round_base(b->count, 0);
-  int nround = 0;
+  int nround = 0, ndense = 0;
   for (int i = 0; i < b->count; ++i) {
     if (!(*use_tile)[i]) continue;
+    const qs::TilePlan& pl = *plans[i];
     round_base[i] = nround;
-    for (const auto& r : plans[i]->rounds) {
-      rtab.push_back(r.bits[0] | (r.bits[1] << 8) | (r.bits[2] << 16) | (r.bits[3] << 24));
-      rtab.push_back(nround * qs::kRoundOperands);
-      rtab.push_back(0);
-      rtab.push_back(0);
-      emb.resize(size_t(nround + 1) * qs::kRoundOperands);
-      qs::embed_round(plans[i]->mats.data() + r.mat,
-                      emb.data() + size_t(nround) * qs::kRoundOperands);
+    const size_t m0 = mats.size();
+    if (pl.mode == qs::TileMode::kPairs)
+      for (const auto& x : pl.mats) {
+        mats.push_back(float(x.real()));
+        mats.push_back(float(x.imag()));
+      }
+    for (const auto& r : pl.rounds) {
+      if (pl.mode == qs::TileMode::kPairs) {
+        int32_t row[4];
+        qs::pair_round_entry(pl, r, row);
+        row[2] += int32_t(m0);
+        if (row[3] >= 0) row[3] += int32_t(m0);
+        rtab.insert(rtab.end(), row, row + 4);
+      } else {
+        rtab.push_back(r.bits[0] | (r.bits[1] << 8) | (r.bits[2] << 16) | (r.bits[3] << 24));
+        rtab.push_back(ndense * qs::kRoundOperands);
+        rtab.push_back(0);
+        rtab.push_back(0);
+        emb.resize(size_t(ndense + 1) * qs::kRoundOperands);
+        qs::embed_round(pl.mats.data() + r.mat, emb.data() + size_t(ndense) * qs::kRoundOperands);
+        ++ndense;
+      }
       ++nround;
     }
   }
   std::vector<qs::TileItem> items;
-  for (size_t p = 0; p < maxp; ++p) {
-    Launch L{items.size(), 0, 0, 0, true};
-    for (int i = 0; i < b->count; ++i) {
-      if (!(*use_tile)[i] || p >= plans[i]->steps.size()) continue;
-      const qs::TileStep& st = plans[i]->steps[p];
-      qs::TileItem it{};
-      it.amp_off = b->off[i];
-      it.first_tile = L.tiles;
-      for (int j = 0; j < H; ++j) it.rows.b[j] = st.hb[j];
-      it.r0 = round_base[i] + st.r0;
-      it.nr = st.nr;
-      items.push_back(it);
-      L.tiles += uint64_t(1) << (b->n[i] - C - H);
-      ++L.nitems;
+  for (size_t p = 0; p < maxp; ++p)
+    for (const qs::TileMode mode : {qs::TileMode::kPairs, qs::TileMode::kDense}) {
+      Launch L{items.size(), 0, 0, 0, true, mode};
+      for (int i = 0; i < b->count; ++i) {
+        if (!(*use_tile)[i] || plans[i]->mode != mode || p >= plans[i]->steps.size()) continue;
+        const qs::TileStep& st = plans[i]->steps[p];
+        qs::TileItem it{};
+        it.amp_off = b->off[i];
+        it.first_tile = L.tiles;
+        for (int j = 0; j < H; ++j) it.rows.b[j] = st.hb[j];
+        it.r0 = round_base[i] + st.r0;
+        it.nr = st.nr;
+        items.push_back(it);
+        L.tiles += uint64_t(1) << (b->n[i] - C - H);
+        ++L.nitems;
+      }
+      if (L.nitems) b->launches.push_back(L);
     }
-    if (L.nitems) b->launches.push_back(L);
-  }
-  const size_t rbytes = (rtab.size() * sizeof(int32_t) + 255) / 256 * 256;
-  b->tmats_off = rbytes;
+  auto up256 = [](size_t x) { return (x + 255) / 256 * 256; };
+  b->temb_off = up256(rtab.size() * sizeof(int32_t));
+  b->tmats_off = b->temb_off + up256(emb.size() * sizeof(float));
+  std::vector<unsigned char> host(b->tmats_off + mats.size() * sizeof(float), 0);
   b->d_titems = static_cast<qs::TileItem*>(qs::device_alloc(items.size() * sizeof(qs::TileItem)));
-  b->d_tdata = qs::device_alloc(rbytes + emb.size() * sizeof(float));
+  b->d_tdata = qs::device_alloc(host.size());
   if (!b->d_titems || !b->d_tdata) return bfail(QS_E_NOMEM, "batch tile tables");
-  std::vector<unsigned char> host(rbytes + emb.size() * sizeof(float), 0);
   std::memcpy(host.data(), rtab.data(), rtab.size() * sizeof(int32_t));
-  std::memcpy(host.data() + rbytes, emb.data(), emb.size() * sizeof(float));
+  if (!emb.empty()) std::memcpy(host.data() + b->temb_off, emb.data(), emb.size() * sizeof(float));
+  if (!mats.empty())
+    std::memcpy(host.data() + b->tmats_off, mats.data(), mats.size() * sizeof(float));
   hipError_t e = hipMemcpy(b->d_titems, items.data(), items.size() * sizeof(qs::TileItem),
                            hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(b->d_tdata, host.data(), host.size(), hipMemcpyHostToDevice);
@@ -284,10 +305,17 @@ int prepare(qs_batch* b, qs_circuit* const* circs, int kmax) {
 hipError_t enqueue(qs_batch* b) {
   for (const Launch& L : b->launches) {
     if (L.tile) {
-      const hipError_t e = qs::launch_tile_mfma_batch(
-          static_cast<float*>(b->arena), b->d_titems + L.item0, L.nitems, L.tiles, b->d_tdata,
-          reinterpret_cast<const float*>(static_cast<const char*>(b->d_tdata) + b->tmats_off),
-          b->stream);
+      const char* data = static_cast<const char*>(b->d_tdata);
+      const hipError_t e =
+          L.mode == qs::TileMode::kPairs
+              ? qs::launch_tile_pair_batch(static_cast<float*>(b->arena), b->d_titems + L.item0,
+                                           L.nitems, L.tiles, data,
+                                           reinterpret_cast<const float*>(data + b->tmats_off),
+                                           b->stream)
+              : qs::launch_tile_mfma_batch(static_cast<float*>(b->arena), b->d_titems + L.item0,
+                                           L.nitems, L.tiles, data,
+                                           reinterpret_cast<const float*>(data + b->temb_off),
+                                           b->stream);
       if (e != hipSuccess) return e;
       continue;
     }

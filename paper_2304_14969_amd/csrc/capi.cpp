@@ -935,7 +935,9 @@ int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   const int prec = st->dtype == QS_C64 ? 0 : 1;
   qs_circuit::TileCache& tc = c->tcache[prec];
   std::vector<int> key(st->perm, st->perm + st->n);
-  if (tc.dev && tc.key == key && tc.plan.dense == (st->dtype == QS_C64 && g_tile_mfma) &&
+  const qs::TileMode mode = st->dtype == QS_C64 && g_tile_mfma ? qs::matrix_tile_mode(c->gates)
+                                                               : qs::TileMode::kSparse;
+  if (tc.dev && tc.key == key && tc.plan.mode == mode &&
       tc.plan.C == qs::tile_low_bits(st->dtype)) {
     *out = &tc;
     return QS_OK;
@@ -948,8 +950,7 @@ int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   std::vector<qs::Gate> phys = c->gates;
   for (auto& g : phys)
     for (int j = 0; j < g.k; ++j) g.q[j] = st->perm[g.q[j]];
-  const bool dense = st->dtype == QS_C64 && g_tile_mfma;
-  tc.plan = qs::plan_tiles(phys, st->n, qs::tile_low_bits(st->dtype), qs::kTileRowBits, 4, dense);
+  tc.plan = qs::plan_tiles(phys, st->n, qs::tile_low_bits(st->dtype), qs::kTileRowBits, 4, mode);
   std::vector<unsigned char> host;
   size_t gates_at = 0, mats_at = 0, emb_at = 0;
   qs::tile_tables(tc.plan, prec == 0, &host, &gates_at, &mats_at, &emb_at);
@@ -985,7 +986,11 @@ int run_tiles(qs_state* st, qs_circuit* c) {
       for (int j = 0; j < qs::kTileRowBits; ++j) rows.b[j] = stp.hb[j];
       const void* rd = base + size_t(stp.r0) * 4 * sizeof(int32_t);
       const void* gt = base + tc->gates_off;
-      if (tc->plan.dense) {
+      if (tc->plan.mode == qs::TileMode::kPairs) {
+        ProfScope ps(st, "tile_mfma", bytes);
+        e = qs::launch_tile_pair(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd, stp.nr,
+                                 reinterpret_cast<const float*>(base + tc->mats_off), st->stream);
+      } else if (tc->plan.mode == qs::TileMode::kDense) {
         ProfScope ps(st, "tile_mfma", bytes);
         e = qs::launch_tile_mfma(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd,
                                  stp.nr, reinterpret_cast<const float*>(base + tc->emb_off),

@@ -406,13 +406,118 @@ struct PassPicker {
 
 }  // namespace
 
-TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W, bool dense) {
+TileMode matrix_tile_mode(const std::vector<Gate>& gates) {
+  for (const auto& g : gates)
+    if (g.k > 2) return TileMode::kDense;
+  return TileMode::kPairs;
+}
+
+namespace {
+
+// The rounds of a pass of gates of one or two qubits on tile bits tq[i], as
+// pairs: each round takes two of the ready gates, those with the longest
+// chains of later gates on their qubits. One-qubit gates (their qubits have no
+// other gate in the pass) are joined two by two first.
+void pair_rounds(TilePlan* plan, const std::vector<Gate>& gates, const std::vector<int>& pass,
+                 const std::vector<std::vector<int>>& tq, int tile_bits) {
+  struct Op { int a, b; std::vector<cd> m; };
+  std::vector<Op> ops;
+  int single = -1;  // a one-qubit gate waiting for another
+  for (size_t i = 0; i < pass.size(); ++i) {
+    const Gate& g = gates[pass[i]];
+    if (g.k == 2) {
+      ops.push_back({tq[i][0], tq[i][1], g.m});
+    } else if (single < 0) {
+      single = int(i);
+    } else {
+      Op o{tq[single][0], tq[i][0], eye(2)};
+      const int bit0 = 0, bit1 = 1;
+      left_apply(o.m, 2, gates[pass[single]].m, 1, &bit0);
+      left_apply(o.m, 2, g.m, 1, &bit1);
+      ops.push_back(std::move(o));
+      single = -1;
+    }
+  }
+  std::vector<int> last(tile_bits, -1);
+  std::vector<int> need(ops.size(), 0), height(ops.size(), 1);
+  std::vector<std::vector<int>> after(ops.size());
+  for (size_t i = 0; i < ops.size(); ++i)
+    for (int q : {ops[i].a, ops[i].b}) {
+      if (last[q] >= 0) after[last[q]].push_back(int(i)), ++need[i];
+      last[q] = int(i);
+    }
+  for (size_t i = ops.size(); i-- > 0;)
+    for (int j : after[i]) height[i] = std::max(height[i], height[j] + 1);
+  std::vector<int> ready;
+  for (size_t i = 0; i < ops.size(); ++i)
+    if (!need[i]) ready.push_back(int(i));
+  auto emit = [&](const Op* o1, const Op* o2) {
+    TileRound r;
+    r.g0 = int(plan->gates.size());
+    int nb = 0;
+    for (const Op* o : {o1, o2}) {
+      if (!o) continue;
+      TileGate tg;
+      tg.kind = 2;
+      tg.j1 = nb;
+      tg.j2 = nb + 1;
+      tg.mat = plan->mats.size();
+      plan->mats.insert(plan->mats.end(), o->m.begin(), o->m.end());
+      plan->gates.push_back(tg);
+      r.bits[nb++] = o->a;
+      r.bits[nb++] = o->b;
+    }
+    r.ng = nb / 2;
+    for (int b = 0; nb < 4; ++b)
+      if (std::find(r.bits, r.bits + nb, b) == r.bits + nb) r.bits[nb++] = b;
+    plan->rounds.push_back(r);
+  };
+  // the last one-qubit gate joins a round that has room, or takes one of its own
+  Op alone;
+  bool waiting = single >= 0;
+  if (waiting) {
+    const int q = tq[single][0], bit0 = 0;
+    alone = {q, -1, eye(2)};
+    left_apply(alone.m, 2, gates[pass[single]].m, 1, &bit0);
+  }
+  auto give_partner = [&](const Op* o) {
+    for (int b = 0; alone.b < 0; ++b)
+      if (b != alone.a && !(o && (b == o->a || b == o->b))) alone.b = b;
+  };
+  while (!ready.empty()) {
+    std::stable_sort(ready.begin(), ready.end(),
+                     [&](int x, int y) { return height[x] > height[y]; });
+    const int i = ready[0], j = ready.size() > 1 ? ready[1] : -1;
+    if (j < 0 && waiting && ops[i].a != alone.a && ops[i].b != alone.a) {
+      give_partner(&ops[i]);
+      emit(&ops[i], &alone);
+      waiting = false;
+    } else {
+      emit(&ops[i], j >= 0 ? &ops[j] : nullptr);
+    }
+    ready.erase(ready.begin(), ready.begin() + (j >= 0 ? 2 : 1));
+    for (int x : {i, j}) {
+      if (x < 0) continue;
+      for (int y : after[x])
+        if (!--need[y]) ready.push_back(y);
+    }
+  }
+  if (waiting) {
+    give_partner(nullptr);
+    emit(&alone, nullptr);
+  }
+}
+
+}  // namespace
+
+TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W, TileMode mode) {
   const std::vector<Gate> gates = merge_gates(circuit, n);
   TilePlan plan;
   plan.C = C;
   plan.H = H;
   plan.W = W;
-  plan.dense = dense;
+  plan.mode = mode;
+  const bool dense = mode == TileMode::kDense;
   std::vector<std::vector<int>> qb(gates.size());
   for (size_t i = 0; i < gates.size(); ++i) qb[i].assign(gates[i].q, gates[i].q + gates[i].k);
   PassPicker picker(gates, n, dense ? W : 2);
@@ -458,6 +563,12 @@ TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W
     std::vector<std::vector<int>> tq(pass.size());
     for (size_t i = 0; i < pass.size(); ++i)
       for (int x : qb[pass[i]]) tq[i].push_back(tbit[x]);
+    if (mode == TileMode::kPairs) {
+      pair_rounds(&plan, gates, pass, tq, C + H);
+      st.nr = int(plan.rounds.size()) - st.r0;
+      plan.steps.push_back(st);
+      continue;
+    }
     DagCursor rd(tq, C + H);
     while (rd.remaining) {
       std::vector<int> rb;
@@ -538,12 +649,28 @@ TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W
   return plan;
 }
 
+void pair_round_entry(const TilePlan& pl, const TileRound& r, int32_t row[4]) {
+  int asc[4];
+  std::copy(r.bits, r.bits + 4, asc);
+  std::sort(asc, asc + 4);
+  row[0] = r.bits[0] | (r.bits[1] << 8) | (r.bits[2] << 16) | (r.bits[3] << 24);
+  row[1] = asc[0] | (asc[1] << 8) | (asc[2] << 16) | (asc[3] << 24);
+  row[2] = int32_t(2 * pl.gates[r.g0].mat);
+  row[3] = r.ng > 1 ? int32_t(2 * pl.gates[r.g0 + 1].mat) : -1;
+}
+
 void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, size_t* gates_off,
                  size_t* mats_off, size_t* emb_off) {
-  const bool dense = pl.dense;
+  const bool dense = pl.mode == TileMode::kDense;
   std::vector<int32_t> tab;
   for (size_t ri = 0; ri < pl.rounds.size(); ++ri) {
     const auto& r = pl.rounds[ri];
+    if (pl.mode == TileMode::kPairs) {
+      int32_t row[4];
+      pair_round_entry(pl, r, row);
+      tab.insert(tab.end(), row, row + 4);
+      continue;
+    }
     tab.push_back(r.bits[0] | (r.bits[1] << 8) | (r.bits[2] << 16) | (r.bits[3] << 24));
     tab.push_back(dense ? int32_t(ri * kRoundOperands) : r.g0);
     tab.push_back(r.ng);
@@ -723,7 +850,9 @@ int qs_circuit_tile_info(const qs_circuit* c, int dtype, int* passes, int* block
   if (dtype != QS_C64 && dtype != QS_C128) return cfail(QS_E_INVAL, "unknown dtype %d", dtype);
   const int C = qs::tile_low_bits(dtype);
   if (c->n < C + 7) return cfail(QS_E_UNSUPPORTED, "%d qubits: fewer than one tile (%d)", c->n, C + 7);
-  const qs::TilePlan pl = qs::plan_tiles(c->gates, c->n, C, 7, 4, dtype == QS_C64);
+  const qs::TilePlan pl =
+      qs::plan_tiles(c->gates, c->n, C, 7, 4,
+                     dtype == QS_C64 ? qs::matrix_tile_mode(c->gates) : qs::TileMode::kSparse);
   if (passes) *passes = pl.passes();
   if (blocks) *blocks = int(pl.steps.size()) - pl.passes();
   if (rounds) *rounds = int(pl.rounds.size());

@@ -48,8 +48,9 @@ struct TileGate {
   size_t mat = 0;    // offset of the matrix in TilePlan::mats (complex entries)
 };
 struct TileRound {
-  int bits[4] = {0, 0, 0, 0};  // tile bits of the round, ascending
-  int g0 = 0, ng = 0;          // its gates in TilePlan::gates (sparse rounds)
+  int bits[4] = {0, 0, 0, 0};  // tile bits of the round, ascending (pairs: the
+                               // first gate's two, then the second's)
+  int g0 = 0, ng = 0;          // its gates in TilePlan::gates (not dense)
   size_t mat = 0;              // dense rounds: offset of the 16x16 product in mats
 };
 struct TileStep {
@@ -60,9 +61,14 @@ struct TileStep {
   Block blk;           // block step, on physical bits
   size_t mat = 0;      // block step: offset of its matrix
 };
+// What the rounds of a plan hold: gates of one or two qubits on any of the
+// round's bits (kSparse); one or two gates on disjoint pairs, the first on the
+// round's bits 0 and 1, the second on 2 and 3 (kPairs); one dense product of
+// gates of at most W qubits (kDense).
+enum class TileMode { kSparse, kPairs, kDense };
 struct TilePlan {
   int C = 0, H = 0, W = 0;
-  bool dense = false;  // rounds are dense W-qubit blocks (any gate of <= W qubits)
+  TileMode mode = TileMode::kSparse;
   std::vector<TileStep> steps;
   std::vector<TileRound> rounds;
   std::vector<TileGate> gates;
@@ -78,22 +84,31 @@ struct TilePlan {
 // state of n >= C + H qubits. One-qubit gates are first multiplied into wider
 // neighbours. A pass takes every gate the dependence order lets it run inside
 // the low bits plus at most H other bits, which are chosen to let many gates
-// run (PassPicker in circuit.cpp). Rounds are formed greedily within a pass,
-// W bits each. Sparse rounds (dense =
-// false) hold gates of one or two qubits; dense rounds hold any gate of at most W qubits and carry the product of their
-// gates. Larger gates run as dense blocks between passes.
-TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, bool dense);
+// run (PassPicker in circuit.cpp). Within a pass, sparse and dense rounds are
+// formed greedily, W bits each; pair rounds take the two ready gates with the
+// longest chains of gates behind them. Gates too wide for a round (more than
+// two qubits, or more than W for dense rounds) run as blocks between passes.
+TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, TileMode mode);
+
+// Rounds of complex64 passes on the matrix cores: pairs, or dense products
+// when the circuit has gates of more than two qubits (so that they still join
+// the passes).
+TileMode matrix_tile_mode(const std::vector<Gate>& gates);
 
 // The device tables of a plan, as one byte image: per round an int4 {bits
 // packed by byte, first gate (sparse) or embedding offset in floats (dense),
-// gate count, 0}; per gate (sparse) an int2 {kind | j1 << 4 | j2 << 8, offset
+// gate count, 0}, or for pairs {bits packed by byte, the same bits ascending,
+// offsets in reals of the two gates' matrices, -1 for none}; per gate an int2 {kind | j1 << 4 | j2 << 8, offset
 // of its matrix in reals}; at emb_off (dense) the rounds' 32 x 32 embeddings
 // in lane order (float); at mats_off the plan's matrices (float or double
 // pairs). Offsets are bytes from the start.
 void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, size_t* gates_off,
                  size_t* mats_off, size_t* emb_off);
 
-// The operands a matrix-core round reads, for the three real products of
+// A pair round's table entry (int4 as above).
+void pair_round_entry(const TilePlan& pl, const TileRound& r, int32_t row[4]);
+
+// The operands a dense matrix-core round reads, for the three real products of
 // Re U X_r, Im U X_i and (Re U + Im U)(X_r + X_i) of a 16 x 16 complex round
 // matrix u (16 x 16 x 4 MFMA A-operand layout): out[(3 s + c) * 64 + lane] =
 // W_c[lane % 16][4 s + lane / 16] with W_0 = Re U, W_1 = Im U,

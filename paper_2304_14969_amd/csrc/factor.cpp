@@ -1708,7 +1708,7 @@ int large_1q_run(FactorState* f, int si, const int* qubits, const double* m,
       for (int e = 0; e < 4; ++e)
         g.m[e] = cd(m[8 * list[i] + 2 * e], m[8 * list[i] + 2 * e + 1]);
     }
-    const TilePlan pl = plan_tiles(gl, S.nq, kLow, kTileRowBits, 4, false);
+    const TilePlan pl = plan_tiles(gl, S.nq, kLow, kTileRowBits, 4, TileMode::kSparse);
     std::vector<unsigned char> tab;
     size_t goff = 0, moff = 0, eoff = 0;
     tile_tables(pl, sizeof(R) == 4, &tab, &goff, &moff, &eoff);

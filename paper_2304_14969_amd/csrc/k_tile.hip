@@ -5,14 +5,14 @@
 // amplitudes) and H = 7 row bits chosen by the planner (complex64: C = 5 by
 // default, 256-byte rows and 32 KiB tiles, 4 or 6 by knob; complex128: C = 4,
 // 256-byte rows, 32 KiB). The tile is staged
-// in LDS (one complex of padding every 16 entries) and transformed round by
-// round, each round acting on 4 tile bits. Complex64 rounds are dense 4-qubit
-// blocks on the matrix cores (k_tile_mfma), each complex product as three
-// real ones (Re U X_r, Im U X_i and (Re U + Im U)(X_r + X_i), 16 x 16 x 4
-// MFMAs: 3/4 of the flops of the 32 x 32 real embedding); complex128 rounds
-// (k_tile_pass) gather, per thread, the 16 amplitudes that differ in the round's bits and
-// apply the round's one- and two-qubit gates in registers (the gate's bits
-// inside the round select a compile-time form).
+// in LDS and transformed round by round, each round acting on 4 tile bits.
+// Three forms of rounds: two two-qubit gates on the FP32 matrix cores
+// (k_tile_pair, complex64 circuits of one- and two-qubit gates); a dense
+// 4-qubit block on the matrix cores (k_tile_mfma, complex64 circuits with
+// gates of three or four qubits), each complex product as three real ones
+// (Re U X_r, Im U X_i and (Re U + Im U)(X_r + X_i), 16 x 16 x 4 MFMAs: 3/4 of
+// the flops of the 32 x 32 real embedding); one- and two-qubit gates one by
+// one in registers (k_tile_pass, complex128).
 #include "qs_internal.h"
 
 namespace qs {
@@ -186,6 +186,185 @@ __global__ void __launch_bounds__(1 << (C + H - kW))
   }
 }
 
+// ---- rounds of two two-qubit gates on the FP32 matrix cores
+// Thread x owns one group of a round, its 16 amplitudes in registers; the
+// round's first gate acts on bits 0 and 1 of the group, the second on bits 2
+// and 3, each a 4 x 4 complex matrix on four quadruples. v_mfma_f32_4x4x1_16b
+// multiplies, in each block of four lanes, a column of a 4 x 4 matrix (lane i
+// of the block supplies row i) by the block's row of four inputs (lane j
+// supplies its own amplitude) and leaves row r of the product in result
+// register r of the lane it belongs to: one instruction adds an amplitude's
+// products into its four outputs for 64 groups and nothing crosses lanes. The
+// four registers of a first-gate result are inputs of four second-gate
+// quadruples, so no register moves.
+//
+// Two-qubit gates fill a random circuit, and a dense 16 x 16 round holding two
+// of them spends 48 instructions of 32 cycles on what takes 128 of 8 here; the
+// vector instructions share the FP32 matrix unit (a loop of both takes the sum
+// of their times), so a round's other instructions count as much: the tile is
+// kept as a plane of real and a plane of imaginary parts, which load and store
+// without packing moves, and the loop runs two rounds at a time so that
+// prefetched matrix rows need no copies. 8-layer circuits against the dense
+// rounds: 37.7 -> 27.9 us at 12 qubits, 119 -> 99 at 20, 861 -> 709 at 24
+// (states in the last-level cache; the passes alone 353), 16.8 -> 14.3 ms at
+// 28 (11.7).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Row lane % 4 of a gate's matrix: the A operands of its four columns.
+struct PairRow {
+  float re[4], im[4];
+};
+
+// y = U x on four quadruples; x(h, c) is input c of quadruple h, output row i
+// of it is (yr[h][i], yi[h][i]).
+template <typename In>
+__device__ __forceinline__ void pair_gate(const PairRow& u, In x, f32x4 (&yr)[4], f32x4 (&yi)[4]) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float nim = -u.im[c];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const float2 v = x(h, c);
+      const f32x4 r = c ? yr[h] : f32x4{}, i = c ? yi[h] : f32x4{};
+      yr[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(u.re[c], v.x, r, 0, 0, 0);
+      yi[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(u.re[c], v.y, i, 0, 0, 0);
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const float2 v = x(h, c);
+      yr[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(nim, v.y, yr[h], 0, 0, 0);
+      yi[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(u.im[c], v.x, yi[h], 0, 0, 0);
+    }
+  }
+}
+
+__device__ __forceinline__ int insert_zero32(int x, int pos) {
+  const int lo = x & ((1 << pos) - 1);
+  return lo | ((x ^ lo) << 1);
+}
+
+// Dword of tile index x in a plane of the LDS tile (one dword of padding every
+// 32), and the length of a plane (a multiple of 64).
+__device__ __forceinline__ int plane_pos(int x) { return x + (x >> 5); }
+template <int TB> constexpr int kPlane = (1 << TB) + ((1 << TB) >> 5) + 63 & ~63;
+
+template <int C, int H, bool STREAM>
+__device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t base,
+                                               const TileRows& rows,
+                                               const int4* __restrict__ rounds, int nrounds,
+                                               const float* __restrict__ mats) {
+  constexpr int TB = C + H;
+  constexpr int NT = 1 << (TB - kW);
+  constexpr int VPR = (1 << C) / 2;        // float4 vectors per row
+  constexpr int NV = (1 << TB) / 2 / NT;   // vectors per thread
+  constexpr int RT = NT / VPR;             // tile rows between a thread's vectors
+  constexpr int RTB = __builtin_ctz(RT);
+  static_assert(RT * VPR == NT && RTB <= H, "tile shape");
+  extern __shared__ unsigned char smraw[];
+  float* re = reinterpret_cast<float*>(smraw);  // real parts, then imaginary ones
+  float* im = re + kPlane<TB>;
+  const int r0 = int(threadIdx.x) / VPR;
+  uint64_t off_t = base | uint64_t((int(threadIdx.x) % VPR) * 2);
+#pragma unroll
+  for (int j = 0; j < RTB; ++j) off_t |= uint64_t((r0 >> j) & 1) << rows.b[j];
+  auto glob_k = [&](int k) {
+    uint64_t g = off_t;
+#pragma unroll
+    for (int j = RTB; j < H; ++j)
+      if (((k * RT) >> j) & 1) g |= uint64_t(1) << rows.b[j];
+    return g;
+  };
+  float4* p4 = reinterpret_cast<float4*>(a);
+  // this lane's rows of a round's matrices (a missing second gate reads the
+  // first one's again)
+  const float* lane_row = mats + 8 * (threadIdx.x & 3);
+  auto load_row = [&](int off) {
+    const float4 x = *reinterpret_cast<const float4*>(lane_row + off);
+    const float4 y = *reinterpret_cast<const float4*>(lane_row + off + 4);
+    return PairRow{{x.x, x.z, y.x, y.z}, {x.y, x.w, y.y, y.w}};
+  };
+  // A round's entry is loaded two rounds ahead, its matrix rows one ahead.
+  struct Round {
+    int bits, asc, second;
+    PairRow m1, m2;
+  };
+  auto entry = [&](int r) { return rounds[r < nrounds ? r : nrounds - 1]; };
+  auto load_round = [&](int4 e) {
+    return Round{e.x, e.y, e.w, load_row(e.z), load_row(e.w < 0 ? e.z : e.w)};
+  };
+  int4 next = entry(1);
+  Round ra = load_round(entry(0));
+  {
+    float4 buf[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) buf[k] = ld16<STREAM>(p4 + glob_k(k) / 2);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int e = threadIdx.x + k * NT;
+      const int x = ((e / VPR) << C) | (e % VPR) * 2;
+      re[plane_pos(x)] = buf[k].x;
+      im[plane_pos(x)] = buf[k].y;
+      re[plane_pos(x) + 1] = buf[k].z;
+      im[plane_pos(x) + 1] = buf[k].w;
+    }
+  }
+  __syncthreads();
+  auto step = [&](const Round& rd) {
+    int x0 = threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x0 = insert_zero32(x0, (rd.asc >> (8 * j)) & 255);
+    const int px = plane_pos(x0);
+    int d[4];  // LDS offset of each round bit; plane_pos adds over disjoint bits
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = plane_pos(1 << ((rd.bits >> (8 * j)) & 255));
+    auto at = [&](int m) {
+      return px + ((m & 1) ? d[0] : 0) + ((m & 2) ? d[1] : 0) + ((m & 4) ? d[2] : 0) +
+             ((m & 8) ? d[3] : 0);
+    };
+    float2 v[kV];
+#pragma unroll
+    for (int m = 0; m < kV; ++m) v[m] = make_float2(re[at(m)], im[at(m)]);
+    f32x4 yr[4], yi[4];
+    pair_gate(rd.m1, [&](int h, int c) { return v[4 * h + c]; }, yr, yi);
+    if (rd.second >= 0) {
+      f32x4 zr[4], zi[4];
+      pair_gate(rd.m2, [&](int l, int c) { return make_float2(yr[c][l], yi[c][l]); }, zr, zi);
+#pragma unroll
+      for (int m = 0; m < kV; ++m) re[at(m)] = zr[m & 3][m >> 2], im[at(m)] = zi[m & 3][m >> 2];
+    } else {
+#pragma unroll
+      for (int m = 0; m < kV; ++m) re[at(m)] = yr[m >> 2][m & 3], im[at(m)] = yi[m >> 2][m & 3];
+    }
+    __syncthreads();
+  };
+  for (int r = 0; r < nrounds; r += 2) {  // two by two: the rows need no copies
+    const Round rb = load_round(next);
+    next = entry(r + 2);
+    step(ra);
+    if (r + 1 == nrounds) break;
+    ra = load_round(next);
+    next = entry(r + 3);
+    step(rb);
+  }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int e = threadIdx.x + k * NT;
+    const int x = ((e / VPR) << C) | (e % VPR) * 2;
+    const int l = plane_pos(x);
+    st16<STREAM>(p4 + glob_k(k) / 2, make_float4(re[l], im[l], re[l + 1], im[l + 1]));
+  }
+}
+
+template <int C, int H, bool STREAM>
+__global__ void __launch_bounds__(1 << (C + H - kW)) __attribute__((amdgpu_waves_per_eu(4)))
+    k_tile_pair(float* __restrict__ a, TileRows rows, const int4* __restrict__ rounds,
+                int nrounds, const float* __restrict__ mats) {
+  uint64_t base = uint64_t(blockIdx.x) << C;
+#pragma unroll
+  for (int j = 0; j < H; ++j) base = insert_zero(base, rows.b[j]);
+  tile_pair_body<C, H, STREAM>(a, base, rows, rounds, nrounds, mats);
+}
+
 // Complex64 passes whose rounds are dense 4-qubit blocks on the FP32 matrix
 // cores. A round multiplies the 16 amplitudes of every group (the other 9
 // tile bits) by the round's 16x16 complex matrix U, as a real GEMM on the
@@ -194,7 +373,6 @@ __global__ void __launch_bounds__(1 << (C + H - kW))
 // group, lane / 32 = real or imaginary part), one K-step per input amplitude.
 // `amats` holds each round's embedding in lane order: entry ks * 64 + lane =
 // Uemb[lane % 32][2 ks + lane / 32].
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 // matrix-core operands of a round per lane: Re U, Im U, Re U + Im U for 4 K-steps
 constexpr int kOps = 12;
 static_assert(kOps * 64 == kRoundOperands, "round operand layout");
@@ -341,9 +519,8 @@ __global__ void __launch_bounds__(1 << (C + H - kW))
 // Many kets at once: workgroup -> item by binary search over the items'
 // first tiles; each item is one pass of one ket of the arena.
 template <int C, int H>
-__global__ void __launch_bounds__(1 << (C + H - kW))
-    k_tile_mfma_batch(float* __restrict__ arena, const TileItem* __restrict__ items, int nitems,
-                      const int4* __restrict__ rounds, const float* __restrict__ amats) {
+__device__ __forceinline__ const TileItem& batch_item(const TileItem* __restrict__ items, int nitems,
+                                                      uint64_t* base) {
   int lo = 0, hi = nitems - 1;
   const uint64_t b = blockIdx.x;
   while (lo < hi) {
@@ -352,11 +529,29 @@ __global__ void __launch_bounds__(1 << (C + H - kW))
     else hi = mid - 1;
   }
   const TileItem& it = items[lo];
-  uint64_t base = (b - it.first_tile) << C;
+  *base = (b - it.first_tile) << C;
 #pragma unroll
-  for (int j = 0; j < H; ++j) base = insert_zero(base, it.rows.b[j]);
+  for (int j = 0; j < H; ++j) *base = insert_zero(*base, it.rows.b[j]);
+  return it;
+}
+
+template <int C, int H>
+__global__ void __launch_bounds__(1 << (C + H - kW))
+    k_tile_mfma_batch(float* __restrict__ arena, const TileItem* __restrict__ items, int nitems,
+                      const int4* __restrict__ rounds, const float* __restrict__ amats) {
+  uint64_t base;
+  const TileItem& it = batch_item<C, H>(items, nitems, &base);
   tile_mfma_body<C, H, false>(arena + 2 * it.amp_off, base, it.rows, rounds + it.r0, it.nr,
                               amats);
+}
+
+template <int C, int H>
+__global__ void __launch_bounds__(1 << (C + H - kW)) __attribute__((amdgpu_waves_per_eu(4)))
+    k_tile_pair_batch(float* __restrict__ arena, const TileItem* __restrict__ items, int nitems,
+                      const int4* __restrict__ rounds, const float* __restrict__ mats) {
+  uint64_t base;
+  const TileItem& it = batch_item<C, H>(items, nitems, &base);
+  tile_pair_body<C, H, false>(arena + 2 * it.amp_off, base, it.rows, rounds + it.r0, it.nr, mats);
 }
 
 }  // namespace
@@ -381,6 +576,35 @@ hipError_t launch_mfma_c(float* a, int n, const TileRows& rows, const void* roun
 }
 }  // namespace
 
+
+namespace {
+template <int C>
+hipError_t launch_pair_c(float* a, int n, const TileRows& rows, const void* rounds, int nrounds,
+                         const float* mats, hipStream_t s) {
+  constexpr int H = kTileRowBits, TB = C + H;
+  if (n < TB || nrounds < 1) return hipErrorInvalidValue;
+  for (int j = 0; j < H; ++j)
+    if (rows.b[j] < C || rows.b[j] >= n || (j > 0 && rows.b[j] <= rows.b[j - 1]))
+      return hipErrorInvalidValue;
+  const size_t bytes = 2 * size_t(kPlane<TB>) * sizeof(float);
+  auto kern = stream_sweep(n, 8, C) ? k_tile_pair<C, H, true> : k_tile_pair<C, H, false>;
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+  hipLaunchKernelGGL(kern, dim3(unsigned(uint64_t(1) << (n - TB))), dim3(1 << (TB - kW)), bytes, s,
+                     a, rows, static_cast<const int4*>(rounds), nrounds, mats);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_tile_pair(float* a, int n, int low_bits, const TileRows& rows,
+                            const void* rounds, int nrounds, const float* mats, hipStream_t s) {
+  switch (low_bits) {
+    case 4: return launch_pair_c<4>(a, n, rows, rounds, nrounds, mats, s);
+    case 5: return launch_pair_c<5>(a, n, rows, rounds, nrounds, mats, s);
+    case 6: return launch_pair_c<6>(a, n, rows, rounds, nrounds, mats, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 hipError_t launch_tile_mfma(float* a, int n, int low_bits, const TileRows& rows,
                             const void* rounds, int nrounds, const float* amats, hipStream_t s) {
@@ -444,6 +668,19 @@ hipError_t launch_tile_mfma_batch(float* arena, const TileItem* items, int nitem
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
   hipLaunchKernelGGL(kern, dim3(unsigned(tiles)), dim3(1 << (TB - kW)), bytes, s, arena, items,
                      nitems, static_cast<const int4*>(rounds), amats);
+  return hipGetLastError();
+}
+
+hipError_t launch_tile_pair_batch(float* arena, const TileItem* items, int nitems, uint64_t tiles,
+                                  const void* rounds, const float* mats, hipStream_t s) {
+  constexpr int C = kBatchTileLow, H = kTileRowBits, TB = C + H;
+  if (nitems < 1 || tiles < 1 || tiles > 0x7fffffffu) return hipErrorInvalidValue;
+  const size_t bytes = 2 * size_t(kPlane<TB>) * sizeof(float);
+  auto kern = k_tile_pair_batch<C, H>;
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+  hipLaunchKernelGGL(kern, dim3(unsigned(tiles)), dim3(1 << (TB - kW)), bytes, s, arena, items,
+                     nitems, static_cast<const int4*>(rounds), mats);
   return hipGetLastError();
 }
 

@@ -60,3 +60,21 @@ def test_gate_lists(qs_lib, dtype, n, name, mfma):
         c.free()
     finally:
         qs_lib.tune_set("tile.mfma", saved)
+
+
+def test_batch_of_every_kind(qs_lib):
+    """One batch whose kets run as passes of pair rounds, passes of dense
+    rounds (gates of three and four qubits) and block launches (wider gates)."""
+    n = [12, 13, 12, 14, 13, 12]
+    names = ["one and two", "up to four", "up to six", "chain", "one-qubit only", "up to four"]
+    g = np.random.default_rng(5)
+    lists = [LISTS[k](w, g) for k, w in zip(names, n)]
+    lists = [[x for x in gates if len(x[1]) < 6] for gates in lists]  # batched blocks: 5 qubits
+    b = qs_lib.Batch(n, C64)
+    b.run([qs_lib.Circuit(w).add_gates(x) for w, x in zip(n, lists)], 5)
+    for i, (w, gates) in enumerate(zip(n, lists)):
+        want = dense.zero_state(w)
+        for _, qubits, m in gates:
+            want = dense.apply_matrix(want, w, qubits, m)
+        assert_parity(b.amplitudes(i), want, C64, f"ket {i} {names[i]}")
+    b.free()
