@@ -404,7 +404,10 @@ int qs_circuit_plan(qs_circuit* c, int kmax);
  * the state's labelling differs). Gates too wide for a round (more than 4
  * qubits with "tile.mfma" on, more than 2 otherwise or for complex128) run
  * as dense blocks between passes. States with fewer qubits than a tile (its
- * low bits + 7) use fused blocks. Same results as the block path up to float rounding order. */
+ * low bits + 7) run whole in the LDS of one workgroup, the circuit in one
+ * launch, when every gate has at most two qubits ("tile.mfma" on for
+ * complex64), and as fused blocks otherwise. Same results as the block path
+ * up to float rounding order. */
 int qs_circuit_use_tiles(qs_circuit* c, int on);
 /* Tile plan of the circuit for a state in the identity labelling (current
  * "tile.*" knobs): passes,

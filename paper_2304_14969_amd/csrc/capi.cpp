@@ -929,16 +929,30 @@ int qs_circuit_free(qs_circuit* c) {
 
 namespace {
 
+// A state smaller than a tile whose circuit has only one- and two-qubit gates
+// runs whole in the LDS of one workgroup (on the matrix cores in complex64,
+// so not with "tile.mfma" off).
+bool runs_whole(const qs_state* st, const qs_circuit* c) {
+  if (st->n > (st->dtype == QS_C64 ? 11 : 10) ||
+      st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits)
+    return false;
+  if (st->dtype == QS_C64 && !g_tile_mfma) return false;
+  return qs::matrix_tile_mode(c->gates) == qs::TileMode::kPairs;
+}
+
 // The tile plan of circuit c for the state's precision and current labelling
 // (planned on physical bits), uploaded once and cached in the circuit.
 int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   const int prec = st->dtype == QS_C64 ? 0 : 1;
   qs_circuit::TileCache& tc = c->tcache[prec];
+  const bool whole = runs_whole(st, c);
+  const int bits = whole ? qs::whole_bits(st->n) : st->n;
+  const int low = whole ? bits - qs::kTileRowBits : qs::tile_low_bits(st->dtype);
   std::vector<int> key(st->perm, st->perm + st->n);
   const qs::TileMode mode = st->dtype == QS_C64 && g_tile_mfma ? qs::matrix_tile_mode(c->gates)
                                                                : qs::TileMode::kSparse;
   if (tc.dev && tc.key == key && tc.plan.mode == mode &&
-      tc.plan.C == qs::tile_low_bits(st->dtype)) {
+      tc.plan.C == low) {
     *out = &tc;
     return QS_OK;
   }
@@ -950,7 +964,7 @@ int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   std::vector<qs::Gate> phys = c->gates;
   for (auto& g : phys)
     for (int j = 0; j < g.k; ++j) g.q[j] = st->perm[g.q[j]];
-  tc.plan = qs::plan_tiles(phys, st->n, qs::tile_low_bits(st->dtype), qs::kTileRowBits, 4, mode);
+  tc.plan = qs::plan_tiles(phys, bits, low, qs::kTileRowBits, 4, mode);
   std::vector<unsigned char> host;
   size_t gates_at = 0, mats_at = 0, emb_at = 0;
   qs::tile_tables(tc.plan, prec == 0, &host, &gates_at, &mats_at, &emb_at);
@@ -976,6 +990,18 @@ int run_tiles(qs_state* st, qs_circuit* c) {
   if (int rc = tile_plan_for(st, c, &tc)) return rc;
   const char* base = static_cast<const char*>(tc->dev);
   const double bytes = 2.0 * std::ldexp(1.0, st->n) * ab(st);
+  if (runs_whole(st, c)) {  // one step with every round
+    ProfScope ps(st, "circuit_lds", bytes);
+    const void* gt = base + tc->gates_off;
+    const int nr = int(tc->plan.rounds.size());
+    const hipError_t e =
+        st->dtype == QS_C64
+            ? qs::launch_whole(static_cast<float*>(st->amps), st->n, base, nr, gt,
+                               reinterpret_cast<const float*>(base + tc->mats_off), st->stream)
+            : qs::launch_whole(static_cast<double*>(st->amps), st->n, base, nr, gt,
+                               reinterpret_cast<const double*>(base + tc->mats_off), st->stream);
+    return device_error(st, e, "circuit in LDS");
+  }
   for (const auto& stp : tc->plan.steps) {
     hipError_t e;
     if (stp.block) {
@@ -1016,7 +1042,8 @@ int run_tiles(qs_state* st, qs_circuit* c) {
 }  // namespace
 
 // Runs a circuit on a dense state as tile passes (unless blocks were chosen;
-// the state must hold one tile's bits) or as planned blocks (planned with
+// the state must hold one tile's bits), in one launch when it is smaller than
+// a tile, or as planned blocks (planned with
 // the default block width first if needed), one sweep each; the circuit's
 // SWAP renaming is then folded into the state's labels. Factorized states
 // apply the gates one by one.
@@ -1257,7 +1284,7 @@ int qs_run(qs_state* st, qs_circuit* c) {
     return fact_rc(st, qs::fact_relabel(f, c->pos.data()));
   }
   if (c->tiles != 0 && !c->gates.empty() &&
-      st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits) {
+      (runs_whole(st, c) || st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits)) {
     if (int rc = run_tiles(st, c)) return rc;
     int np[64];
     for (int q = 0; q < st->n; ++q) np[q] = st->perm[c->pos[q]];

@@ -104,6 +104,38 @@ __device__ __forceinline__ void apply_gate(Cx<R> (&v)[kV], int code, const R* __
   }
 }
 
+// The rounds of a tile staged in LDS (thread x: group x of each round).
+template <typename R>
+__device__ __forceinline__ void gate_rounds(Cx<R>* sm, const int4* __restrict__ rounds, int nrounds,
+                                            const int2* __restrict__ gates,
+                                            const R* __restrict__ mats) {
+  for (int r = 0; r < nrounds; ++r) {
+    const int4 rd = rounds[r];
+    const int b0 = rd.x & 255, b1 = (rd.x >> 8) & 255, b2 = (rd.x >> 16) & 255,
+              b3 = (rd.x >> 24) & 255;
+    int x0 = threadIdx.x;
+    x0 = int(insert_zero(uint64_t(x0), b0));
+    x0 = int(insert_zero(uint64_t(x0), b1));
+    x0 = int(insert_zero(uint64_t(x0), b2));
+    x0 = int(insert_zero(uint64_t(x0), b3));
+    int pos[kV];
+    Cx<R> v[kV];
+#pragma unroll
+    for (int m = 0; m < kV; ++m) {
+      pos[m] = lds_pos(x0 | ((m & 1) << b0) | (((m >> 1) & 1) << b1) | (((m >> 2) & 1) << b2) |
+                       (((m >> 3) & 1) << b3));
+      v[m] = sm[pos[m]];
+    }
+    for (int g = rd.y; g < rd.y + rd.z; ++g) {
+      const int2 gg = gates[g];
+      apply_gate<R>(v, gg.x, mats + gg.y);
+    }
+#pragma unroll
+    for (int m = 0; m < kV; ++m) sm[pos[m]] = v[m];
+    __syncthreads();
+  }
+}
+
 template <typename R, int C, int H, bool STREAM>
 __global__ void __launch_bounds__(1 << (C + H - kW))
     k_tile_pass(R* __restrict__ a, TileRows rows, const int4* __restrict__ rounds, int nrounds,
@@ -145,31 +177,7 @@ __global__ void __launch_bounds__(1 << (C + H - kW))
     }
   }
   __syncthreads();
-  for (int r = 0; r < nrounds; ++r) {
-    const int4 rd = rounds[r];
-    const int b0 = rd.x & 255, b1 = (rd.x >> 8) & 255, b2 = (rd.x >> 16) & 255,
-              b3 = (rd.x >> 24) & 255;
-    int x0 = threadIdx.x;
-    x0 = int(insert_zero(uint64_t(x0), b0));
-    x0 = int(insert_zero(uint64_t(x0), b1));
-    x0 = int(insert_zero(uint64_t(x0), b2));
-    x0 = int(insert_zero(uint64_t(x0), b3));
-    int pos[kV];
-    Cx<R> v[kV];
-#pragma unroll
-    for (int m = 0; m < kV; ++m) {
-      pos[m] = lds_pos(x0 | ((m & 1) << b0) | (((m >> 1) & 1) << b1) | (((m >> 2) & 1) << b2) |
-                       (((m >> 3) & 1) << b3));
-      v[m] = sm[pos[m]];
-    }
-    for (int g = rd.y; g < rd.y + rd.z; ++g) {
-      const int2 gg = gates[g];
-      apply_gate<R>(v, gg.x, mats + gg.y);
-    }
-#pragma unroll
-    for (int m = 0; m < kV; ++m) sm[pos[m]] = v[m];
-    __syncthreads();
-  }
+  gate_rounds<R>(sm, rounds, nrounds, gates, mats);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT;
@@ -248,6 +256,79 @@ __device__ __forceinline__ int insert_zero32(int x, int pos) {
 __device__ __forceinline__ int plane_pos(int x) { return x + (x >> 5); }
 template <int TB> constexpr int kPlane = (1 << TB) + ((1 << TB) >> 5) + 63 & ~63;
 
+// The rounds of a tile staged in LDS (thread x: group x of each round). A
+// round's entry is loaded two rounds ahead, its matrix rows one ahead; the
+// first ones when the object is made, before the tile's own loads.
+struct PairRounds {
+  struct Round {
+    int bits, asc, second;
+    PairRow m1, m2;
+  };
+  const int4* __restrict__ rounds;
+  int nrounds;
+  const float* __restrict__ lane_row;  // this lane's row of the matrix at offset 0
+  int4 next;
+  Round ra;
+
+  __device__ __forceinline__ PairRow load_row(int off) const {
+    const float4 x = *reinterpret_cast<const float4*>(lane_row + off);
+    const float4 y = *reinterpret_cast<const float4*>(lane_row + off + 4);
+    return PairRow{{x.x, x.z, y.x, y.z}, {x.y, x.w, y.y, y.w}};
+  }
+  __device__ __forceinline__ int4 entry(int r) const {
+    return rounds[r < nrounds ? r : nrounds - 1];
+  }
+  // a missing second gate reads the first one's row again
+  __device__ __forceinline__ Round load_round(int4 e) const {
+    return Round{e.x, e.y, e.w, load_row(e.z), load_row(e.w < 0 ? e.z : e.w)};
+  }
+  __device__ __forceinline__ PairRounds(const int4* __restrict__ r, int n,
+                                        const float* __restrict__ mats)
+      : rounds(r), nrounds(n), lane_row(mats + 8 * (threadIdx.x & 3)) {
+    next = entry(1);
+    ra = load_round(entry(0));
+  }
+  __device__ __forceinline__ void step(const Round& rd, float* re, float* im) const {
+    int x0 = threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x0 = insert_zero32(x0, (rd.asc >> (8 * j)) & 255);
+    const int px = plane_pos(x0);
+    int d[4];  // LDS offset of each round bit; plane_pos adds over disjoint bits
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = plane_pos(1 << ((rd.bits >> (8 * j)) & 255));
+    auto at = [&](int m) {
+      return px + ((m & 1) ? d[0] : 0) + ((m & 2) ? d[1] : 0) + ((m & 4) ? d[2] : 0) +
+             ((m & 8) ? d[3] : 0);
+    };
+    float2 v[kV];
+#pragma unroll
+    for (int m = 0; m < kV; ++m) v[m] = make_float2(re[at(m)], im[at(m)]);
+    f32x4 yr[4], yi[4];
+    pair_gate(rd.m1, [&](int h, int c) { return v[4 * h + c]; }, yr, yi);
+    if (rd.second >= 0) {
+      f32x4 zr[4], zi[4];
+      pair_gate(rd.m2, [&](int l, int c) { return make_float2(yr[c][l], yi[c][l]); }, zr, zi);
+#pragma unroll
+      for (int m = 0; m < kV; ++m) re[at(m)] = zr[m & 3][m >> 2], im[at(m)] = zi[m & 3][m >> 2];
+    } else {
+#pragma unroll
+      for (int m = 0; m < kV; ++m) re[at(m)] = yr[m >> 2][m & 3], im[at(m)] = yi[m >> 2][m & 3];
+    }
+    __syncthreads();
+  }
+  __device__ __forceinline__ void run(float* re, float* im) {
+    for (int r = 0; r < nrounds; r += 2) {  // two by two: the rows need no copies
+      const Round rb = load_round(next);
+      next = entry(r + 2);
+      step(ra, re, im);
+      if (r + 1 == nrounds) break;
+      ra = load_round(next);
+      next = entry(r + 3);
+      step(rb, re, im);
+    }
+  }
+};
+
 template <int C, int H, bool STREAM>
 __device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t base,
                                                const TileRows& rows,
@@ -275,25 +356,7 @@ __device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t b
     return g;
   };
   float4* p4 = reinterpret_cast<float4*>(a);
-  // this lane's rows of a round's matrices (a missing second gate reads the
-  // first one's again)
-  const float* lane_row = mats + 8 * (threadIdx.x & 3);
-  auto load_row = [&](int off) {
-    const float4 x = *reinterpret_cast<const float4*>(lane_row + off);
-    const float4 y = *reinterpret_cast<const float4*>(lane_row + off + 4);
-    return PairRow{{x.x, x.z, y.x, y.z}, {x.y, x.w, y.y, y.w}};
-  };
-  // A round's entry is loaded two rounds ahead, its matrix rows one ahead.
-  struct Round {
-    int bits, asc, second;
-    PairRow m1, m2;
-  };
-  auto entry = [&](int r) { return rounds[r < nrounds ? r : nrounds - 1]; };
-  auto load_round = [&](int4 e) {
-    return Round{e.x, e.y, e.w, load_row(e.z), load_row(e.w < 0 ? e.z : e.w)};
-  };
-  int4 next = entry(1);
-  Round ra = load_round(entry(0));
+  PairRounds rr(rounds, nrounds, mats);
   {
     float4 buf[NV];
 #pragma unroll
@@ -309,43 +372,7 @@ __device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t b
     }
   }
   __syncthreads();
-  auto step = [&](const Round& rd) {
-    int x0 = threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) x0 = insert_zero32(x0, (rd.asc >> (8 * j)) & 255);
-    const int px = plane_pos(x0);
-    int d[4];  // LDS offset of each round bit; plane_pos adds over disjoint bits
-#pragma unroll
-    for (int j = 0; j < 4; ++j) d[j] = plane_pos(1 << ((rd.bits >> (8 * j)) & 255));
-    auto at = [&](int m) {
-      return px + ((m & 1) ? d[0] : 0) + ((m & 2) ? d[1] : 0) + ((m & 4) ? d[2] : 0) +
-             ((m & 8) ? d[3] : 0);
-    };
-    float2 v[kV];
-#pragma unroll
-    for (int m = 0; m < kV; ++m) v[m] = make_float2(re[at(m)], im[at(m)]);
-    f32x4 yr[4], yi[4];
-    pair_gate(rd.m1, [&](int h, int c) { return v[4 * h + c]; }, yr, yi);
-    if (rd.second >= 0) {
-      f32x4 zr[4], zi[4];
-      pair_gate(rd.m2, [&](int l, int c) { return make_float2(yr[c][l], yi[c][l]); }, zr, zi);
-#pragma unroll
-      for (int m = 0; m < kV; ++m) re[at(m)] = zr[m & 3][m >> 2], im[at(m)] = zi[m & 3][m >> 2];
-    } else {
-#pragma unroll
-      for (int m = 0; m < kV; ++m) re[at(m)] = yr[m >> 2][m & 3], im[at(m)] = yi[m >> 2][m & 3];
-    }
-    __syncthreads();
-  };
-  for (int r = 0; r < nrounds; r += 2) {  // two by two: the rows need no copies
-    const Round rb = load_round(next);
-    next = entry(r + 2);
-    step(ra);
-    if (r + 1 == nrounds) break;
-    ra = load_round(next);
-    next = entry(r + 3);
-    step(rb);
-  }
+  rr.run(re, im);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT;
@@ -363,6 +390,66 @@ __global__ void __launch_bounds__(1 << (C + H - kW)) __attribute__((amdgpu_waves
 #pragma unroll
   for (int j = 0; j < H; ++j) base = insert_zero(base, rows.b[j]);
   tile_pair_body<C, H, STREAM>(a, base, rows, rounds, nrounds, mats);
+}
+
+// ---- states that fit one tile with room to spare
+// A state of n <= TB qubits whole in the LDS of one workgroup, every round of
+// the circuit in one launch; indices from 2^n on are zeros that no gate moves.
+// Fused blocks, one launch each, are the alternative: a pair round takes about
+// 0.85 us here, a launch about 4 (8 layers at 11 qubits: 23 against 112 us in
+// 14 blocks; at 6 qubits 14 against 48; complex128 at 10 and 6 qubits 47
+// against 81 and 25 against 44).
+template <int TB>
+__global__ void __launch_bounds__(1 << (TB - kW)) __attribute__((amdgpu_waves_per_eu(4)))
+    k_whole_pair(float* __restrict__ a, int n, const int4* __restrict__ rounds, int nrounds,
+                 const float* __restrict__ mats) {
+  constexpr int NT = 1 << (TB - kW), NV = (1 << TB) / 2 / NT;
+  extern __shared__ unsigned char smraw[];
+  float* re = reinterpret_cast<float*>(smraw);
+  float* im = re + kPlane<TB>;
+  float4* p4 = reinterpret_cast<float4*>(a);
+  const int vecs = 1 << (n - 1);
+  PairRounds rr(rounds, nrounds, mats);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int e = threadIdx.x + k * NT, l = plane_pos(2 * e);
+    const float4 b = e < vecs ? p4[e] : make_float4(0.f, 0.f, 0.f, 0.f);
+    re[l] = b.x;
+    im[l] = b.y;
+    re[l + 1] = b.z;
+    im[l + 1] = b.w;
+  }
+  __syncthreads();
+  rr.run(re, im);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int e = threadIdx.x + k * NT, l = plane_pos(2 * e);
+    if (e < vecs) p4[e] = make_float4(re[l], im[l], re[l + 1], im[l + 1]);
+  }
+}
+
+template <int TB>
+__global__ void __launch_bounds__(1 << (TB - kW))
+    k_whole_gates(double* __restrict__ a, int n, const int4* __restrict__ rounds, int nrounds,
+                  const int2* __restrict__ gates, const double* __restrict__ mats) {
+  constexpr int NT = 1 << (TB - kW), NV = (1 << TB) / NT;
+  extern __shared__ unsigned char smraw[];
+  Cx<double>* sm = reinterpret_cast<Cx<double>*>(smraw);
+  double2* p2 = reinterpret_cast<double2*>(a);
+  const int amps = 1 << n;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int e = threadIdx.x + k * NT;
+    const double2 b = e < amps ? p2[e] : make_double2(0.0, 0.0);
+    sm[lds_pos(e)] = {b.x, b.y};
+  }
+  __syncthreads();
+  gate_rounds<double>(sm, rounds, nrounds, gates, mats);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int e = threadIdx.x + k * NT;
+    if (e < amps) p2[e] = make_double2(sm[lds_pos(e)].r, sm[lds_pos(e)].i);
+  }
 }
 
 // Complex64 passes whose rounds are dense 4-qubit blocks on the FP32 matrix
@@ -615,6 +702,39 @@ hipError_t launch_tile_mfma(float* a, int n, int low_bits, const TileRows& rows,
     default: return hipErrorInvalidValue;
   }
 }
+
+namespace {
+template <int TB>
+hipError_t launch_whole_tb(float* a, int n, const void* rounds, int nrounds, const void*,
+                           const float* mats, hipStream_t s) {
+  hipLaunchKernelGGL(k_whole_pair<TB>, dim3(1), dim3(1 << (TB - kW)),
+                     2 * size_t(kPlane<TB>) * sizeof(float), s, a, n,
+                     static_cast<const int4*>(rounds), nrounds, mats);
+  return hipGetLastError();
+}
+template <int TB>
+hipError_t launch_whole_tb(double* a, int n, const void* rounds, int nrounds, const void* gates,
+                           const double* mats, hipStream_t s) {
+  hipLaunchKernelGGL(k_whole_gates<TB>, dim3(1), dim3(1 << (TB - kW)),
+                     size_t((1 << TB) + ((1 << TB) >> 4)) * sizeof(double2), s, a, n,
+                     static_cast<const int4*>(rounds), nrounds, static_cast<const int2*>(gates),
+                     mats);
+  return hipGetLastError();
+}
+}  // namespace
+
+template <typename R>
+hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const void* gates,
+                        const R* mats, hipStream_t s) {
+  if (n < 1 || nrounds < 1) return hipErrorInvalidValue;
+  if (whole_bits(n) == 10) return launch_whole_tb<10>(a, n, rounds, nrounds, gates, mats, s);
+  if (whole_bits(n) == 11) return launch_whole_tb<11>(a, n, rounds, nrounds, gates, mats, s);
+  return hipErrorInvalidValue;
+}
+template hipError_t launch_whole<float>(float*, int, const void*, int, const void*, const float*,
+                                        hipStream_t);
+template hipError_t launch_whole<double>(double*, int, const void*, int, const void*,
+                                         const double*, hipStream_t);
 
 // complex64 (dtype 1): rows of 2^g_tile_low_c64 amplitudes (4: 128 bytes, 5:
 // 256 bytes, 6: 512 bytes); complex128: 16 (256 bytes). Rows of 32 complex64

@@ -378,6 +378,14 @@ hipError_t launch_tile_pass(R* a, int n, int low_bits, const TileRows& rows, con
 // floats (row-major, interleaved), 16-byte aligned.
 hipError_t launch_tile_pair(float* a, int n, int low_bits, const TileRows& rows,
                             const void* rounds, int nrounds, const float* mats, hipStream_t s);
+// A state of n <= 11 (complex64) or 10 (complex128) qubits and every round of
+// a circuit of one- and two-qubit gates in one launch of one workgroup; tables
+// of a one-pass plan on whole_bits(n) bits (complex64: pair rounds, complex128:
+// sparse rounds).
+inline int whole_bits(int n) { return n < 10 ? 10 : n; }
+template <typename R>
+hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const void* gates,
+                        const R* mats, hipStream_t s);
 // Batched complex64 tile passes: one item = one pass of one ket of an arena
 // of n >= kBatchTileLow + kTileRowBits qubits; items sorted by first_tile,
 // the tiles of item i are [first_tile_i, first_tile_{i+1}); its rounds are
