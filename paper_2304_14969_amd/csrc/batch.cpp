@@ -131,17 +131,11 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
     const qs::TilePlan& pl = *plans[i];
     round_base[i] = nround;
     const size_t m0 = mats.size();
-    if (pl.mode == qs::TileMode::kPairs)
-      for (const auto& x : pl.mats) {
-        mats.push_back(float(x.real()));
-        mats.push_back(float(x.imag()));
-      }
+    mats.insert(mats.end(), pl.reals.begin(), pl.reals.end());
     for (const auto& r : pl.rounds) {
       if (pl.mode == qs::TileMode::kPairs) {
         int32_t row[4];
-        qs::pair_round_entry(pl, r, row);
-        row[2] += int32_t(m0);
-        if (row[3] >= 0) row[3] += int32_t(m0);
+        qs::pair_round_entry(r, m0, row);
         rtab.insert(rtab.end(), row, row + 4);
       } else {
         rtab.push_back(r.bits[0] | (r.bits[1] << 8) | (r.bits[2] << 16) | (r.bits[3] << 24));

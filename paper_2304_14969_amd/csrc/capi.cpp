@@ -949,8 +949,9 @@ int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   const int bits = whole ? qs::whole_bits(st->n) : st->n;
   const int low = whole ? bits - qs::kTileRowBits : qs::tile_low_bits(st->dtype);
   std::vector<int> key(st->perm, st->perm + st->n);
-  const qs::TileMode mode = st->dtype == QS_C64 && g_tile_mfma ? qs::matrix_tile_mode(c->gates)
-                                                               : qs::TileMode::kSparse;
+  const qs::TileMode mode = st->dtype == QS_C128 ? qs::TileMode::kPairs
+                            : g_tile_mfma        ? qs::matrix_tile_mode(c->gates)
+                                                 : qs::TileMode::kSparse;
   if (tc.dev && tc.key == key && tc.plan.mode == mode &&
       tc.plan.C == low) {
     *out = &tc;
@@ -992,14 +993,13 @@ int run_tiles(qs_state* st, qs_circuit* c) {
   const double bytes = 2.0 * std::ldexp(1.0, st->n) * ab(st);
   if (runs_whole(st, c)) {  // one step with every round
     ProfScope ps(st, "circuit_lds", bytes);
-    const void* gt = base + tc->gates_off;
+    const void* num = base + tc->gates_off;
     const int nr = int(tc->plan.rounds.size());
     const hipError_t e =
-        st->dtype == QS_C64
-            ? qs::launch_whole(static_cast<float*>(st->amps), st->n, base, nr, gt,
-                               reinterpret_cast<const float*>(base + tc->mats_off), st->stream)
-            : qs::launch_whole(static_cast<double*>(st->amps), st->n, base, nr, gt,
-                               reinterpret_cast<const double*>(base + tc->mats_off), st->stream);
+        st->dtype == QS_C64 ? qs::launch_whole(static_cast<float*>(st->amps), st->n, base, nr,
+                                               static_cast<const float*>(num), st->stream)
+                            : qs::launch_whole(static_cast<double*>(st->amps), st->n, base, nr,
+                                               static_cast<const double*>(num), st->stream);
     return device_error(st, e, "circuit in LDS");
   }
   for (const auto& stp : tc->plan.steps) {
@@ -1013,9 +1013,12 @@ int run_tiles(qs_state* st, qs_circuit* c) {
       const void* rd = base + size_t(stp.r0) * 4 * sizeof(int32_t);
       const void* gt = base + tc->gates_off;
       if (tc->plan.mode == qs::TileMode::kPairs) {
-        ProfScope ps(st, "tile_mfma", bytes);
-        e = qs::launch_tile_pair(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd, stp.nr,
-                                 reinterpret_cast<const float*>(base + tc->mats_off), st->stream);
+        ProfScope ps(st, st->dtype == QS_C64 ? "tile_mfma" : "tile_pass", bytes);
+        e = st->dtype == QS_C64
+                ? qs::launch_tile_pair(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd,
+                                       stp.nr, static_cast<const float*>(gt), st->stream)
+                : qs::launch_tile_pair(static_cast<double*>(st->amps), st->n, tc->plan.C, rows, rd,
+                                       stp.nr, static_cast<const double*>(gt), st->stream);
       } else if (tc->plan.mode == qs::TileMode::kDense) {
         ProfScope ps(st, "tile_mfma", bytes);
         e = qs::launch_tile_mfma(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd,
@@ -1023,15 +1026,9 @@ int run_tiles(qs_state* st, qs_circuit* c) {
                                  st->stream);
       } else {
         ProfScope ps(st, "tile_pass", bytes);
-        e = st->dtype == QS_C64
-                ? qs::launch_tile_pass(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd,
-                                       stp.nr, gt,
-                                       reinterpret_cast<const float*>(base + tc->mats_off),
-                                       st->stream)
-                : qs::launch_tile_pass(static_cast<double*>(st->amps), st->n, tc->plan.C, rows,
-                                       rd, stp.nr, gt,
-                                       reinterpret_cast<const double*>(base + tc->mats_off),
-                                       st->stream);
+        e = qs::launch_tile_pass(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd, stp.nr,
+                                 gt, reinterpret_cast<const float*>(base + tc->mats_off),
+                                 st->stream);
       }
     }
     if (int rc = device_error(st, e, "tile pass")) return rc;

@@ -254,11 +254,11 @@ std::vector<int> take_group(DagCursor& dag, int budget, std::vector<int>* chosen
 namespace {
 
 // The gate list with its one-qubit gates multiplied into wider neighbours
-// (float64): into the last gate on their qubit if it has two or more qubits,
-// else, collected, into the next one; a gate on the same qubits as the gate
-// before it on each of them is multiplied into that one. What stays are gates
-// of two or more qubits and one product per qubit that only has one-qubit
-// gates. The order keeps every qubit's gates in order.
+// (float64): collected into the next gate of two or more qubits on their
+// qubit, or, where none follows, into the last one; a gate on the same qubits
+// as the gate before it on each of them is multiplied into that one. What
+// stays are gates of two or more qubits and one product per qubit that only
+// has one-qubit gates. The order keeps every qubit's gates in order.
 std::vector<Gate> merge_gates(const std::vector<Gate>& gates, int n) {
   std::vector<Gate> out;
   std::vector<int> last(n, -1);  // per qubit: its last gate in out
@@ -266,48 +266,47 @@ std::vector<Gate> merge_gates(const std::vector<Gate>& gates, int n) {
   auto at = [](const Gate& g, int q) { return int(std::find(g.q, g.q + g.k, q) - g.q); };
   for (const Gate& g : gates) {
     if (g.k == 1) {
-      const int q = g.q[0], zero = 0;
-      if (last[q] >= 0) {
-        const int b = at(out[last[q]], q);
-        left_apply(out[last[q]].m, out[last[q]].k, g.m, 1, &b);
-      } else {
-        if (pend[q].empty()) pend[q] = eye(1);
-        left_apply(pend[q], 1, g.m, 1, &zero);
-      }
+      const int zero = 0;
+      auto& u = pend[g.q[0]];
+      if (u.empty()) u = eye(1);
+      left_apply(u, 1, g.m, 1, &zero);
       continue;
     }
     int prev = last[g.q[0]];
     for (int j = 1; j < g.k; ++j)
       if (last[g.q[j]] != prev) prev = -1;
-    if (prev >= 0 && out[prev].k == g.k) {
-      int lp[QS_MAX_FUSED];
-      for (int j = 0; j < g.k; ++j) lp[j] = at(out[prev], g.q[j]);
-      left_apply(out[prev].m, g.k, g.m, g.k, lp);
-      continue;
-    }
-    Gate w = g;
-    bool any = false;
-    for (int j = 0; j < g.k; ++j) any |= !pend[g.q[j]].empty();
-    if (any) {
+    const bool onto = prev >= 0 && out[prev].k == g.k;
+    Gate w;
+    if (!onto) {
+      w = g;
       w.m = eye(g.k);
-      for (int j = 0; j < g.k; ++j)
-        if (!pend[g.q[j]].empty()) left_apply(w.m, g.k, pend[g.q[j]], 1, &j);
-      int lp[QS_MAX_FUSED];
-      for (int j = 0; j < g.k; ++j) lp[j] = j;
-      left_apply(w.m, g.k, g.m, g.k, lp);
-      for (int j = 0; j < g.k; ++j) pend[g.q[j]].clear();
     }
+    Gate& t = onto ? out[prev] : w;
+    int lp[QS_MAX_FUSED];
+    for (int j = 0; j < g.k; ++j) lp[j] = at(t, g.q[j]);
+    for (int j = 0; j < g.k; ++j) {
+      auto& u = pend[g.q[j]];
+      if (!u.empty()) left_apply(t.m, t.k, u, 1, &lp[j]);
+      u.clear();
+    }
+    left_apply(t.m, t.k, g.m, g.k, lp);
+    if (onto) continue;
     for (int j = 0; j < g.k; ++j) last[g.q[j]] = int(out.size());
     out.push_back(std::move(w));
   }
-  for (int q = 0; q < n; ++q)
-    if (!pend[q].empty()) {
-      Gate w;
-      w.k = 1;
-      w.q[0] = q;
-      w.m = std::move(pend[q]);
-      out.push_back(std::move(w));
+  for (int q = 0; q < n; ++q) {
+    if (pend[q].empty()) continue;
+    if (last[q] >= 0) {
+      const int b = at(out[last[q]], q);
+      left_apply(out[last[q]].m, out[last[q]].k, pend[q], 1, &b);
+      continue;
     }
+    Gate w;
+    w.k = 1;
+    w.q[0] = q;
+    w.m = std::move(pend[q]);
+    out.push_back(std::move(w));
+  }
   return out;
 }
 
@@ -453,21 +452,18 @@ void pair_rounds(TilePlan* plan, const std::vector<Gate>& gates, const std::vect
     if (!need[i]) ready.push_back(int(i));
   auto emit = [&](const Op* o1, const Op* o2) {
     TileRound r;
-    r.g0 = int(plan->gates.size());
+    r.mat = plan->reals.size();
+    r.ng = o2 ? 2 : 1;
     int nb = 0;
     for (const Op* o : {o1, o2}) {
       if (!o) continue;
-      TileGate tg;
-      tg.kind = 2;
-      tg.j1 = nb;
-      tg.j2 = nb + 1;
-      tg.mat = plan->mats.size();
-      plan->mats.insert(plan->mats.end(), o->m.begin(), o->m.end());
-      plan->gates.push_back(tg);
       r.bits[nb++] = o->a;
       r.bits[nb++] = o->b;
+      for (const cd& v : o->m) {
+        plan->reals.push_back(v.real());
+        plan->reals.push_back(v.imag());
+      }
     }
-    r.ng = nb / 2;
     for (int b = 0; nb < 4; ++b)
       if (std::find(r.bits, r.bits + nb, b) == r.bits + nb) r.bits[nb++] = b;
     plan->rounds.push_back(r);
@@ -649,25 +645,26 @@ TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W
   return plan;
 }
 
-void pair_round_entry(const TilePlan& pl, const TileRound& r, int32_t row[4]) {
+void pair_round_entry(const TileRound& r, size_t base, int32_t row[4]) {
   int asc[4];
   std::copy(r.bits, r.bits + 4, asc);
   std::sort(asc, asc + 4);
   row[0] = r.bits[0] | (r.bits[1] << 8) | (r.bits[2] << 16) | (r.bits[3] << 24);
   row[1] = asc[0] | (asc[1] << 8) | (asc[2] << 16) | (asc[3] << 24);
-  row[2] = int32_t(2 * pl.gates[r.g0].mat);
-  row[3] = r.ng > 1 ? int32_t(2 * pl.gates[r.g0 + 1].mat) : -1;
+  row[2] = int32_t(base + r.mat);
+  row[3] = r.ng > 1 ? 1 : 0;
 }
 
 void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, size_t* gates_off,
                  size_t* mats_off, size_t* emb_off) {
   const bool dense = pl.mode == TileMode::kDense;
+  const bool pairs = pl.mode == TileMode::kPairs;
   std::vector<int32_t> tab;
   for (size_t ri = 0; ri < pl.rounds.size(); ++ri) {
     const auto& r = pl.rounds[ri];
-    if (pl.mode == TileMode::kPairs) {
+    if (pairs) {
       int32_t row[4];
-      pair_round_entry(pl, r, row);
+      pair_round_entry(r, 0, row);
       tab.insert(tab.end(), row, row + 4);
       continue;
     }
@@ -687,7 +684,8 @@ void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, 
   // dense rounds: each round's matrix-core operands in lane order, then the
   // matrices of the block steps; sparse rounds: every matrix as is
   const size_t emb = dense ? pl.rounds.size() * kRoundOperands * sizeof(float) : 0;
-  const size_t total = emb_at + emb + 2 * pl.mats.size() * esz;
+  const size_t real_at = emb_at + emb + 2 * pl.mats.size() * esz;
+  const size_t total = real_at + pl.reals.size() * esz;
   out->assign(total, 0);
   unsigned char* host = out->data();
   std::memcpy(host, tab.data(), tab.size() * sizeof(int32_t));
@@ -708,7 +706,15 @@ void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, 
       std::memcpy(host + emb_at + emb + 2 * i * esz, v, sizeof v);
     }
   }
-  *gates_off = gates_at;
+  for (size_t i = 0; i < pl.reals.size(); ++i) {
+    if (c64) {
+      const float v = float(pl.reals[i]);
+      std::memcpy(host + real_at + i * esz, &v, sizeof v);
+    } else {
+      std::memcpy(host + real_at + i * esz, &pl.reals[i], sizeof(double));
+    }
+  }
+  *gates_off = pairs ? real_at : gates_at;
   *emb_off = emb_at;
   *mats_off = emb_at + emb;
 }
@@ -852,7 +858,7 @@ int qs_circuit_tile_info(const qs_circuit* c, int dtype, int* passes, int* block
   if (c->n < C + 7) return cfail(QS_E_UNSUPPORTED, "%d qubits: fewer than one tile (%d)", c->n, C + 7);
   const qs::TilePlan pl =
       qs::plan_tiles(c->gates, c->n, C, 7, 4,
-                     dtype == QS_C64 ? qs::matrix_tile_mode(c->gates) : qs::TileMode::kSparse);
+                     dtype == QS_C64 ? qs::matrix_tile_mode(c->gates) : qs::TileMode::kPairs);
   if (passes) *passes = pl.passes();
   if (blocks) *blocks = int(pl.steps.size()) - pl.passes();
   if (rounds) *rounds = int(pl.rounds.size());

@@ -50,8 +50,8 @@ struct TileGate {
 struct TileRound {
   int bits[4] = {0, 0, 0, 0};  // tile bits of the round, ascending (pairs: the
                                // first gate's two, then the second's)
-  int g0 = 0, ng = 0;          // its gates in TilePlan::gates (not dense)
-  size_t mat = 0;              // dense rounds: offset of the 16x16 product in mats
+  int g0 = 0, ng = 0;          // its gates in TilePlan::gates (sparse); pairs: 1 or 2 gates
+  size_t mat = 0;              // dense: offset of the 16x16 product in mats; pairs: in reals
 };
 struct TileStep {
   bool block = false;  // a dense block (a gate on more than two qubits), not a pass
@@ -64,7 +64,8 @@ struct TileStep {
 // What the rounds of a plan hold: gates of one or two qubits on any of the
 // round's bits (kSparse); one or two gates on disjoint pairs, the first on the
 // round's bits 0 and 1, the second on 2 and 3 (kPairs); one dense product of
-// gates of at most W qubits (kDense).
+// gates of at most W qubits (kDense). A pair round's numbers (TilePlan::reals)
+// are its gates' 4 x 4 complex matrices (32 reals each, row-major).
 enum class TileMode { kSparse, kPairs, kDense };
 struct TilePlan {
   int C = 0, H = 0, W = 0;
@@ -73,6 +74,7 @@ struct TilePlan {
   std::vector<TileRound> rounds;
   std::vector<TileGate> gates;
   std::vector<cd> mats;
+  std::vector<double> reals;  // pair rounds
   int passes() const {
     int p = 0;
     for (const auto& s : steps) p += s.block ? 0 : 1;
@@ -90,23 +92,25 @@ struct TilePlan {
 // two qubits, or more than W for dense rounds) run as blocks between passes.
 TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, TileMode mode);
 
-// Rounds of complex64 passes on the matrix cores: pairs, or dense products
-// when the circuit has gates of more than two qubits (so that they still join
-// the passes).
+// Rounds of complex64 passes: pairs, or dense products when the circuit has
+// gates of more than two qubits (so that they still join the passes).
+// (Complex128 passes always have pairs.)
 TileMode matrix_tile_mode(const std::vector<Gate>& gates);
 
 // The device tables of a plan, as one byte image: per round an int4 {bits
 // packed by byte, first gate (sparse) or embedding offset in floats (dense),
 // gate count, 0}, or for pairs {bits packed by byte, the same bits ascending,
-// offsets in reals of the two gates' matrices, -1 for none}; per gate an int2 {kind | j1 << 4 | j2 << 8, offset
+// offset of its numbers, 1 if it has a second gate}; per gate
+// (sparse) an int2 {kind | j1 << 4 | j2 << 8, offset
 // of its matrix in reals}; at emb_off (dense) the rounds' 32 x 32 embeddings
 // in lane order (float); at mats_off the plan's matrices (float or double
-// pairs). Offsets are bytes from the start.
+// pairs); for pairs, at gates_off their numbers. Offsets are bytes from the
+// start.
 void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, size_t* gates_off,
                  size_t* mats_off, size_t* emb_off);
 
-// A pair round's table entry (int4 as above).
-void pair_round_entry(const TilePlan& pl, const TileRound& r, int32_t row[4]);
+// A pair round's table entry (int4 as above), its numbers moved by `base`.
+void pair_round_entry(const TileRound& r, size_t base, int32_t row[4]);
 
 // The operands a dense matrix-core round reads, for the three real products of
 // Re U X_r, Im U X_i and (Re U + Im U)(X_r + X_i) of a 16 x 16 complex round

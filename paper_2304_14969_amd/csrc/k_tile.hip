@@ -30,7 +30,7 @@ __device__ __forceinline__ uint64_t insert_zero(uint64_t x, int pos) {
   const uint64_t lo = x & ((uint64_t(1) << pos) - 1);
   return lo | ((x ^ lo) << 1);
 }
-__device__ __forceinline__ int lds_pos(int x) { return x + (x >> 4); }
+constexpr __device__ __forceinline__ int lds_pos(int x) { return x + (x >> 4); }
 
 template <typename R>
 __device__ __forceinline__ Cx<R> cmac(Cx<R> acc, Cx<R> a, Cx<R> b) {
@@ -218,34 +218,31 @@ __global__ void __launch_bounds__(1 << (C + H - kW))
 // 28 (11.7).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Row lane % 4 of a gate's matrix: the A operands of its four columns.
-struct PairRow {
-  float re[4], im[4];
-};
-
-// y = U x on four quadruples; x(h, c) is input c of quadruple h, output row i
-// of it is (yr[h][i], yi[h][i]).
+// y = U x on four quadruples for a complex U, of which this lane holds row
+// lane % 4 (u: its entries, interleaved); x(h, c) is input c of quadruple h,
+// output row i of it is (yr[h][i], yi[h][i]).
 template <typename In>
-__device__ __forceinline__ void pair_gate(const PairRow& u, In x, f32x4 (&yr)[4], f32x4 (&yi)[4]) {
+__device__ __forceinline__ void pair_gate(const float4 (&u)[2], In x, f32x4 (&yr)[4],
+                                          f32x4 (&yi)[4]) {
+  const float ur[4] = {u[0].x, u[0].z, u[1].x, u[1].z}, ui[4] = {u[0].y, u[0].w, u[1].y, u[1].w};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const float nim = -u.im[c];
+    const float nim = -ui[c];
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
       const float2 v = x(h, c);
       const f32x4 r = c ? yr[h] : f32x4{}, i = c ? yi[h] : f32x4{};
-      yr[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(u.re[c], v.x, r, 0, 0, 0);
-      yi[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(u.re[c], v.y, i, 0, 0, 0);
+      yr[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(ur[c], v.x, r, 0, 0, 0);
+      yi[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(ur[c], v.y, i, 0, 0, 0);
     }
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
       const float2 v = x(h, c);
       yr[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(nim, v.y, yr[h], 0, 0, 0);
-      yi[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(u.im[c], v.x, yi[h], 0, 0, 0);
+      yi[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(ui[c], v.x, yi[h], 0, 0, 0);
     }
   }
 }
-
 __device__ __forceinline__ int insert_zero32(int x, int pos) {
   const int lo = x & ((1 << pos) - 1);
   return lo | ((x ^ lo) << 1);
@@ -253,59 +250,66 @@ __device__ __forceinline__ int insert_zero32(int x, int pos) {
 
 // Dword of tile index x in a plane of the LDS tile (one dword of padding every
 // 32), and the length of a plane (a multiple of 64).
-__device__ __forceinline__ int plane_pos(int x) { return x + (x >> 5); }
+constexpr __device__ __forceinline__ int plane_pos(int x) { return x + (x >> 5); }
 template <int TB> constexpr int kPlane = (1 << TB) + ((1 << TB) >> 5) + 63 & ~63;
 
-// The rounds of a tile staged in LDS (thread x: group x of each round). A
-// round's entry is loaded two rounds ahead, its matrix rows one ahead; the
-// first ones when the object is made, before the tile's own loads.
+// LDS offsets of a group's 16 amplitudes in a round of a tile whose entry of
+// index x is POS(x), additive over disjoint bits: thread x's group of the round
+// with these bits (in the order of its gates, and ascending).
+template <int (*POS)(int)>
+struct GroupPos {
+  int px, d[4];
+  __device__ __forceinline__ GroupPos(int bits, int asc) {
+    int x0 = threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x0 = insert_zero32(x0, (asc >> (8 * j)) & 255);
+    px = POS(x0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = POS(1 << ((bits >> (8 * j)) & 255));
+  }
+  __device__ __forceinline__ int operator()(int m) const {
+    return px + ((m & 1) ? d[0] : 0) + ((m & 2) ? d[1] : 0) + ((m & 4) ? d[2] : 0) +
+           ((m & 8) ? d[3] : 0);
+  }
+};
+
+// The complex64 rounds of a tile staged in LDS (thread x: group x of each
+// round). A round's entry is loaded two rounds ahead, its matrix rows one
+// ahead; the first ones when the object is made, before the tile's own loads.
 struct PairRounds {
   struct Round {
-    int bits, asc, second;
-    PairRow m1, m2;
+    int bits, asc, flags;
+    float4 m1[2], m2[2];  // this lane's row of the first and second gate
   };
   const int4* __restrict__ rounds;
   int nrounds;
-  const float* __restrict__ lane_row;  // this lane's row of the matrix at offset 0
+  const float* __restrict__ num;
   int4 next;
   Round ra;
 
-  __device__ __forceinline__ PairRow load_row(int off) const {
-    const float4 x = *reinterpret_cast<const float4*>(lane_row + off);
-    const float4 y = *reinterpret_cast<const float4*>(lane_row + off + 4);
-    return PairRow{{x.x, x.z, y.x, y.z}, {x.y, x.w, y.y, y.w}};
-  }
   __device__ __forceinline__ int4 entry(int r) const {
     return rounds[r < nrounds ? r : nrounds - 1];
   }
-  // a missing second gate reads the first one's row again
   __device__ __forceinline__ Round load_round(int4 e) const {
-    return Round{e.x, e.y, e.w, load_row(e.z), load_row(e.w < 0 ? e.z : e.w)};
+    const float* row = num + 8 * (threadIdx.x & 3);
+    const int second = e.z + ((e.w & 1) ? 32 : 0);  // none: the first one's row again
+    auto q = [&](int off) { return *reinterpret_cast<const float4*>(row + off); };
+    return Round{e.x, e.y, e.w, {q(e.z), q(e.z + 4)}, {q(second), q(second + 4)}};
   }
   __device__ __forceinline__ PairRounds(const int4* __restrict__ r, int n,
-                                        const float* __restrict__ mats)
-      : rounds(r), nrounds(n), lane_row(mats + 8 * (threadIdx.x & 3)) {
+                                        const float* __restrict__ numbers)
+      : rounds(r), nrounds(n), num(numbers) {
     next = entry(1);
     ra = load_round(entry(0));
   }
   __device__ __forceinline__ void step(const Round& rd, float* re, float* im) const {
-    int x0 = threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) x0 = insert_zero32(x0, (rd.asc >> (8 * j)) & 255);
-    const int px = plane_pos(x0);
-    int d[4];  // LDS offset of each round bit; plane_pos adds over disjoint bits
-#pragma unroll
-    for (int j = 0; j < 4; ++j) d[j] = plane_pos(1 << ((rd.bits >> (8 * j)) & 255));
-    auto at = [&](int m) {
-      return px + ((m & 1) ? d[0] : 0) + ((m & 2) ? d[1] : 0) + ((m & 4) ? d[2] : 0) +
-             ((m & 8) ? d[3] : 0);
-    };
+    const GroupPos<plane_pos> at(rd.bits, rd.asc);
     float2 v[kV];
 #pragma unroll
     for (int m = 0; m < kV; ++m) v[m] = make_float2(re[at(m)], im[at(m)]);
     f32x4 yr[4], yi[4];
     pair_gate(rd.m1, [&](int h, int c) { return v[4 * h + c]; }, yr, yi);
-    if (rd.second >= 0) {
+    if (rd.flags & 1) {
       f32x4 zr[4], zi[4];
       pair_gate(rd.m2, [&](int l, int c) { return make_float2(yr[c][l], yi[c][l]); }, zr, zi);
 #pragma unroll
@@ -328,6 +332,56 @@ struct PairRounds {
     }
   }
 };
+
+// LDS entry of index x of a complex128 tile: 8 lanes of 16-byte entries fill
+// the banks, so the padding follows every 8 entries (every 16: 3% slower).
+constexpr __host__ __device__ __forceinline__ int wide_pos(int x) { return x + (x >> 3); }
+
+// Complex128 rounds on vector FMA (the FP64 matrix rate is the vector rate),
+// the numbers read through the scalar cache. FMAs bound them; a round is two
+// gates in fixed places, 4 KB of code, where k_tile_pass selects among twelve
+// forms by a switch (28 KB, fetched anew by every launch for the two or three
+// rounds a small state has). 8-layer circuits with its rounds and with these:
+// 44.9 -> 37.2 us at 11 qubits, 204 -> 187 at 20, 1.71 -> 1.62 ms at 24. (Taking
+// each gate as phases times a real matrix, 5/8 of the FMAs, gained 5% more but
+// with 1.4 times the error against 64 bits.)
+__device__ __forceinline__ void pair_gate_f64(Cx<double> (&v)[kV], int s, int t,
+                                              const double* __restrict__ u) {
+  // quadruple h: entries t h + s c
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    Cx<double> in[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) in[c] = v[t * h + s * c];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      Cx<double> y{0, 0};
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        y = cmac(y, Cx<double>{u[2 * (4 * r + c)], u[2 * (4 * r + c) + 1]}, in[c]);
+      v[t * h + s * r] = y;
+    }
+  }
+}
+
+__device__ __forceinline__ void pair_rounds_f64(Cx<double>* sm, const int4* __restrict__ rounds,
+                                                int nrounds, const double* __restrict__ num) {
+  int4 e = rounds[0];
+  for (int r = 0; r < nrounds; ++r) {
+    const int4 next = rounds[r + 1 < nrounds ? r + 1 : r];
+    const double* __restrict__ u = num + e.z;
+    const GroupPos<wide_pos> at(e.x, e.y);
+    Cx<double> v[kV];
+#pragma unroll
+    for (int m = 0; m < kV; ++m) v[m] = sm[at(m)];
+    pair_gate_f64(v, 1, 4, u);
+    if (e.w & 1) pair_gate_f64(v, 4, 1, u + 32);
+#pragma unroll
+    for (int m = 0; m < kV; ++m) sm[at(m)] = v[m];
+    e = next;
+    __syncthreads();
+  }
+}
 
 template <int C, int H, bool STREAM>
 __device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t base,
@@ -382,14 +436,58 @@ __device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t b
   }
 }
 
+// The same pass in complex128.
 template <int C, int H, bool STREAM>
-__global__ void __launch_bounds__(1 << (C + H - kW)) __attribute__((amdgpu_waves_per_eu(4)))
-    k_tile_pair(float* __restrict__ a, TileRows rows, const int4* __restrict__ rounds,
-                int nrounds, const float* __restrict__ mats) {
+__device__ __forceinline__ void tile_pair_body(double* __restrict__ a, uint64_t base,
+                                               const TileRows& rows,
+                                               const int4* __restrict__ rounds, int nrounds,
+                                               const double* __restrict__ num) {
+  constexpr int TB = C + H, NT = 1 << (TB - kW), NV = (1 << TB) / NT;
+  constexpr int RT = NT >> C, RTB = __builtin_ctz(RT);  // tile rows between a thread's entries
+  extern __shared__ unsigned char smraw[];
+  Cx<double>* sm = reinterpret_cast<Cx<double>*>(smraw);
+  const int r0 = int(threadIdx.x) >> C;
+  uint64_t off_t = base | (threadIdx.x & ((1 << C) - 1));
+#pragma unroll
+  for (int j = 0; j < RTB; ++j) off_t |= uint64_t((r0 >> j) & 1) << rows.b[j];
+  auto glob_k = [&](int k) {
+    uint64_t g = off_t;
+#pragma unroll
+    for (int j = RTB; j < H; ++j)
+      if (((k * RT) >> j) & 1) g |= uint64_t(1) << rows.b[j];
+    return g;
+  };
+  double2* p2 = reinterpret_cast<double2*>(a);
+  double2 buf[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) buf[k] = ld16<STREAM>(p2 + glob_k(k));
+#pragma unroll
+  for (int k = 0; k < NV; ++k) sm[wide_pos(threadIdx.x + k * NT)] = {buf[k].x, buf[k].y};
+  __syncthreads();
+  pair_rounds_f64(sm, rounds, nrounds, num);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const Cx<double> x = sm[wide_pos(threadIdx.x + k * NT)];
+    st16<STREAM>(p2 + glob_k(k), make_double2(x.r, x.i));
+  }
+}
+
+template <typename R> constexpr int kPairWaves = sizeof(R) == 4 ? 4 : 2;  // per SIMD, by registers
+// LDS bytes of a tile of pair rounds
+template <typename R, int TB>
+constexpr size_t pair_lds() {
+  return sizeof(R) == 4 ? 2 * size_t(kPlane<TB>) * 4 : size_t(wide_pos(1 << TB)) * 16;
+}
+
+template <typename R, int C, int H, bool STREAM>
+__global__ void __launch_bounds__(1 << (C + H - kW))
+__attribute__((amdgpu_waves_per_eu(kPairWaves<R>)))
+    k_tile_pair(R* __restrict__ a, TileRows rows, const int4* __restrict__ rounds, int nrounds,
+                const R* __restrict__ num) {
   uint64_t base = uint64_t(blockIdx.x) << C;
 #pragma unroll
   for (int j = 0; j < H; ++j) base = insert_zero(base, rows.b[j]);
-  tile_pair_body<C, H, STREAM>(a, base, rows, rounds, nrounds, mats);
+  tile_pair_body<C, H, STREAM>(a, base, rows, rounds, nrounds, num);
 }
 
 // ---- states that fit one tile with room to spare
@@ -430,8 +528,8 @@ __global__ void __launch_bounds__(1 << (TB - kW)) __attribute__((amdgpu_waves_pe
 
 template <int TB>
 __global__ void __launch_bounds__(1 << (TB - kW))
-    k_whole_gates(double* __restrict__ a, int n, const int4* __restrict__ rounds, int nrounds,
-                  const int2* __restrict__ gates, const double* __restrict__ mats) {
+    k_whole_pair(double* __restrict__ a, int n, const int4* __restrict__ rounds, int nrounds,
+                 const double* __restrict__ num) {
   constexpr int NT = 1 << (TB - kW), NV = (1 << TB) / NT;
   extern __shared__ unsigned char smraw[];
   Cx<double>* sm = reinterpret_cast<Cx<double>*>(smraw);
@@ -441,14 +539,14 @@ __global__ void __launch_bounds__(1 << (TB - kW))
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT;
     const double2 b = e < amps ? p2[e] : make_double2(0.0, 0.0);
-    sm[lds_pos(e)] = {b.x, b.y};
+    sm[wide_pos(e)] = {b.x, b.y};
   }
   __syncthreads();
-  gate_rounds<double>(sm, rounds, nrounds, gates, mats);
+  pair_rounds_f64(sm, rounds, nrounds, num);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT;
-    if (e < amps) p2[e] = make_double2(sm[lds_pos(e)].r, sm[lds_pos(e)].i);
+    if (e < amps) p2[e] = make_double2(sm[wide_pos(e)].r, sm[wide_pos(e)].i);
   }
 }
 
@@ -665,33 +763,39 @@ hipError_t launch_mfma_c(float* a, int n, const TileRows& rows, const void* roun
 
 
 namespace {
-template <int C>
-hipError_t launch_pair_c(float* a, int n, const TileRows& rows, const void* rounds, int nrounds,
-                         const float* mats, hipStream_t s) {
+template <typename R, int C>
+hipError_t launch_pair_c(R* a, int n, const TileRows& rows, const void* rounds, int nrounds,
+                         const R* num, hipStream_t s) {
   constexpr int H = kTileRowBits, TB = C + H;
   if (n < TB || nrounds < 1) return hipErrorInvalidValue;
   for (int j = 0; j < H; ++j)
     if (rows.b[j] < C || rows.b[j] >= n || (j > 0 && rows.b[j] <= rows.b[j - 1]))
       return hipErrorInvalidValue;
-  const size_t bytes = 2 * size_t(kPlane<TB>) * sizeof(float);
-  auto kern = stream_sweep(n, 8, C) ? k_tile_pair<C, H, true> : k_tile_pair<C, H, false>;
+  const size_t bytes = pair_lds<R, TB>();
+  auto kern =
+      stream_sweep(n, 2 * sizeof(R), C) ? k_tile_pair<R, C, H, true> : k_tile_pair<R, C, H, false>;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
   hipLaunchKernelGGL(kern, dim3(unsigned(uint64_t(1) << (n - TB))), dim3(1 << (TB - kW)), bytes, s,
-                     a, rows, static_cast<const int4*>(rounds), nrounds, mats);
+                     a, rows, static_cast<const int4*>(rounds), nrounds, num);
   return hipGetLastError();
 }
 }  // namespace
 
-hipError_t launch_tile_pair(float* a, int n, int low_bits, const TileRows& rows,
-                            const void* rounds, int nrounds, const float* mats, hipStream_t s) {
-  switch (low_bits) {
-    case 4: return launch_pair_c<4>(a, n, rows, rounds, nrounds, mats, s);
-    case 5: return launch_pair_c<5>(a, n, rows, rounds, nrounds, mats, s);
-    case 6: return launch_pair_c<6>(a, n, rows, rounds, nrounds, mats, s);
-    default: return hipErrorInvalidValue;
+template <typename R>
+hipError_t launch_tile_pair(R* a, int n, int low_bits, const TileRows& rows, const void* rounds,
+                            int nrounds, const R* num, hipStream_t s) {
+  if (low_bits == 4) return launch_pair_c<R, 4>(a, n, rows, rounds, nrounds, num, s);
+  if constexpr (sizeof(R) == 4) {
+    if (low_bits == 5) return launch_pair_c<R, 5>(a, n, rows, rounds, nrounds, num, s);
+    if (low_bits == 6) return launch_pair_c<R, 6>(a, n, rows, rounds, nrounds, num, s);
   }
+  return hipErrorInvalidValue;
 }
+template hipError_t launch_tile_pair<float>(float*, int, int, const TileRows&, const void*, int,
+                                            const float*, hipStream_t);
+template hipError_t launch_tile_pair<double>(double*, int, int, const TileRows&, const void*, int,
+                                             const double*, hipStream_t);
 
 hipError_t launch_tile_mfma(float* a, int n, int low_bits, const TileRows& rows,
                             const void* rounds, int nrounds, const float* amats, hipStream_t s) {
@@ -704,37 +808,28 @@ hipError_t launch_tile_mfma(float* a, int n, int low_bits, const TileRows& rows,
 }
 
 namespace {
-template <int TB>
-hipError_t launch_whole_tb(float* a, int n, const void* rounds, int nrounds, const void*,
-                           const float* mats, hipStream_t s) {
-  hipLaunchKernelGGL(k_whole_pair<TB>, dim3(1), dim3(1 << (TB - kW)),
-                     2 * size_t(kPlane<TB>) * sizeof(float), s, a, n,
-                     static_cast<const int4*>(rounds), nrounds, mats);
-  return hipGetLastError();
-}
-template <int TB>
-hipError_t launch_whole_tb(double* a, int n, const void* rounds, int nrounds, const void* gates,
-                           const double* mats, hipStream_t s) {
-  hipLaunchKernelGGL(k_whole_gates<TB>, dim3(1), dim3(1 << (TB - kW)),
-                     size_t((1 << TB) + ((1 << TB) >> 4)) * sizeof(double2), s, a, n,
-                     static_cast<const int4*>(rounds), nrounds, static_cast<const int2*>(gates),
-                     mats);
+template <typename R, int TB>
+hipError_t launch_whole_tb(R* a, int n, const void* rounds, int nrounds, const R* num,
+                           hipStream_t s) {
+  void (*kern)(R*, int, const int4*, int, const R*) = k_whole_pair<TB>;
+  hipLaunchKernelGGL(kern, dim3(1), dim3(1 << (TB - kW)), (pair_lds<R, TB>()), s, a, n,
+                     static_cast<const int4*>(rounds), nrounds, num);
   return hipGetLastError();
 }
 }  // namespace
 
 template <typename R>
-hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const void* gates,
-                        const R* mats, hipStream_t s) {
+hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const R* num,
+                        hipStream_t s) {
   if (n < 1 || nrounds < 1) return hipErrorInvalidValue;
-  if (whole_bits(n) == 10) return launch_whole_tb<10>(a, n, rounds, nrounds, gates, mats, s);
-  if (whole_bits(n) == 11) return launch_whole_tb<11>(a, n, rounds, nrounds, gates, mats, s);
+  if (whole_bits(n) == 10) return launch_whole_tb<R, 10>(a, n, rounds, nrounds, num, s);
+  if constexpr (sizeof(R) == 4)
+    if (whole_bits(n) == 11) return launch_whole_tb<R, 11>(a, n, rounds, nrounds, num, s);
   return hipErrorInvalidValue;
 }
-template hipError_t launch_whole<float>(float*, int, const void*, int, const void*, const float*,
-                                        hipStream_t);
-template hipError_t launch_whole<double>(double*, int, const void*, int, const void*,
-                                         const double*, hipStream_t);
+template hipError_t launch_whole<float>(float*, int, const void*, int, const float*, hipStream_t);
+template hipError_t launch_whole<double>(double*, int, const void*, int, const double*,
+                                         hipStream_t);
 
 // complex64 (dtype 1): rows of 2^g_tile_low_c64 amplitudes (4: 128 bytes, 5:
 // 256 bytes, 6: 512 bytes); complex128: 16 (256 bytes). Rows of 32 complex64
@@ -795,7 +890,7 @@ hipError_t launch_tile_pair_batch(float* arena, const TileItem* items, int nitem
                                   const void* rounds, const float* mats, hipStream_t s) {
   constexpr int C = kBatchTileLow, H = kTileRowBits, TB = C + H;
   if (nitems < 1 || tiles < 1 || tiles > 0x7fffffffu) return hipErrorInvalidValue;
-  const size_t bytes = 2 * size_t(kPlane<TB>) * sizeof(float);
+  const size_t bytes = pair_lds<float, TB>();
   auto kern = k_tile_pair_batch<C, H>;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));

@@ -372,20 +372,19 @@ extern int g_tile_low_c64;  // low tile bits of complex64 passes: 5 or 6
 template <typename R>
 hipError_t launch_tile_pass(R* a, int n, int low_bits, const TileRows& rows, const void* rounds,
                             int nrounds, const void* gates, const R* mats, hipStream_t s);
-// Complex64 pass of pair rounds on the FP32 matrix cores: `rounds` int4 {bits
-// packed 8 per byte, the same ascending, offsets of the two gates' 4 x 4
-// matrices in mats (the second -1 if there is none)}; a gate's matrix is 32
-// floats (row-major, interleaved), 16-byte aligned.
-hipError_t launch_tile_pair(float* a, int n, int low_bits, const TileRows& rows,
-                            const void* rounds, int nrounds, const float* mats, hipStream_t s);
+// Pass of pair rounds: `rounds` int4 {bits packed 8 per byte, the same
+// ascending, offset of the round's numbers in num, 1 if it has a second gate};
+// num as in TilePlan (16-byte aligned).
+template <typename R>
+hipError_t launch_tile_pair(R* a, int n, int low_bits, const TileRows& rows, const void* rounds,
+                            int nrounds, const R* num, hipStream_t s);
 // A state of n <= 11 (complex64) or 10 (complex128) qubits and every round of
 // a circuit of one- and two-qubit gates in one launch of one workgroup; tables
-// of a one-pass plan on whole_bits(n) bits (complex64: pair rounds, complex128:
-// sparse rounds).
+// of a one-pass plan of pair rounds on whole_bits(n) bits.
 inline int whole_bits(int n) { return n < 10 ? 10 : n; }
 template <typename R>
-hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const void* gates,
-                        const R* mats, hipStream_t s);
+hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const R* num,
+                        hipStream_t s);
 // Batched complex64 tile passes: one item = one pass of one ket of an arena
 // of n >= kBatchTileLow + kTileRowBits qubits; items sorted by first_tile,
 // the tiles of item i are [first_tile_i, first_tile_{i+1}); its rounds are
@@ -398,7 +397,7 @@ struct TileItem {
   int r0, nr;
 };
 hipError_t launch_tile_pair_batch(float* arena, const TileItem* items, int nitems, uint64_t tiles,
-                                  const void* rounds, const float* mats, hipStream_t s);
+                                  const void* rounds, const float* num, hipStream_t s);
 hipError_t launch_tile_mfma_batch(float* arena, const TileItem* items, int nitems, uint64_t tiles,
                                   const void* rounds, const float* amats, hipStream_t s);
 // Floats of one dense round's matrix-core operands: for each of 4 K-steps the
