@@ -61,7 +61,7 @@ struct qs_batch {
   // tables of the last prepared run
   qs::BatchItem* d_items = nullptr;
   void* d_mats = nullptr;
-  bool tiles = true;                  // complex64 kets of >= 12 qubits as tile passes
+  bool tiles = true;                  // kets as tile passes where their gates allow it
   qs::TileItem* d_titems = nullptr;   // tile items of every pass launch
   // what the prepared tables were built from: the circuits, their generations,
   // kmax and the tile switch (a run with the same reuses them)
@@ -102,15 +102,22 @@ void drop_run(qs_batch* b) {
 // nothing to do.
 int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_tile) {
   use_tile->assign(b->count, 0);
-  if (!b->tiles || b->dtype != QS_C64) return QS_OK;
-  constexpr int C = qs::kBatchTileLow, H = qs::kTileRowBits;
+  if (!b->tiles) return QS_OK;
+  const bool c64 = b->dtype == QS_C64;
+  constexpr int H = qs::kTileRowBits;
+  const int C = qs::batch_tile_low(b->dtype);
   std::vector<const qs::TilePlan*> plans(b->count, nullptr);
   size_t maxp = 0;
   for (int i = 0; i < b->count; ++i) {
     qs_circuit* c = circs[i];
-    if (b->n[i] < C + H || c->gates.empty()) continue;
-    if (!c->bplan_ok || c->bplan.C != C) {
-      c->bplan = qs::plan_tiles(c->gates, b->n[i], C, H, 4, qs::matrix_tile_mode(c->gates));
+    if (c->gates.empty()) continue;
+    const qs::TileMode pairs = qs::TileMode::kPairs;
+    const qs::TileMode mode = c64 ? qs::matrix_tile_mode(c->gates) : pairs;
+    // a ket smaller than a tile is planned on the tile's bits (one pass)
+    const int bits = std::max(b->n[i], C + H);
+    if (bits > b->n[i] && mode != pairs) continue;
+    if (!c->bplan_ok || c->bplan.C != C || c->bplan.mode != mode) {
+      c->bplan = qs::plan_tiles(c->gates, bits, C, H, 4, mode);
       c->bplan_ok = true;
     }
     plans[i] = &c->bplan;
@@ -123,7 +130,8 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
   if (!maxp) return QS_OK;
   // rounds of every ket, in ket order; round_base[i] = first round of ket i
   std::vector<int32_t> rtab;
-  std::vector<float> emb, mats;
+  std::vector<float> emb;
+  std::vector<double> mats;
   std::vector<int> round_base(b->count, 0);
   int nround = 0, ndense = 0;
   for (int i = 0; i < b->count; ++i) {
@@ -159,11 +167,12 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
         qs::TileItem it{};
         it.amp_off = b->off[i];
         it.first_tile = L.tiles;
+        it.amps = uint64_t(1) << b->n[i];
         for (int j = 0; j < H; ++j) it.rows.b[j] = st.hb[j];
         it.r0 = round_base[i] + st.r0;
         it.nr = st.nr;
         items.push_back(it);
-        L.tiles += uint64_t(1) << (b->n[i] - C - H);
+        L.tiles += uint64_t(1) << std::max(0, b->n[i] - C - H);
         ++L.nitems;
       }
       if (L.nitems) b->launches.push_back(L);
@@ -171,14 +180,18 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
   auto up256 = [](size_t x) { return (x + 255) / 256 * 256; };
   b->temb_off = up256(rtab.size() * sizeof(int32_t));
   b->tmats_off = b->temb_off + up256(emb.size() * sizeof(float));
-  std::vector<unsigned char> host(b->tmats_off + mats.size() * sizeof(float), 0);
+  const size_t esz = c64 ? sizeof(float) : sizeof(double);
+  std::vector<unsigned char> host(b->tmats_off + mats.size() * esz, 0);
   b->d_titems = static_cast<qs::TileItem*>(qs::device_alloc(items.size() * sizeof(qs::TileItem)));
   b->d_tdata = qs::device_alloc(host.size());
   if (!b->d_titems || !b->d_tdata) return bfail(QS_E_NOMEM, "batch tile tables");
   std::memcpy(host.data(), rtab.data(), rtab.size() * sizeof(int32_t));
   if (!emb.empty()) std::memcpy(host.data() + b->temb_off, emb.data(), emb.size() * sizeof(float));
-  if (!mats.empty())
-    std::memcpy(host.data() + b->tmats_off, mats.data(), mats.size() * sizeof(float));
+  for (size_t j = 0; j < mats.size(); ++j) {
+    const float f = float(mats[j]);
+    std::memcpy(host.data() + b->tmats_off + j * esz,
+                c64 ? static_cast<const void*>(&f) : static_cast<const void*>(&mats[j]), esz);
+  }
   hipError_t e = hipMemcpy(b->d_titems, items.data(), items.size() * sizeof(qs::TileItem),
                            hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(b->d_tdata, host.data(), host.size(), hipMemcpyHostToDevice);
@@ -202,16 +215,23 @@ int prepare(qs_batch* b, qs_circuit* const* circs, int kmax) {
     if (c->n != b->n[i]) return bfail(QS_E_INVAL, "circuit %d has %d qubits, ket %d", i, c->n, b->n[i]);
     for (int q = 0; q < c->n; ++q)
       if (c->pos[q] != q) return bfail(QS_E_UNSUPPORTED, "batched circuits cannot contain SWAP gates");
-    if (!c->planned || c->kmax != kmax)
-      if (int rc = qs::circuit_plan_blocks(c, kmax)) return rc;
-    for (const auto& blk : c->blocks)
-      if (blk.k > 5) return bfail(QS_E_UNSUPPORTED, "batched blocks have at most 5 qubits");
+    for (const auto& g : c->gates)
+      if (g.k > 5) return bfail(QS_E_UNSUPPORTED, "batched blocks have at most 5 qubits");
   }
   drop_run(b);
   std::vector<char> use_tile;
   if (int rc = prepare_tiles(b, circs, &use_tile)) {
     drop_run(b);
     return rc;
+  }
+  for (int i = 0; i < b->count; ++i) {
+    if (use_tile[i])
+      qs::circuit_plan_blocks_later(circs[i], kmax);
+    else if (!circs[i]->planned || circs[i]->kmax != kmax)
+      if (int rc = qs::circuit_plan_blocks(circs[i], kmax)) {
+        drop_run(b);
+        return rc;
+      }
   }
   // matrices: every block of every circuit that runs as blocks
   std::vector<std::vector<uint64_t>> moff(b->count);
@@ -301,7 +321,12 @@ hipError_t enqueue(qs_batch* b) {
     if (L.tile) {
       const char* data = static_cast<const char*>(b->d_tdata);
       const hipError_t e =
-          L.mode == qs::TileMode::kPairs
+          b->dtype == QS_C128
+              ? qs::launch_tile_pair_batch(static_cast<double*>(b->arena), b->d_titems + L.item0,
+                                           L.nitems, L.tiles, data,
+                                           reinterpret_cast<const double*>(data + b->tmats_off),
+                                           b->stream)
+          : L.mode == qs::TileMode::kPairs
               ? qs::launch_tile_pair_batch(static_cast<float*>(b->arena), b->d_titems + L.item0,
                                            L.nitems, L.tiles, data,
                                            reinterpret_cast<const float*>(data + b->tmats_off),

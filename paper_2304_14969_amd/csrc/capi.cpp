@@ -312,6 +312,7 @@ void circuit_invalidate(qs_circuit* c) {
     c->tcache[p].plan = qs::TilePlan();
   }
   c->planned = false;
+  c->due = false;
   c->blocks.clear();
   c->bplan_ok = false;
   c->bplan = qs::TilePlan();

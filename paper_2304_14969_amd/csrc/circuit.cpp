@@ -13,6 +13,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <mutex>
 #include <string>
 
 #include "circuit.h"
@@ -764,6 +765,23 @@ int circuit_plan_blocks(qs_circuit* c, int kmax) {
   c->planned = true;
   return QS_OK;
 }
+
+void circuit_plan_blocks_later(qs_circuit* c, int kmax) {
+  if ((c->planned || c->due) && c->kmax == kmax) return;
+  if (c->planned) circuit_invalidate(c);
+  c->kmax = kmax;
+  c->due = true;
+}
+
+void circuit_blocks_due(const qs_circuit* circuit) {
+  static std::mutex mu;  // two threads may ask about one circuit
+  std::lock_guard<std::mutex> lock(mu);
+  qs_circuit* c = const_cast<qs_circuit*>(circuit);
+  if (!c->due || c->planned) return;
+  c->blocks = fuse(c->gates, c->n, c->kmax);
+  c->planned = true;
+  c->due = false;
+}
 }  // namespace qs
 
 extern "C" {
@@ -867,6 +885,7 @@ int qs_circuit_tile_info(const qs_circuit* c, int dtype, int* passes, int* block
 
 int qs_circuit_info(const qs_circuit* c, int* ngates, int* nblocks, int* max_k) {
   if (!c) return cfail(QS_E_INVAL, "circuit is NULL");
+  qs::circuit_blocks_due(c);
   if (ngates) *ngates = int(c->gates.size());
   if (nblocks) *nblocks = c->planned ? int(c->blocks.size()) : -1;
   if (max_k) {
@@ -879,6 +898,7 @@ int qs_circuit_info(const qs_circuit* c, int* ngates, int* nblocks, int* max_k) 
 
 int qs_circuit_block(const qs_circuit* c, int i, int* k, int* qubits, double* m) {
   if (!c || !k) return cfail(QS_E_INVAL, "NULL argument");
+  qs::circuit_blocks_due(c);
   if (!c->planned) return cfail(QS_E_INVAL, "circuit is not planned");
   if (i < 0 || i >= int(c->blocks.size())) return cfail(QS_E_INVAL, "block %d out of range", i);
   const qs::Block& b = c->blocks[i];

@@ -123,6 +123,10 @@ void embed_round(const cd* u, float* out);
 // recording a choice of run mode (internal planning; qs_circuit_plan does
 // record it).
 int circuit_plan_blocks(qs_circuit* c, int kmax);
+// As if circuit_plan_blocks had been called with this valid width, but leaves
+// the work until someone asks for the blocks (circuit_blocks_due does it).
+void circuit_plan_blocks_later(qs_circuit* c, int kmax);
+void circuit_blocks_due(const qs_circuit* c);
 
 }  // namespace qs
 
@@ -133,6 +137,7 @@ struct qs_circuit {
   std::vector<int> pos;         // logical qubit -> virtual position after all SWAPs
   int kmax = 5;
   bool planned = false;
+  bool due = false;             // blocks of at most kmax qubits are due, not made yet
   std::vector<qs::Block> blocks;
   // device copies of the block matrices, per precision (owned)
   void* dmat[2] = {nullptr, nullptr};

@@ -383,11 +383,14 @@ __device__ __forceinline__ void pair_rounds_f64(Cx<double>* sm, const int4* __re
   }
 }
 
-template <int C, int H, bool STREAM>
+// BOUND: the state may be smaller than the tile (base 0, row bits on from C);
+// indices from `amps` on are zeros and stay out of memory.
+template <int C, int H, bool STREAM, bool BOUND = false>
 __device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t base,
                                                const TileRows& rows,
                                                const int4* __restrict__ rounds, int nrounds,
-                                               const float* __restrict__ mats) {
+                                               const float* __restrict__ mats,
+                                               uint64_t amps = 0) {
   constexpr int TB = C + H;
   constexpr int NT = 1 << (TB - kW);
   constexpr int VPR = (1 << C) / 2;        // float4 vectors per row
@@ -414,7 +417,9 @@ __device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t b
   {
     float4 buf[NV];
 #pragma unroll
-    for (int k = 0; k < NV; ++k) buf[k] = ld16<STREAM>(p4 + glob_k(k) / 2);
+    for (int k = 0; k < NV; ++k)
+      buf[k] = !BOUND || glob_k(k) < amps ? ld16<STREAM>(p4 + glob_k(k) / 2)
+                                          : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int e = threadIdx.x + k * NT;
@@ -432,16 +437,18 @@ __device__ __forceinline__ void tile_pair_body(float* __restrict__ a, uint64_t b
     const int e = threadIdx.x + k * NT;
     const int x = ((e / VPR) << C) | (e % VPR) * 2;
     const int l = plane_pos(x);
-    st16<STREAM>(p4 + glob_k(k) / 2, make_float4(re[l], im[l], re[l + 1], im[l + 1]));
+    if (!BOUND || glob_k(k) < amps)
+      st16<STREAM>(p4 + glob_k(k) / 2, make_float4(re[l], im[l], re[l + 1], im[l + 1]));
   }
 }
 
 // The same pass in complex128.
-template <int C, int H, bool STREAM>
+template <int C, int H, bool STREAM, bool BOUND = false>
 __device__ __forceinline__ void tile_pair_body(double* __restrict__ a, uint64_t base,
                                                const TileRows& rows,
                                                const int4* __restrict__ rounds, int nrounds,
-                                               const double* __restrict__ num) {
+                                               const double* __restrict__ num,
+                                               uint64_t amps = 0) {
   constexpr int TB = C + H, NT = 1 << (TB - kW), NV = (1 << TB) / NT;
   constexpr int RT = NT >> C, RTB = __builtin_ctz(RT);  // tile rows between a thread's entries
   extern __shared__ unsigned char smraw[];
@@ -460,7 +467,8 @@ __device__ __forceinline__ void tile_pair_body(double* __restrict__ a, uint64_t 
   double2* p2 = reinterpret_cast<double2*>(a);
   double2 buf[NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) buf[k] = ld16<STREAM>(p2 + glob_k(k));
+  for (int k = 0; k < NV; ++k)
+    buf[k] = !BOUND || glob_k(k) < amps ? ld16<STREAM>(p2 + glob_k(k)) : make_double2(0.0, 0.0);
 #pragma unroll
   for (int k = 0; k < NV; ++k) sm[wide_pos(threadIdx.x + k * NT)] = {buf[k].x, buf[k].y};
   __syncthreads();
@@ -468,7 +476,7 @@ __device__ __forceinline__ void tile_pair_body(double* __restrict__ a, uint64_t 
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const Cx<double> x = sm[wide_pos(threadIdx.x + k * NT)];
-    st16<STREAM>(p2 + glob_k(k), make_double2(x.r, x.i));
+    if (!BOUND || glob_k(k) < amps) st16<STREAM>(p2 + glob_k(k), make_double2(x.r, x.i));
   }
 }
 
@@ -730,13 +738,15 @@ __global__ void __launch_bounds__(1 << (C + H - kW))
                               amats);
 }
 
-template <int C, int H>
-__global__ void __launch_bounds__(1 << (C + H - kW)) __attribute__((amdgpu_waves_per_eu(4)))
-    k_tile_pair_batch(float* __restrict__ arena, const TileItem* __restrict__ items, int nitems,
-                      const int4* __restrict__ rounds, const float* __restrict__ mats) {
+template <typename R, int C, int H>
+__global__ void __launch_bounds__(1 << (C + H - kW))
+__attribute__((amdgpu_waves_per_eu(kPairWaves<R>)))
+    k_tile_pair_batch(R* __restrict__ arena, const TileItem* __restrict__ items, int nitems,
+                      const int4* __restrict__ rounds, const R* __restrict__ num) {
   uint64_t base;
   const TileItem& it = batch_item<C, H>(items, nitems, &base);
-  tile_pair_body<C, H, false>(arena + 2 * it.amp_off, base, it.rows, rounds + it.r0, it.nr, mats);
+  tile_pair_body<C, H, false, true>(arena + 2 * it.amp_off, base, it.rows, rounds + it.r0, it.nr,
+                                    num, it.amps);
 }
 
 }  // namespace
@@ -886,18 +896,24 @@ hipError_t launch_tile_mfma_batch(float* arena, const TileItem* items, int nitem
   return hipGetLastError();
 }
 
-hipError_t launch_tile_pair_batch(float* arena, const TileItem* items, int nitems, uint64_t tiles,
-                                  const void* rounds, const float* mats, hipStream_t s) {
-  constexpr int C = kBatchTileLow, H = kTileRowBits, TB = C + H;
+template <typename R>
+hipError_t launch_tile_pair_batch(R* arena, const TileItem* items, int nitems, uint64_t tiles,
+                                  const void* rounds, const R* num, hipStream_t s) {
+  constexpr int C = sizeof(R) == 4 ? kBatchTileLow : kBatchTileLowWide, H = kTileRowBits,
+                TB = C + H;
   if (nitems < 1 || tiles < 1 || tiles > 0x7fffffffu) return hipErrorInvalidValue;
-  const size_t bytes = pair_lds<float, TB>();
-  auto kern = k_tile_pair_batch<C, H>;
+  const size_t bytes = pair_lds<R, TB>();
+  auto kern = k_tile_pair_batch<R, C, H>;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
   hipLaunchKernelGGL(kern, dim3(unsigned(tiles)), dim3(1 << (TB - kW)), bytes, s, arena, items,
-                     nitems, static_cast<const int4*>(rounds), mats);
+                     nitems, static_cast<const int4*>(rounds), num);
   return hipGetLastError();
 }
+template hipError_t launch_tile_pair_batch<float>(float*, const TileItem*, int, uint64_t,
+                                                  const void*, const float*, hipStream_t);
+template hipError_t launch_tile_pair_batch<double>(double*, const TileItem*, int, uint64_t,
+                                                   const void*, const double*, hipStream_t);
 
 template hipError_t launch_tile_pass<float>(float*, int, int, const TileRows&, const void*, int,
                                             const void*, const float*, hipStream_t);

@@ -385,19 +385,23 @@ inline int whole_bits(int n) { return n < 10 ? 10 : n; }
 template <typename R>
 hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const R* num,
                         hipStream_t s);
-// Batched complex64 tile passes: one item = one pass of one ket of an arena
-// of n >= kBatchTileLow + kTileRowBits qubits; items sorted by first_tile,
-// the tiles of item i are [first_tile_i, first_tile_{i+1}); its rounds are
-// rounds[r0 .. r0 + nr) (int4 as for launch_tile_pair or launch_tile_mfma).
-constexpr int kBatchTileLow = 5;
+// Batched tile passes: one item = one pass of one ket of an arena; items sorted
+// by first_tile, the tiles of item i are [first_tile_i, first_tile_{i+1}); its
+// rounds are rounds[r0 .. r0 + nr) (int4 as for launch_tile_pair or
+// launch_tile_mfma). Tiles have batch_tile_low + kTileRowBits bits; a pair item
+// may be a smaller ket, alone in its tile (indices from `amps` on are zeros).
+constexpr int kBatchTileLow = 5, kBatchTileLowWide = 4;
+inline int batch_tile_low(int dtype) { return dtype == 1 ? kBatchTileLow : kBatchTileLowWide; }
 struct TileItem {
   uint64_t amp_off;     // amplitude offset of the ket in the arena
   uint64_t first_tile;  // first workgroup of the item
+  uint64_t amps;        // amplitudes of the ket
   TileRows rows;
   int r0, nr;
 };
-hipError_t launch_tile_pair_batch(float* arena, const TileItem* items, int nitems, uint64_t tiles,
-                                  const void* rounds, const float* num, hipStream_t s);
+template <typename R>
+hipError_t launch_tile_pair_batch(R* arena, const TileItem* items, int nitems, uint64_t tiles,
+                                  const void* rounds, const R* num, hipStream_t s);
 hipError_t launch_tile_mfma_batch(float* arena, const TileItem* items, int nitems, uint64_t tiles,
                                   const void* rounds, const float* amats, hipStream_t s);
 // Floats of one dense round's matrix-core operands: for each of 4 K-steps the

@@ -78,3 +78,47 @@ def test_batch_of_every_kind(qs_lib):
             want = dense.apply_matrix(want, w, qubits, m)
         assert_parity(b.amplitudes(i), want, C64, f"ket {i} {names[i]}")
     b.free()
+
+
+@pytest.mark.parametrize("dtype", [C64, C128])
+def test_batch_of_every_width(qs_lib, dtype):
+    """Kets of 1 to 14 qubits in one arena: those smaller than a tile are one
+    pass each, alone in their tile, and leave their neighbours alone."""
+    import workloads as w
+    widths = [3, 14, 1, 2, 11, 12, 5, 10, 13, 4, 6, 9, 7, 8, 1, 11]
+    lists = [w.random_circuit(n, 4, 70 + i) if n > 1 else [("h", 0), ("u3", 0, 0.3, 0.1, 0.2)]
+             for i, n in enumerate(widths)]
+    circs = [qs_lib.Circuit(n).add_gates(x) for n, x in zip(widths, lists)]
+    b = qs_lib.Batch(widths, dtype)
+    for again in range(2):
+        b.reset()
+        b.run(circs)
+        for i, (n, gates) in enumerate(zip(widths, lists)):
+            assert_parity(b.amplitudes(i), dense.run_circuit(dense.zero_state(n), n, gates), dtype,
+                          f"ket {i} n={n}")
+    b.free()
+
+
+def test_batch_leaves_the_blocks_of_its_width(qs_lib):
+    """A circuit that a batch ran as tile passes answers for its blocks as if
+    the batch had planned them, and runs as them when asked to."""
+    n = 12
+    gates = workloads.random_circuit(n, 4, 3)
+    c = qs_lib.Circuit(n).add_gates(gates)
+    assert c.info()["blocks"] == -1
+    b = qs_lib.Batch([n], C64)
+    b.run([c], 3)
+    ref = qs_lib.Circuit(n).add_gates(gates).plan(3)
+    assert c.info() == ref.info()
+    assert c.block(0)[0] == ref.block(0)[0]
+    b.reset()
+    b.run([c], 3)
+    want = dense.run_circuit(dense.zero_state(n), n, gates)
+    assert_parity(b.amplitudes(0), want, C64)
+    b.free()
+    c.use_tiles(False)
+    with qs_lib.State(n, C64) as st:
+        st.run(c)
+        assert_parity(st.amplitudes(), want, C64)
+    c.add_gates([("h", 0)])
+    assert c.info()["blocks"] == -1
