@@ -153,6 +153,11 @@ hipError_t launch_cphase(R* amps, int n, int a, int b, R cr, R ci, hipStream_t s
 template <typename R>
 hipError_t launch_bitswap(R* amps, int n, int a, int b, hipStream_t s);
 
+// Bits exchanged in pairs, in place, in one sweep: image[q] is the bit that
+// bit q's value moves to (image[image[q]] == q).
+template <typename R>
+hipError_t launch_bit_pairs(R* amps, int n, const int* image, hipStream_t s);
+
 // Dense k-qubit block; `mat` is a device array of 2^k x 2^k complex values
 // (interleaved, row-major) in the state's precision, `qubits` the k bits.
 template <typename R>
