@@ -511,6 +511,19 @@ hipError_t launch_col_c(R* a, int n, int start, int len, int lo, int sign, R sca
   return launch_col_cfg<R, G, C, REV, 256, 5>(a, n, start, len, lo, sign, scale, st, s);
 }
 
+// Columns of a strided pass over a small state: as few (down to 64-byte rows)
+// as it takes to give every CU a workgroup; 0: the usual width. A pair of
+// transforms with the usual widths and with these: complex64 28.4 -> 24.4 us at
+// 18 qubits, 38.7 -> 30.3 at 19, 41.8 -> 39.2 at 20 (two workgroups per CU, rows
+// narrower still: 26.3, 33.8 and 45.2).
+template <typename R>
+int small_col_bits(int n, int G) {
+  constexpr int CB = col_bits<R>();
+  int C = CB;
+  while (C > CB - 3 && n - G - C < 8) --C;
+  return C < CB ? C : 0;
+}
+
 // Strided tiles of 2^G rows x 2^C columns: 512-byte rows (64 KiB at G = 7),
 // or 256-byte rows for G = 8 (64 KiB) and, for complex128 or with
 // qft.col_rows >= 1, for G = 7 (32 KiB, more workgroups per CU: a complex128
@@ -520,6 +533,16 @@ template <typename R, int G, bool REV>
 hipError_t launch_col(R* a, int n, int start, int len, int lo, int sign, R scale,
                       const QftTuning& tune, hipStream_t s) {
   constexpr int CB = col_bits<R>();
+  if (tune.col_rows == 0 && tune.threads == 0 && tune.round_bits == 4) {
+    const int st = stream_policy<R>(n, tune);
+    const int rows = small_col_bits<R>(n, G);
+    if (rows == CB - 1)
+      return launch_col_cfg<R, G, CB - 1, REV, 256, 4>(a, n, start, len, lo, sign, scale, st, s);
+    if (rows == CB - 2)
+      return launch_col_cfg<R, G, CB - 2, REV, 256, 4>(a, n, start, len, lo, sign, scale, st, s);
+    if (rows == CB - 3)
+      return launch_col_cfg<R, G, CB - 3, REV, 256, 4>(a, n, start, len, lo, sign, scale, st, s);
+  }
   if constexpr (G == 8) {
     if constexpr (sizeof(R) == 4)
       if (tune.col_rows == 2)  // 128-byte rows, 32 KiB tiles
@@ -640,6 +663,19 @@ int qft_plan(int n, int start, int len, bool rev, const QftTuning& tune, QftPass
   int T = tune.lds_bits > 0 ? tune.lds_bits : 12;
   if (T > lds_bits<R>()) T = lds_bits<R>();
   if (tune.lds_bits == 0 && big && (sizeof(R) == 8 || pass_count(11) <= pass_count(12))) T = 11;
+  // Small states: the smallest tile from 9 bits on that adds no pass (in
+  // complex64 9 or 12). The 12-bit one leaves CUs idle below 20 qubits and
+  // holds few waves for its LDS above. A transform and its inverse with 12
+  // bits and with these: complex64 20.5 -> 17.3 us at 13 qubits, 24.2 -> 18.8 at
+  // 16, 71 -> 69 at 21 (23 qubits would be slower, 160 -> 190: two 7-bit strided
+  // passes); complex128 25.8 -> 18.4 at 14, 44.3 -> 40.8 at 19, 101 -> 84 at 21,
+  // 617 -> 568 at 24, 1307 -> 1203 at 25.
+  if (tune.lds_bits == 0 && !use_reg && n <= (sizeof(R) == 4 ? 22 : 25))
+    for (int t = 9; t < 12; t += sizeof(R) == 4 ? 3 : 1)
+      if (pass_count(t) <= pass_count(12)) {
+        T = t;
+        break;
+      }
   if (T > n) T = n;
   int reg_lo = start > T ? start : T;
   if (!use_reg && reg_lo < col_bits<R>()) reg_lo = col_bits<R>();
