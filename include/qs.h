@@ -132,7 +132,7 @@ int qs_apply_swap(qs_state* st, int a, int b);
 /* Dense k-qubit block (1 <= k <= QS_MAX_FUSED): m is 2^k x 2^k complex
  * (2*4^k doubles), row/column bit j <-> qubits[j]. For every assignment of the
  * other n-k bits, the 2^k amplitudes that differ only in `qubits` are
- * multiplied by m. Blocks of 4 or 5 qubits run on the matrix cores
+ * multiplied by m. Blocks of 4 to 6 qubits run on the matrix cores
  * ("fused.mfma": FP32 for complex64, FP64 for complex128) once the state
  * holds a full tile (2^k x 128 amplitudes in complex64, 2^k x 64 in
  * complex128, more when the block has low bits); other widths and smaller
@@ -423,7 +423,7 @@ int qs_circuit_block(const qs_circuit* c, int i, int* k, int* qubits, double* m)
 /* Apply a circuit to a state of the same width: tile passes or blocks as
  * qs_circuit_use_tiles describes (blocks planned first if needed).
  * Block matrices are uploaded once per precision and kept with the circuit.
- * Blocks of 4-5 qubits run on the matrix cores. A factorized state
+ * Blocks of 4-6 qubits run on the matrix cores. A factorized state
  * takes the gates one by one under its separation policy (see
  * qs_held_count for the gates an exact run holds back); when a gate fails
  * there (QS_E_CAPACITY: a merge past the state's cap), the gates before it
@@ -513,8 +513,9 @@ int qs_check(qs_state* st, double tol);
  *   "qft.lds_bits"   bits of the contiguous LDS tile of the QFT's low pass:
  *                    1 to 13 for complex64 / 12 for complex128 (larger
  *                    values are clamped to that); 0 (default): 12, or 11
- *                    for complex64 states above 256 MiB when that adds no
- *                    pass;
+ *                    for complex64 states above 256 MiB, 9 for those up to
+ *                    22 qubits, and 9 to 11 for complex128 ones up to 25,
+ *                    each when that adds no pass;
  *   "qft.stream"     global accesses of the LDS tile passes: 0 (default)
  *                    streaming (non-temporal) for states above 256 MiB, plain
  *                    below (such states partly stay in the last-level
@@ -598,7 +599,7 @@ int qs_check(qs_state* st, double tol);
  *   "factor.kickback" 1 (default): a held gate whose target is a one-qubit
  *                    subsystem in an eigenstate of its matrix acts on its
  *                    control alone (qs_held_count); 0: off;
- *   "fused.mfma"     1 (default): blocks of 4 or 5 qubits run on the matrix
+ *   "fused.mfma"     1 (default): blocks of 4 to 6 qubits run on the matrix
  *                    cores (FP32 for complex64, FP64 for complex128) when
  *                    their geometry fits; 0: vector FMA.
  * QS_E_INVAL for an unknown key or a value out of range. */

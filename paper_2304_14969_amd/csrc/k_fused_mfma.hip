@@ -1,10 +1,10 @@
-// Dense k-qubit block (k = 4, 5) on the matrix cores: complex64 states on the
+// Dense k-qubit block (k = 4 to 6) on the matrix cores: complex64 states on the
 // FP32 ones, complex128 states on the FP64 ones.
 //
 // For every assignment of the n-k bits outside the block (a "group"), the 2^k
 // amplitudes of the group are multiplied by the block's complex matrix U. Over
 // a tile of groups this is a complex product Y = U X with X = 2^k rows x
-// groups, computed as three real products on v_mfma_f32_16x16x4f32 (or
+// groups, computed (k = 4, 5; 6 below) as three real products on v_mfma_f32_16x16x4f32 (or
 // v_mfma_f64_16x16x4f64):
 //   P1 = Re U X_r,  P2 = Im U X_i,  P3 = (Re U + Im U)(X_r + X_i),
 //   Re Y = P1 - P2,  Im Y = P3 - P1 - P2
@@ -232,6 +232,148 @@ k_fused_mfma(R* __restrict__ a, FusedGeom g, const R* __restrict__ mat) {
   }
 }
 
+// ---- 6-qubit blocks
+// The matrix (64 x 64) stays in LDS for the workgroup's life and its operands
+// are read from there step by step (in registers they would take 192). A
+// workgroup takes tiles of 64 (complex64) or 32 (complex128) groups, one after
+// another, the next one's loads on their way during the products; a wavefront
+// owns 16 groups and all 64 output rows, or half of the rows in complex128.
+// Four real products (Re U X_r - Im U X_i, Re U X_i + Im U X_r), as precise as
+// the vector kernel, which a thread's chain of 4096 products held up. The
+// matrix cores bound it: 24 qubits complex64, 8.6 Gflop and 0.27 GB, take 90-93
+// us (vector kernel 232-279, the 121 Tflop/s of the instruction 71), 23 qubits
+// complex128 88-90 us (364-368); states of a few tiles 20-27 us (101-170),
+// most of it the first fetch of code and matrix.
+template <typename R> struct Prec6;
+template <> struct Prec6<float> { static constexpr int GB = 6, RB = 4; };
+template <> struct Prec6<double> { static constexpr int GB = 5, RB = 2; };
+
+template <typename R, bool NT>
+__global__ void __launch_bounds__(kThreads) k_fused6_mfma(R* __restrict__ a, FusedGeom g,
+                                                          const R* __restrict__ mat,
+                                                          unsigned tiles) {
+  using P = Prec<R>;
+  using Cx = typename P::Cx;
+  using V = typename P::V;
+  using Acc = typename P::Acc;
+  constexpr int K = 6, D = 64, S4 = D / 4, GB = Prec6<R>::GB, RB = Prec6<R>::RB, TB = K + GB;
+  constexpr int BLK = (1 << GB) / 16;   // 16-group blocks of a tile
+  static_assert(BLK * (4 / RB) == 4, "4 wavefronts");
+  extern __shared__ __align__(16) unsigned char lds6[];
+  Cx* sm = reinterpret_cast<Cx*>(lds6);
+  Cx* smat = sm + (1 << TB);
+  const int C = g.C, h = g.h, swz = g.swz;
+  auto lp = [&](int x) { return x ^ ((x >> swz) & 15); };  // plain for swz = 16
+  auto toff = [&](int c) {
+    int t = 0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) t |= ((c >> j) & 1) << g.tpos[j];
+    return t;
+  };
+  // entry (r, c) at r D + (c ^ 4 (r mod 16)): the 16 rows x 4 columns of an
+  // operand read cover every bank equally
+  auto mpos = [](int r, int c) { return r * D + (c ^ (4 * (r & 15))); };
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int q = lane >> 4, col = lane & 15;
+  const int blk = wave % BLK, row0 = (wave / BLK) * 16 * RB;
+  int tb = 16 * blk + col;  // this lane's group: zeros at the block's tile bits
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+    if (i < g.nlow) tb = insert_zero32(tb, g.lowblk[i]);
+  const int pin = lp(tb | toff(q)), pout = lp(tb | toff(P::QS * q));
+  constexpr int NV = (1 << TB) / P::AP / kThreads;
+  // amplitude of tile entry t, which is linear over OR: the tile's part, this
+  // thread's and vector v's (uniform), of which the last two are kept
+  auto glob = [&](int t) {
+    uint64_t x = uint64_t(t & ((1 << C) - 1));
+#pragma unroll
+    for (int i = 0; i < K; ++i) x |= uint64_t((t >> (C + i)) & 1) << g.qhi[i];  // t < 2^(C + h)
+    return x;
+  };
+  auto base = [&](unsigned tile) {
+    uint64_t ob = uint64_t(tile) << C;
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      if (i < h) ob = insert_zero64(ob, g.qhi[i]);
+    return ob;
+  };
+  const int te = int(threadIdx.x) * P::AP;
+  const uint64_t gt = glob(te);
+  uint64_t gv[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) gv[v] = glob(v * kThreads * P::AP);
+  V buf[NV];
+  auto fetch = [&](uint64_t ob) {
+    const R* p = a + 2 * (ob | gt);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) buf[v] = ld16<NT>(reinterpret_cast<const V*>(p + 2 * gv[v]));
+  };
+  constexpr int NM = D * D / kThreads;
+  Cx mreg[NM];
+#pragma unroll
+  for (int v = 0; v < NM; ++v) mreg[v] = reinterpret_cast<const Cx*>(mat)[threadIdx.x + v * kThreads];
+  uint64_t ob = base(blockIdx.x);
+  fetch(ob);
+#pragma unroll
+  for (int v = 0; v < NM; ++v) {
+    const int e = threadIdx.x + v * kThreads;
+    smat[mpos(e / D, e % D)] = mreg[v];
+  }
+  for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const int t = lp(te + v * kThreads * P::AP);
+      if constexpr (P::AP == 2) {
+        const V x = buf[v];
+        reinterpret_cast<V*>(sm)[t >> 1] = (t & 1) ? V{x.z, x.w, x.x, x.y} : x;
+      } else {
+        sm[t] = buf[v];
+      }
+    }
+    __syncthreads();
+    const uint64_t here = ob;
+    if (tile + gridDim.x < tiles) {  // the next tile is on its way meanwhile
+      ob = base(tile + gridDim.x);
+      fetch(ob);
+    }
+    Acc yr[RB], yi[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) yr[rb] = yi[rb] = Acc{};
+#pragma unroll
+    for (int s = 0; s < S4; ++s) {
+      const Cx v = sm[pin ^ lp(toff(4 * s))];
+      const R nx = -v.y;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const Cx u = smat[mpos(row0 + 16 * rb + col, 4 * s + q)];
+        yr[rb] = mfma16(u.x, v.x, yr[rb]);
+        yi[rb] = mfma16(u.x, v.y, yi[rb]);
+        yr[rb] = mfma16(u.y, nx, yr[rb]);
+        yi[rb] = mfma16(u.y, v.x, yi[rb]);
+      }
+    }
+    if (BLK < 4) __syncthreads();  // wavefronts that share groups have read them
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        sm[pout ^ lp(toff(row0 + 16 * rb + P::IS * i))] = Cx{yr[rb][i], yi[rb][i]};
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const int l = lp(te + v * kThreads * P::AP);
+      V* dst = reinterpret_cast<V*>(a + 2 * (here | gt | gv[v]));
+      if constexpr (P::AP == 2) {
+        const V x = reinterpret_cast<const V*>(sm)[l >> 1];
+        st16<NT>(dst, (l & 1) ? V{x.z, x.w, x.x, x.y} : x);
+      } else {
+        st16<NT>(dst, sm[l]);
+      }
+    }
+    __syncthreads();  // the next tile takes this one's place
+  }
+}
+
 }  // namespace
 
 namespace {
@@ -259,7 +401,7 @@ int lds_steps(const int* entry) {
 // wavefront 0 decide. 4-qubit blocks keep the plain layout: eight of their
 // workgroups share a CU and hide the conflicts (swizzling measured slower).
 int lds_swizzle(const FusedGeom& g) {
-  if (g.k != 5) return 16;
+  if (g.k < 5) return 16;
   auto toff = [&](int c) {
     int t = 0;
     for (int j = 0; j < g.k; ++j) t |= ((c >> j) & 1) << g.tpos[j];
@@ -289,9 +431,10 @@ int lds_swizzle(const FusedGeom& g) {
 
 // Tile geometry for a block on `qubits` (k of them) in an n-qubit state of
 // amp_bytes-byte amplitudes, or false if the state is too small for a tile of
-// 128 (complex64) or 64 (complex128) groups.
+// 128 (complex64) or 64 (complex128) groups, half of that for k = 6.
 bool fused_geometry(int n, const int* qubits, int k, FusedGeom* g, int amp_bytes) {
-  const int group_bits = amp_bytes == 8 ? Prec<float>::GB : Prec<double>::GB;
+  const int group_bits = k == 6 ? (amp_bytes == 8 ? Prec6<float>::GB : Prec6<double>::GB)
+                                : (amp_bytes == 8 ? Prec<float>::GB : Prec<double>::GB);
   // smallest C such that the block bits below C leave group_bits free low bits
   int C = group_bits;
   for (;;) {
@@ -323,7 +466,7 @@ bool fused_geometry(int n, const int* qubits, int k, FusedGeom* g, int amp_bytes
       g->tpos[j] = C + rank;
     }
   }
-  g->swz = amp_bytes == 8 ? lds_swizzle(*g) : 16;
+  g->swz = amp_bytes == 8 || k == 6 ? lds_swizzle(*g) : 16;
   return true;
 }
 
@@ -331,11 +474,22 @@ namespace {
 template <typename R>
 hipError_t launch_mfma_block(R* a, int n, const int* qubits, int k, const R* mat, hipStream_t s) {
   FusedGeom g{};
-  if ((k != 4 && k != 5) || !fused_geometry(n, qubits, k, &g, int(2 * sizeof(R))))
+  if (k < 4 || k > 6 || !fused_geometry(n, qubits, k, &g, int(2 * sizeof(R))))
     return hipErrorNotSupported;
   const uint64_t tiles = uint64_t(1) << (n - g.C - g.h);
   if (tiles > 0x7fffffffu) return hipErrorNotSupported;
   const bool nt = stream_sweep(n, 2 * sizeof(R), g.C);  // rows of 2^C contiguous amplitudes
+  if (k == 6) {
+    const size_t bytes = ((size_t(1) << (6 + Prec6<R>::GB)) + 64 * 64) * 2 * sizeof(R);
+    auto kern6 = nt ? k_fused6_mfma<R, true> : k_fused6_mfma<R, false>;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern6),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+    // as many workgroups as the LDS of the 256 CUs holds at once
+    const unsigned most = 256 * unsigned(163840 / bytes);
+    hipLaunchKernelGGL(kern6, dim3(tiles < most ? unsigned(tiles) : most), dim3(kThreads), bytes, s,
+                       a, g, mat, unsigned(tiles));
+    return hipGetLastError();
+  }
   const bool sw = g.swz < 16;
   decltype(&k_fused_mfma<R, 4, true, true>) kern;
   if (k == 4)

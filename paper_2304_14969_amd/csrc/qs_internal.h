@@ -182,7 +182,7 @@ struct FusedGeom {
 };
 bool fused_geometry(int n, const int* qubits, int k, FusedGeom* g, int amp_bytes);
 
-// block of k = 4 or 5 qubits on the matrix cores (v_mfma_f32_16x16x4f32 for
+// block of k = 4 to 6 qubits on the matrix cores (v_mfma_f32_16x16x4f32 for
 // complex64, v_mfma_f64_16x16x4f64 for complex128); returns
 // hipErrorNotSupported when the state is too small for the tile.
 hipError_t launch_fused_mfma(float* amps, int n, const int* qubits, int k, const float* mat,
