@@ -50,7 +50,7 @@ __device__ __forceinline__ uint64_t insert_zero64(uint64_t x, int pos) {
   const uint64_t lo = x & ((uint64_t(1) << pos) - 1);
   return lo | ((x ^ lo) << 1);
 }
-__device__ __forceinline__ int insert_zero32(int x, int pos) {
+__host__ __device__ __forceinline__ int insert_zero32(int x, int pos) {
   const int lo = x & ((1 << pos) - 1);
   return lo | ((x ^ lo) << 1);
 }
@@ -92,7 +92,6 @@ k_fused_mfma(R* __restrict__ a, FusedGeom g, const R* __restrict__ mat) {
   constexpr int NB = (1 << P::GB) / 64;  // 16-group blocks per wave
   constexpr int BKT = RB == 1 && NB >= 2 ? 2 : 1;  // blocks in flight per wave
   constexpr int TB = K + P::GB;       // tile bits
-  constexpr int LAP = P::AP == 2 ? 1 : 0;
   // k = 5: 32 KiB tile + 8 KiB matrix (complex64, four workgroups fill a
   // CU's LDS) or 32 + 16 KiB (complex128, three)
   __shared__ __align__(16) Cx sm[1 << TB];
@@ -112,18 +111,32 @@ k_fused_mfma(R* __restrict__ a, FusedGeom g, const R* __restrict__ mat) {
   auto mpos = [](int r, int c) { return r * D + (c ^ (4 * (r & (D / 4 - 1)))); };
 
   // global index of tile entry t: low C bits in place, tile bit C+i -> qhi[i],
-  // the workgroup index fills the remaining bits
+  // the workgroup index fills the remaining bits. It is linear over OR: this
+  // thread's part is computed once, that of its vector v (entry v kThreads AP
+  // on) is uniform. Loops over the block's bits are unrolled, as their scalar
+  // loads would otherwise wait one by one. 5-qubit blocks with bits above the
+  // rows, 24 qubits complex64: 60-67 -> 48-52 us, 23 qubits complex128 58-69
+  // -> 47-51; 4-qubit ones 38-45 -> 37-41.
   uint64_t ob = uint64_t(blockIdx.x) << C;
-  for (int i = 0; i < h; ++i) ob = insert_zero64(ob, g.qhi[i]);
-  auto glob = [&](int t) {
-    uint64_t x = ob | uint64_t(t & ((1 << C) - 1));
-    for (int i = 0; i < h; ++i) x |= uint64_t((t >> (C + i)) & 1) << g.qhi[i];
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+    if (i < h) ob = insert_zero64(ob, g.qhi[i]);
+  auto glob = [&](int t) {  // t < 2^(C + h)
+    uint64_t x = uint64_t(t & ((1 << C) - 1));
+#pragma unroll
+    for (int i = 0; i < K; ++i) x |= uint64_t((t >> (C + i)) & 1) << g.qhi[i];
     return x;
   };
-  // tile entry of this thread's vector e: 2^h rows of 2^C amplitudes, AP
-  // amplitudes per vector
-  const int vrow = C - LAP;  // log2 vectors per row
-  auto tent = [&](int e) { return ((e >> vrow) << C) | ((e & ((1 << vrow) - 1)) << LAP); };
+  const int te = int(threadIdx.x) * P::AP;
+  R* at = a + 2 * (ob | glob(te));
+  constexpr int NV = (1 << TB) / P::AP / kThreads;
+  uint64_t gb[4];  // vectors 1, 2, 4, 8
+#pragma unroll
+  for (int j = 0; j < 4; ++j) gb[j] = glob((kThreads * P::AP) << j);
+  auto gv = [&](int v) {
+    return (v & 1 ? gb[0] : 0) | (v & 2 ? gb[1] : 0) | (v & 4 ? gb[2] : 0) | (v & 8 ? gb[3] : 0);
+  };
+  static_assert(NV <= 16, "four bits of vectors");
 
   // the matrix first, then the tile (the matrix loads complete first)
   constexpr int NM = D * D / kThreads;
@@ -131,11 +144,10 @@ k_fused_mfma(R* __restrict__ a, FusedGeom g, const R* __restrict__ mat) {
   Cx mreg[NM];
 #pragma unroll
   for (int v = 0; v < NM; ++v) mreg[v] = reinterpret_cast<const Cx*>(mat)[threadIdx.x + v * kThreads];
-  constexpr int NV = (1 << TB) / P::AP / kThreads;
   V buf[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v)
-    buf[v] = ld16<NT>(reinterpret_cast<const V*>(a + 2 * glob(tent(threadIdx.x + v * kThreads))));
+    buf[v] = ld16<NT>(reinterpret_cast<const V*>(at + 2 * gv(v)));
 #pragma unroll
   for (int v = 0; v < NM; ++v) {
     const int e = threadIdx.x + v * kThreads;
@@ -143,7 +155,7 @@ k_fused_mfma(R* __restrict__ a, FusedGeom g, const R* __restrict__ mat) {
   }
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    const int t = lp(tent(threadIdx.x + v * kThreads));
+    const int t = lp(te + v * kThreads * P::AP);
     if constexpr (P::AP == 2) {
       // entries t and t + 1 (t even) land at lp(t) and lp(t) ^ 1: one
       // 16-byte write, its halves swapped when lp(t) is odd
@@ -180,7 +192,9 @@ k_fused_mfma(R* __restrict__ a, FusedGeom g, const R* __restrict__ mat) {
 #pragma unroll
     for (int j = 0; j < BKT; ++j) {
       int tb = wave * (16 * NB) + 16 * (b0 + j) + col;
-      for (int i = 0; i < g.nlow; ++i) tb = insert_zero32(tb, g.lowblk[i]);
+#pragma unroll
+      for (int i = 0; i < K; ++i)
+        if (i < g.nlow) tb = insert_zero32(tb, g.lowblk[i]);
       pin[j] = lp(tb | qin);
       pout[j] = lp(tb | qout);
     }
@@ -220,9 +234,8 @@ k_fused_mfma(R* __restrict__ a, FusedGeom g, const R* __restrict__ mat) {
   // store the tile
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    const int t = tent(threadIdx.x + v * kThreads);
-    const int l = lp(t);
-    V* dst = reinterpret_cast<V*>(a + 2 * glob(t));
+    const int l = lp(te + v * kThreads * P::AP);
+    V* dst = reinterpret_cast<V*>(at + 2 * gv(v));
     if constexpr (P::AP == 2) {
       const V x = reinterpret_cast<const V*>(sm)[l >> 1];
       st16<NT>(dst, (l & 1) ? V{x.z, x.w, x.x, x.y} : x);
@@ -240,10 +253,9 @@ k_fused_mfma(R* __restrict__ a, FusedGeom g, const R* __restrict__ mat) {
 // owns 16 groups and all 64 output rows, or half of the rows in complex128.
 // Four real products (Re U X_r - Im U X_i, Re U X_i + Im U X_r), as precise as
 // the vector kernel, which a thread's chain of 4096 products held up. The
-// matrix cores bound it: 24 qubits complex64, 8.6 Gflop and 0.27 GB, take 90-93
+// matrix cores bound it: 24 qubits complex64, 8.6 Gflop and 0.27 GB, take 88-92
 // us (vector kernel 232-279, the 121 Tflop/s of the instruction 71), 23 qubits
-// complex128 88-90 us (364-368); states of a few tiles 20-27 us (101-170),
-// most of it the first fetch of code and matrix.
+// complex128 84-88 us (364-368); states of a few tiles 12-13 us (101-170).
 template <typename R> struct Prec6;
 template <> struct Prec6<float> { static constexpr int GB = 6, RB = 4; };
 template <> struct Prec6<double> { static constexpr int GB = 5, RB = 2; };
@@ -299,14 +311,18 @@ __global__ void __launch_bounds__(kThreads) k_fused6_mfma(R* __restrict__ a, Fus
   };
   const int te = int(threadIdx.x) * P::AP;
   const uint64_t gt = glob(te);
-  uint64_t gv[NV];
+  uint64_t gb[3];  // vectors 1, 2, 4
 #pragma unroll
-  for (int v = 0; v < NV; ++v) gv[v] = glob(v * kThreads * P::AP);
+  for (int j = 0; j < 3; ++j) gb[j] = glob((kThreads * P::AP) << j);
+  auto gv = [&](int v) {
+    return (v & 1 ? gb[0] : 0) | (v & 2 ? gb[1] : 0) | (v & 4 ? gb[2] : 0);
+  };
+  static_assert(NV == 8, "three bits of vectors");
   V buf[NV];
   auto fetch = [&](uint64_t ob) {
     const R* p = a + 2 * (ob | gt);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) buf[v] = ld16<NT>(reinterpret_cast<const V*>(p + 2 * gv[v]));
+    for (int v = 0; v < NV; ++v) buf[v] = ld16<NT>(reinterpret_cast<const V*>(p + 2 * gv(v)));
   };
   constexpr int NM = D * D / kThreads;
   Cx mreg[NM];
@@ -362,7 +378,7 @@ __global__ void __launch_bounds__(kThreads) k_fused6_mfma(R* __restrict__ a, Fus
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int l = lp(te + v * kThreads * P::AP);
-      V* dst = reinterpret_cast<V*>(a + 2 * (here | gt | gv[v]));
+      V* dst = reinterpret_cast<V*>(a + 2 * (here | gt | gv(v)));
       if constexpr (P::AP == 2) {
         const V x = reinterpret_cast<const V*>(sm)[l >> 1];
         st16<NT>(dst, (l & 1) ? V{x.z, x.w, x.x, x.y} : x);
@@ -378,18 +394,11 @@ __global__ void __launch_bounds__(kThreads) k_fused6_mfma(R* __restrict__ a, Fus
 
 namespace {
 // Cost of one wavefront LDS access of 8-byte entries: 32 banks of 4 bytes,
-// so entry x occupies bank pair x mod 16; distinct entries on one pair are
-// served one after another (the wavefront takes at least 4 such steps).
+// so entry x occupies bank pair x mod 16; the (64 distinct) entries on one
+// pair are served one after another.
 int lds_steps(const int* entry) {
-  int cnt[16] = {}, seen[64], ns = 0;
-  int worst = 0;
-  for (int l = 0; l < 64; ++l) {
-    bool dup = false;
-    for (int i = 0; i < ns && !dup; ++i) dup = seen[i] == entry[l];
-    if (dup) continue;
-    seen[ns++] = entry[l];
-    worst = std::max(worst, ++cnt[entry[l] & 15]);
-  }
+  int cnt[16] = {}, worst = 0;
+  for (int l = 0; l < 64; ++l) worst = std::max(worst, ++cnt[entry[l] & 15]);
   return worst;
 }
 
@@ -407,19 +416,20 @@ int lds_swizzle(const FusedGeom& g) {
     for (int j = 0; j < g.k; ++j) t |= ((c >> j) & 1) << g.tpos[j];
     return t;
   };
+  int xr[64], xw[64];
+  for (int lane = 0; lane < 64; ++lane) {
+    const int q = lane >> 4;
+    int tb = lane & 15;
+    for (int i = 0; i < g.nlow; ++i) tb = insert_zero32(tb, g.lowblk[i]);
+    xr[lane] = tb | toff(q);
+    xw[lane] = tb | toff(4 * q);
+  }
   int best = 16, best_cost = 1 << 30, plain_reads = 0;
   for (int sw : {16, 4, 5, 6, 7, 8, 9, 10, 11}) {
     int rd[64], wr[64];
     for (int lane = 0; lane < 64; ++lane) {
-      const int q = lane >> 4, col = lane & 15;
-      int tb = col;
-      for (int i = 0; i < g.nlow; ++i) {
-        const int lo = tb & ((1 << g.lowblk[i]) - 1);
-        tb = lo | ((tb ^ lo) << 1);
-      }
-      const int xr = tb | toff(q), xw = tb | toff(4 * q);
-      rd[lane] = xr ^ ((xr >> sw) & 15);
-      wr[lane] = xw ^ ((xw >> sw) & 15);
+      rd[lane] = xr[lane] ^ ((xr[lane] >> sw) & 15);
+      wr[lane] = xw[lane] ^ ((xw[lane] >> sw) & 15);
     }
     const int reads = lds_steps(rd), cost = 64 * reads + lds_steps(wr);
     if (sw == 16) plain_reads = reads;
