@@ -210,12 +210,13 @@ struct ProfScope {
   }
 };
 
+const char* const kFusedNames[] = {"", "fused1", "fused2", "fused3", "fused4", "fused5", "fused6"};
+
 // Dense block on physical bits phys[0..k) with a device matrix in the state's
 // precision: blocks of 4 to 6 qubits go to the matrix cores (FP32 for
 // complex64, FP64 for complex128) when the state holds a full tile,
 // everything else to the vector-FMA kernel.
 hipError_t launch_block(qs_state* st, const int* phys, int k, const void* dmat) {
-  static const char* names[] = {"", "fused1", "fused2", "fused3", "fused4", "fused5", "fused6"};
   static const char* mnames[] = {"", "", "", "", "fused4_mfma", "fused5_mfma",
                                  "fused6_mfma"};
   const double bytes = 2.0 * std::ldexp(1.0, st->n) * ab(st);
@@ -228,7 +229,7 @@ hipError_t launch_block(qs_state* st, const int* phys, int k, const void* dmat) 
       return qs::launch_fused_mfma(static_cast<float*>(st->amps), st->n, phys, k,
                                    static_cast<const float*>(dmat), st->stream);
     }
-    ProfScope ps(st, names[k], bytes);
+    ProfScope ps(st, kFusedNames[k], bytes);
     return qs::launch_apply_fused(static_cast<float*>(st->amps), st->n, phys, k,
                                   static_cast<const float*>(dmat), st->stream);
   }
@@ -237,7 +238,7 @@ hipError_t launch_block(qs_state* st, const int* phys, int k, const void* dmat) 
     return qs::launch_fused_mfma(static_cast<double*>(st->amps), st->n, phys, k,
                                  static_cast<const double*>(dmat), st->stream);
   }
-  ProfScope ps(st, names[k], bytes);
+  ProfScope ps(st, kFusedNames[k], bytes);
   return qs::launch_apply_fused(static_cast<double*>(st->amps), st->n, phys, k,
                                 static_cast<const double*>(dmat), st->stream);
 }
@@ -835,6 +836,14 @@ int qs_apply_fused(qs_state* st, const int* qubits, int k, const double* m) {
   }
   if (st->fact) return fact_rc(st, qs::fact_apply(st->fact, qubits, k, m));
   hipError_t e;
+  if (k <= 3) {
+    ProfScope ps(st, kFusedNames[k], 2.0 * std::ldexp(1.0, st->n) * ab(st));
+    e = st->dtype == QS_C64 ? qs::launch_apply_small(static_cast<float*>(st->amps), st->n, phys, k,
+                                                     m, st->stream)
+                            : qs::launch_apply_small(static_cast<double*>(st->amps), st->n, phys, k,
+                                                     m, st->stream);
+    return device_error(st, e, "apply_fused");
+  }
   if (st->dtype == QS_C64) {
     std::vector<float> mf(2 * D * D);
     for (size_t i = 0; i < mf.size(); ++i) mf[i] = static_cast<float>(m[i]);

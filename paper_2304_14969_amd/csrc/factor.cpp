@@ -1239,6 +1239,10 @@ int fact_apply(FactorState* f, const int* qubits, int k, const double* m) {
       for (int i = 0; i < 4; ++i) { mm.re[i] = m[2 * i]; mm.im[i] = m[2 * i + 1]; }
       e = launch_apply_1q(static_cast<double*>(S.amps), S.nq, local[0], mm, f->stream);
     }
+  } else if (k <= 3) {
+    e = f->dtype == QS_C64
+            ? launch_apply_small(static_cast<float*>(S.amps), S.nq, local, k, m, f->stream)
+            : launch_apply_small(static_cast<double*>(S.amps), S.nq, local, k, m, f->stream);
   } else {
     const size_t D = size_t(1) << k;
     e = upload(f, f->mat, m, D * D);

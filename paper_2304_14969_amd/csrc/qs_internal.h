@@ -163,7 +163,7 @@ hipError_t launch_bit_pairs(R* amps, int n, const int* image, hipStream_t s);
 template <typename R>
 hipError_t launch_apply_fused(R* amps, int n, const int* qubits, int k, const R* mat,
                               hipStream_t s);
-// The same for k <= 2 with the host matrix (FP64, interleaved, row-major)
+// The same for k <= 3 with the host matrix (FP64, interleaved, row-major)
 // cast to R and passed in the kernel arguments: no device copy of it.
 template <typename R>
 hipError_t launch_apply_small(R* amps, int n, const int* qubits, int k, const double* host_mat,
