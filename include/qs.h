@@ -135,8 +135,8 @@ int qs_apply_swap(qs_state* st, int a, int b);
  * multiplied by m. Blocks of 4 to 6 qubits run on the matrix cores
  * ("fused.mfma": FP32 for complex64, FP64 for complex128) once the state
  * holds a full tile (2^k x 128 amplitudes in complex64, 2^k x 64 in
- * complex128, more when the block has low bits); other widths and smaller
- * states on vector FMA. */
+ * complex128, half of that for 6 qubits); other widths and smaller states on
+ * vector FMA. */
 int qs_apply_fused(qs_state* st, const int* qubits, int k, const double* m);
 
 /* A named gate (QS_GATE_* below) built in float64 inside the library and

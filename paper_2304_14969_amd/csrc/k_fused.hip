@@ -119,6 +119,61 @@ __global__ void __launch_bounds__(kBlock) k_fused_arg(R* __restrict__ a, uint64_
   }
 }
 
+// Blocks of 4 to 6 qubits on states below a matrix-core tile (at most 2^11
+// amplitudes): state and matrix in the LDS of one workgroup, one thread per
+// output amplitude (two at 2^11). A thread per group, as above, leaves 8 to 128
+// threads with chains of 256 to 4096 products. The rows of a group are on
+// consecutive lanes: an input amplitude is a broadcast, and entry (r, c) of the
+// matrix at r D + (c ^ r) keeps a column's reads on different banks. Sums run
+// over c in the vector kernel's order. 9 qubits complex64, k = 4, 5, 6: 7.8, 22.6,
+// 94 -> 6.6, 6.2, 8.1 us, 11 qubits -, 22, 95 -> -, 8.1, 12.4; 10 qubits
+// complex128 -, 18, 165 -> -, 6.8, 11.2.
+constexpr int kSmallThreads = 1024;
+template <typename R, int K>
+__global__ void __launch_bounds__(kSmallThreads) k_fused_small(R* __restrict__ a, int n, Block6 b,
+                                                               const R* __restrict__ mat) {
+  constexpr int D = 1 << K;
+  extern __shared__ __align__(16) unsigned char small_lds[];
+  Cx<R>* M = reinterpret_cast<Cx<R>*>(small_lds);
+  Cx<R>* x = M + D * D;
+  const int N = 1 << n;
+  for (int e = threadIdx.x; e < N; e += kSmallThreads) x[e] = reinterpret_cast<const Cx<R>*>(a)[e];
+  for (int e = threadIdx.x; e < D * D; e += kSmallThreads)
+    M[(e & ~(D - 1)) | ((e ^ (e >> K)) & (D - 1))] = reinterpret_cast<const Cx<R>*>(mat)[e];
+  __syncthreads();
+  for (int o = threadIdx.x; o < N; o += kSmallThreads) {
+    const int r = o & (D - 1);
+    int base = o >> K, bit[K], at = 0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) base = int(insert_zero(base, b.sorted[j]));
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      bit[j] = 1 << b.q[j];
+      at |= r >> j & 1 ? bit[j] : 0;
+    }
+    R yr = 0, yi = 0;
+#pragma unroll 8
+    for (int c = 0; c < D; ++c) {
+      int t = base;
+#pragma unroll
+      for (int j = 0; j < K; ++j) t |= c >> j & 1 ? bit[j] : 0;
+      const Cx<R> m = M[(r << K) | (c ^ r)], v = x[t];
+      yr = fmadd(m.r, v.r, fmadd(-m.i, v.i, yr));
+      yi = fmadd(m.r, v.i, fmadd(m.i, v.r, yi));
+    }
+    reinterpret_cast<Cx<R>*>(a)[base | at] = {yr, yi};
+  }
+}
+
+template <typename R, int K>
+hipError_t launch_small_state(R* a, int n, const Block6& b, const R* mat, hipStream_t s) {
+  const size_t bytes = ((size_t(1) << (2 * K)) + (size_t(1) << n)) * sizeof(Cx<R>);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_fused_small<R, K>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+  hipLaunchKernelGGL((k_fused_small<R, K>), dim3(1), dim3(kSmallThreads), bytes, s, a, n, b, mat);
+  return hipGetLastError();
+}
+
 unsigned fused_grid(uint64_t groups) {
   const uint64_t want = (groups + kBlock - 1) / kBlock, cap = uint64_t(1) << 20;
   return static_cast<unsigned>(want < cap ? (want > 0 ? want : 1) : cap);
@@ -183,6 +238,11 @@ template <typename R>
 hipError_t launch_apply_fused(R* a, int n, const int* qubits, int k, const R* mat,
                               hipStream_t s) {
   const Block6 b = make_block(qubits, k);
+  if (k >= 4 && n <= 11) switch (k) {
+      case 4: return launch_small_state<R, 4>(a, n, b, mat, s);
+      case 5: return launch_small_state<R, 5>(a, n, b, mat, s);
+      case 6: return launch_small_state<R, 6>(a, n, b, mat, s);
+    }
   switch (k) {
     case 1: return launch_k<R, 1>(a, n, b, mat, s);
     case 2: return launch_k<R, 2>(a, n, b, mat, s);

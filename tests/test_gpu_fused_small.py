@@ -1,5 +1,6 @@
-"""Blocks whose matrix rides in the kernel arguments, from states of only the
-block's qubits up, against the dense oracle; dense and factorized states."""
+"""Blocks whose matrix rides in the kernel arguments, and blocks on states below
+a matrix-core tile, from states of only the block's qubits up, against the
+dense oracle; dense and factorized states."""
 import numpy as np
 import pytest
 
@@ -45,3 +46,18 @@ def test_argument_blocks(qs_lib, n, k, dtype):
         assert_parity(dn.amplitudes(), want, dtype, f"factorized k={k} n={n}")
         st.free()
         dn.free()
+
+
+@pytest.mark.parametrize("dtype", [C64, C128])
+@pytest.mark.parametrize("k", [4, 5, 6])
+@pytest.mark.parametrize("n", [6, 7, 9, 10, 11, 12])
+def test_blocks_on_small_states(qs_lib, n, k, dtype):
+    a = workloads.gaussian_state(n, n)
+    rng = np.random.default_rng(n + k)
+    with qs_lib.State(n, dtype) as st:
+        for i in range(6):
+            bits = [int(x) for x in rng.choice(n, size=k, replace=False)]
+            m = haar(2 ** k, 10 * i + k)
+            st.set_amplitudes(a)
+            st.apply_fused(bits, m)
+            assert_parity(st.amplitudes(), dense.apply_matrix(a, n, bits, m), dtype, f"{bits}")
