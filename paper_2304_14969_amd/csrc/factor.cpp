@@ -128,6 +128,8 @@ void sub_free(FactorState* f, int nq, void* p) {
   device_free(p);
 }
 
+// A one-qubit subsystem of qubit q known to be in the state amp; the caller's
+// kernel writes its amplitudes.
 int new_single(FactorState* f, int q, const double amp[4], Sub* out) {
   Sub s;
   s.nq = 1;
@@ -136,15 +138,25 @@ int new_single(FactorState* f, int q, const double amp[4], Sub* out) {
   for (int i = 0; i < 4; ++i) s.h[i] = amp[i];
   s.amps = sub_alloc(f, 1);
   if (!s.amps) return ffail(QS_E_NOMEM, "allocating a one-qubit subsystem");
-  const hipError_t e = f->dtype == QS_C64
-                           ? launch_store_single(static_cast<float*>(s.amps), amp, f->stream)
-                           : launch_store_single(static_cast<double*>(s.amps), amp, f->stream);
-  if (int rc = dev_err(e, "one-qubit subsystem")) {
-    sub_free(f, 1, s.amps);
-    return rc;
-  }
   *out = s;
   return QS_OK;
+}
+
+// Every qubit a subsystem of its own, in the basis state x, by one launch.
+int push_basis(FactorState* f, uint64_t x) {
+  void* amps[64];
+  for (int q = 0; q < f->n; ++q) {
+    const double b0[4] = {1.0, 0.0, 0.0, 0.0}, b1[4] = {0.0, 0.0, 1.0, 0.0};
+    Sub s;
+    if (int rc = new_single(f, q, ((x >> q) & 1) ? b1 : b0, &s)) return rc;
+    f->subs.push_back(s);
+    amps[q] = s.amps;
+  }
+  const hipError_t e =
+      f->dtype == QS_C64
+          ? launch_store_basis(reinterpret_cast<float**>(amps), f->n, x, f->stream)
+          : launch_store_basis(reinterpret_cast<double**>(amps), f->n, x, f->stream);
+  return dev_err(e, "one-qubit subsystems");
 }
 
 void log_attempt(FactorState* f, int q, int nsub, double eps, bool rounded, int partner,
@@ -327,16 +339,11 @@ int decide_qubit(FactorState* f, int q, int si, int t, const double st[4], doubl
   void* rest = sub_alloc(f, S.nq - 1);
   if (!rest) return ffail(QS_E_NOMEM, "allocating a %d-qubit subsystem", S.nq - 1);
   Sub single;
+  if (int rc = new_single(f, q, phi, &single)) {
+    sub_free(f, S.nq - 1, rest);
+    return rc;
+  }
   if (f->defer) {  // queued: the projection and the new subsystem in one operation
-    single.nq = 1;
-    single.q[0] = q;
-    single.known = true;
-    for (int i = 0; i < 4; ++i) single.h[i] = phi[i];
-    single.amps = sub_alloc(f, 1);
-    if (!single.amps) {
-      sub_free(f, S.nq - 1, rest);
-      return ffail(QS_E_NOMEM, "allocating a one-qubit subsystem");
-    }
     FactorState::QOp op;
     op.kind = 1;
     op.a = S.amps;
@@ -347,17 +354,14 @@ int decide_qubit(FactorState* f, int q, int si, int t, const double st[4], doubl
     for (int i = 0; i < 4; ++i) op.phi[i] = phi[i];
     op.scale = scale;
     f->qops.push_back(op);
-  } else if (int rc = new_single(f, q, phi, &single)) {
-    sub_free(f, S.nq - 1, rest);
-    return rc;
   }
   hipError_t e = hipSuccess;
   if (!f->defer)
     e = f->dtype == QS_C64
             ? launch_decompose(static_cast<float*>(rest), static_cast<const float*>(S.amps), S.nq,
-                               t, phi, scale, f->stream)
+                               t, phi, scale, static_cast<float*>(single.amps), f->stream)
             : launch_decompose(static_cast<double*>(rest), static_cast<const double*>(S.amps),
-                               S.nq, t, phi, scale, f->stream);
+                               S.nq, t, phi, scale, static_cast<double*>(single.amps), f->stream);
   if (e != hipSuccess) {
     sub_free(f, S.nq - 1, rest);
     sub_free(f, 1, single.amps);
@@ -601,14 +605,9 @@ int fact_init(FactorState* f) {
   f->gates_since.assign(f->n, 0);
   f->partner.assign(f->n, -1);
   f->merged_last.assign(f->n, 0);
-  for (int q = 0; q < f->n; ++q) {
-    const double zero[4] = {1.0, 0.0, 0.0, 0.0};
-    Sub s;
-    if (int rc = new_single(f, q, zero, &s)) {
-      fact_release(f);
-      return rc;
-    }
-    f->subs.push_back(s);
+  if (int rc = push_basis(f, 0)) {
+    fact_release(f);
+    return rc;
   }
   f->F = 1.0;
   f->dirty = 0;
@@ -648,12 +647,7 @@ void fact_drain(FactorState* f) {
 
 int fact_set_basis(FactorState* f, uint64_t x) {
   fact_release(f);
-  for (int q = 0; q < f->n; ++q) {
-    const double b0[4] = {1.0, 0.0, 0.0, 0.0}, b1[4] = {0.0, 0.0, 1.0, 0.0};
-    Sub s;
-    if (int rc = new_single(f, q, ((x >> q) & 1) ? b1 : b0, &s)) return rc;
-    f->subs.push_back(s);
-  }
+  if (int rc = push_basis(f, x)) return rc;
   f->F = 1.0;
   f->dirty = 0;
   f->deferred = 0;
@@ -1640,8 +1634,7 @@ int launch_queue_t(FactorState* f) {
     const FactorState::QOp& q = *large[i];
     if (q.kind == 1) {
       e = launch_decompose(static_cast<R*>(q.c), static_cast<const R*>(q.a), q.na, q.t0, q.phi,
-                           q.scale, f->stream);
-      if (e == hipSuccess) e = launch_store_single(static_cast<R*>(q.single), q.phi, f->stream);
+                           q.scale, static_cast<R*>(q.single), f->stream);
       continue;
     }
     e = launch_merge_gate(static_cast<R*>(q.c), static_cast<const R*>(q.a), q.na,
@@ -1963,6 +1956,18 @@ int fact_try_separate(FactorState* f, double p, int* n_separated) {
   return rc;
 }
 
+template <typename R>
+hipError_t gather_product(FactorState* f, const uint64_t* didx, uint64_t m, double* dout) {
+  GatherSubs<R> g{};
+  int used = 0;
+  for (const Sub& s : f->subs) {
+    g.amps[g.count] = static_cast<const R*>(s.amps);
+    for (int t = 0; t < s.nq; ++t) g.qubit[used++] = uint8_t(s.q[t]);
+    g.first[++g.count] = uint8_t(used);
+  }
+  return launch_gather_product(g, didx, m, dout, f->stream);
+}
+
 int fact_gather(FactorState* f, const uint64_t* idx, uint64_t m, double* out) {
   uint64_t* didx = static_cast<uint64_t*>(device_alloc(m * sizeof(uint64_t)));
   double* dout = static_cast<double*>(device_alloc(m * 2 * sizeof(double)));
@@ -1971,19 +1976,10 @@ int fact_gather(FactorState* f, const uint64_t* idx, uint64_t m, double* out) {
     device_free(dout);
     return ffail(QS_E_NOMEM, "staging allocation failed");
   }
-  std::vector<double> ones(2 * m, 0.0);
-  for (uint64_t j = 0; j < m; ++j) ones[2 * j] = 1.0;
   hipError_t e = hipMemcpyAsync(didx, idx, m * sizeof(uint64_t), hipMemcpyHostToDevice, f->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(dout, ones.data(), m * 2 * sizeof(double), hipMemcpyHostToDevice, f->stream);
-  for (size_t s = 0; s < f->subs.size() && e == hipSuccess; ++s) {
-    Perm64 bits{};
-    bits.n = f->subs[s].nq;
-    for (int t = 0; t < bits.n; ++t) bits.p[t] = int8_t(f->subs[s].q[t]);
-    e = f->dtype == QS_C64
-            ? launch_gather_mul(static_cast<const float*>(f->subs[s].amps), didx, m, bits, dout, f->stream)
-            : launch_gather_mul(static_cast<const double*>(f->subs[s].amps), didx, m, bits, dout, f->stream);
-  }
+    e = f->dtype == QS_C64 ? gather_product<float>(f, didx, m, dout)
+                           : gather_product<double>(f, didx, m, dout);
   if (e == hipSuccess)
     e = hipMemcpyAsync(out, dout, m * 2 * sizeof(double), hipMemcpyDeviceToHost, f->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(f->stream);

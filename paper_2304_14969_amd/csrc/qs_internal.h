@@ -352,13 +352,14 @@ hipError_t launch_fact_1q_batch(const Fact1qItem<R>* host_items, const Fact1qIte
                                 int nitems, const Fact1qGate<R>* host_gates,
                                 const Fact1qGate<R>* gates, int ngates, int max_nq,
                                 hipStream_t s);
-// A one-qubit subsystem: the two amplitudes amp = {Re a0, Im a0, Re a1, Im a1}.
+// One-qubit subsystems amps[0..n), n <= 64: the q-th in |bit q of x>.
 template <typename R>
-hipError_t launch_store_single(R* dst, const double amp[4], hipStream_t s);
-// phi = {Re phi0, Im phi0, Re phi1, Im phi1}
+hipError_t launch_store_basis(R* const* amps, int n, uint64_t x, hipStream_t s);
+// phi = {Re phi0, Im phi0, Re phi1, Im phi1}, also stored as the subsystem
+// `single` (two amplitudes)
 template <typename R>
 hipError_t launch_decompose(R* b, const R* a, int nq, int t, const double phi[4], double scale,
-                            hipStream_t s);
+                            R* single, hipStream_t s);
 template <typename R>
 hipError_t launch_inner(const R* a, const R* b, uint64_t count, double* scratch, hipStream_t s);
 
@@ -486,10 +487,16 @@ struct Perm64 {
 template <typename R>
 hipError_t launch_gather(const R* amps, const uint64_t* idx, uint64_t m, Perm64 perm,
                          double* out, hipStream_t s);
-// out[j] *= a[local index of idx[j]], bit t of the local index = bit bits.p[t]
-// of idx[j]
+// out[j] = product over the subsystems of amps[s][local index of idx[j]], bit
+// t of the local index = bit qubit[first[s] + t] of idx[j]
 template <typename R>
-hipError_t launch_gather_mul(const R* a, const uint64_t* idx, uint64_t m, Perm64 bits,
-                             double* out, hipStream_t s);
+struct GatherSubs {
+  const R* amps[64];
+  int count;
+  uint8_t first[65], qubit[64];
+};
+template <typename R>
+hipError_t launch_gather_product(const GatherSubs<R>& subs, const uint64_t* idx, uint64_t m,
+                                 double* out, hipStream_t s);
 
 }  // namespace qs
