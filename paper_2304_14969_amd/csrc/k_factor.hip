@@ -23,18 +23,33 @@ __device__ __forceinline__ uint64_t insert_zero(uint64_t x, int pos) {
   return lo | ((x ^ lo) << 1);
 }
 
+// Sums of N values over the workgroup, for every thread. The tree is fixed (i
+// and i + 128, then i and i + 64, ..., i and i + 1): all values go through LDS
+// once, wavefront w then owns rows w, w + 4, ... and folds them by shuffles. A
+// barrier per level for all rows cost more than the sums of a small subsystem;
+// an approximate run of 54 qubits, some 100 such sweeps in turn, 2410 -> 2230 us.
 template <int N>
 __device__ __forceinline__ void block_sum(double (&v)[N], double* sh) {
-  // sh holds N * kBlock doubles; fixed tree order
+  static_assert(kBlock == 256, "four wavefronts");
+  constexpr int kRows = (N + 3) / 4;
 #pragma unroll
   for (int k = 0; k < N; ++k) sh[k * kBlock + threadIdx.x] = v[k];
   __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double s[kRows];
 #pragma unroll
-      for (int k = 0; k < N; ++k) sh[k * kBlock + threadIdx.x] += sh[k * kBlock + threadIdx.x + w];
-    __syncthreads();
+  for (int r = 0; r < kRows; ++r) {
+    const double* row = sh + min(wave + 4 * r, N - 1) * kBlock + lane;
+    s[r] = (row[0] + row[128]) + (row[64] + row[192]);
   }
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1)
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) s[r] += __shfl_down(s[r], w);
+#pragma unroll
+  for (int r = 0; r < kRows; ++r)
+    if (lane == 0 && wave + 4 * r < N) sh[(wave + 4 * r) * kBlock] = s[r];
+  __syncthreads();
 #pragma unroll
   for (int k = 0; k < N; ++k) v[k] = sh[k * kBlock];
 }
