@@ -515,7 +515,8 @@ int qs_check(qs_state* st, double tol);
  *                    values are clamped to that); 0 (default): 12, or 11
  *                    for complex64 states above 256 MiB, 9 for those up to
  *                    22 qubits, and 9 to 11 for complex128 ones up to 25,
- *                    each when that adds no pass;
+ *                    each when that adds no pass; 13 for complex64 states up
+ *                    to 22 qubits where that saves one;
  *   "qft.stream"     global accesses of the LDS tile passes: 0 (default)
  *                    streaming (non-temporal) for states above 256 MiB, plain
  *                    below (such states partly stay in the last-level
@@ -540,7 +541,9 @@ int qs_check(qs_state* st, double tol);
  *   "qft.high_pass"  passes above that tile: 0 = strided LDS tiles, 1 =
  *                    register passes of up to 5 bits;
  *   "qft.col_max"    most bits of one strided LDS pass: 8 (default; 256-byte
- *                    rows) or 7 (512-byte rows), both 64 KiB tiles; a 7-bit
+ *                    rows; with qft.lds_bits 0 also 9 for complex64 states
+ *                    up to 22 qubits where that saves a pass) or 7 (512-byte
+ *                    rows), all 64 KiB tiles; a 7-bit
  *                    complex64 pass always has 512-byte rows unless
  *                    qft.col_rows = 1 (complex128 ones have 256-byte rows);
  *   "qft.col_rows"   1: strided passes of 7 bits use 256-byte rows (32 KiB

@@ -343,6 +343,12 @@ __global__ void __launch_bounds__(NT, sizeof(R) == 4 ? 2 : 1)
   }
 }
 
+// Rows shorter than 256 bytes leave a round's columns on few banks: padded.
+template <typename R>
+__host__ __device__ constexpr bool col_pad(int C) {
+  return C < (sizeof(R) == 4 ? 5 : 4);
+}
+
 // Strided tile: 2^G rows (global bits [lo, lo+G)) x 2^C contiguous columns
 // (global bits [0, C)), C <= lo. Tile index = row * 2^C + column.
 template <typename R, int G, int C, bool REV, int NT, int WMAX>
@@ -353,6 +359,7 @@ __global__ void __launch_bounds__(NT) k_qft_col(R* __restrict__ a, int start, in
   using V = typename Vec16<R>::T;
   constexpr int AP = Vec16<R>::AMPS;
   constexpr int TB = G + C;
+  constexpr bool PAD = col_pad<R>(C);
   constexpr int VPR = (1 << C) / AP;        // vectors per row
   constexpr int NV = (1 << TB) / AP / NT;   // vectors per thread
   static_assert(NV >= 1 && VPR >= 1, "tile shape");
@@ -383,21 +390,21 @@ __global__ void __launch_bounds__(NT) k_qft_col(R* __restrict__ a, int start, in
     const int e = threadIdx.x + k * NT;
     const int x = ((e / VPR) << C) | (e % VPR) * AP;
     if constexpr (AP == 2) {
-      sm[x] = {buf[k].x, buf[k].y};
-      sm[x + 1] = {buf[k].z, buf[k].w};
+      sm[lds_pos<PAD>(x)] = {buf[k].x, buf[k].y};
+      sm[lds_pos<PAD>(x + 1)] = {buf[k].z, buf[k].w};
     } else {
-      sm[x] = {buf[k].x, buf[k].y};
+      sm[lds_pos<PAD>(x)] = {buf[k].x, buf[k].y};
     }
   }
   __syncthreads();
-  tile_rounds<R, REV, false, NT, WMAX>(sm, TB, C, TB, lo, start, len, sign, glob);
+  tile_rounds<R, REV, PAD, NT, WMAX>(sm, TB, C, TB, lo, start, len, sign, glob);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT;
     const int x = ((e / VPR) << C) | (e % VPR) * AP;
-    const Cx<R> v0 = sm[x];
+    const Cx<R> v0 = sm[lds_pos<PAD>(x)];
     if constexpr (AP == 2) {
-      const Cx<R> v1 = sm[x + 1];
+      const Cx<R> v1 = sm[lds_pos<PAD>(x + 1)];
       buf[k] = {v0.r * scale, v0.i * scale, v1.r * scale, v1.i * scale};
     } else {
       buf[k] = {v0.r * scale, v0.i * scale};
@@ -426,6 +433,7 @@ template <typename R> constexpr int lds_bits() { return sizeof(R) == 4 ? 13 : 12
 template <typename R> constexpr int col_bits() { return sizeof(R) == 4 ? 6 : 5; }
 constexpr int kColMax = 7;   // strided pass bits with 512-byte rows
 constexpr int kColMax8 = 8;  // with 256-byte rows (knob qft.col_max)
+constexpr int kColMax9 = 9;  // with 128-byte rows (small states, see qft_plan)
 constexpr int kRegMax = 5;
 
 // Threads of a tile launch: at most `cap`, at most one per 16-byte vector of
@@ -471,7 +479,8 @@ hipError_t launch_col_cfg(R* a, int n, int start, int len, int lo, int sign, R s
   if (lo < C || n < lo + G) return hipErrorInvalidValue;
   constexpr int NT =
       tile_threads(G + C, (1 << (G + C)) / Vec16<R>::AMPS, round_width(G, WMAX), CAP);
-  const size_t bytes = (size_t(1) << (G + C)) * 2 * sizeof(R);
+  const size_t bytes =
+      ((size_t(1) << (G + C)) + (col_pad<R>(C) ? size_t(1) << (G + C - 4) : 0)) * 2 * sizeof(R);
   auto kern = k_qft_col<R, G, C, REV, NT, WMAX>;
   allow_lds(kern, bytes);
   const unsigned grid = static_cast<unsigned>(uint64_t(1) << (n - G - C));
@@ -533,11 +542,15 @@ template <typename R, int G, bool REV>
 hipError_t launch_col(R* a, int n, int start, int len, int lo, int sign, R scale,
                       const QftTuning& tune, hipStream_t s) {
   constexpr int CB = col_bits<R>();
+  if constexpr (G == 9)  // 128-byte rows
+    return launch_col_cfg<R, G, CB - 2, REV, 512, 4>(a, n, start, len, lo, sign, scale,
+                                                     stream_policy<R>(n, tune), s);
   if (tune.col_rows == 0 && tune.threads == 0 && tune.round_bits == 4) {
     const int st = stream_policy<R>(n, tune);
     const int rows = small_col_bits<R>(n, G);
-    if (rows == CB - 1)
-      return launch_col_cfg<R, G, CB - 1, REV, 256, 4>(a, n, start, len, lo, sign, scale, st, s);
+    if (rows == CB - 1)  // (8 bits: a 64 KiB tile per CU, 512 threads for its latency)
+      return launch_col_cfg<R, G, CB - 1, REV, G == 8 ? 512 : 256, 4>(a, n, start, len, lo, sign,
+                                                                      scale, st, s);
     if (rows == CB - 2)
       return launch_col_cfg<R, G, CB - 2, REV, 256, 4>(a, n, start, len, lo, sign, scale, st, s);
     if (rows == CB - 3)
@@ -560,7 +573,10 @@ hipError_t launch_lds_t(R* a, int n, int start, int len, int lo, int hi, int sig
                         const QftTuning& tune, hipStream_t s) {
   // complex128 stays at rounds of 4 bits: 32 double-precision amplitudes per
   // thread would leave one wave per SIMD
-  const int cap = tune.threads > 0 ? tune.threads : 256;
+  // a large tile or less per CU: 512 threads (a transform and its inverse on
+  // 21 qubits complex64, 66 -> 54.5 us; with two tiles per CU, 22 qubits, 91
+  // against 84)
+  const int cap = tune.threads > 0 ? tune.threads : (T >= 12 && n - T <= 8 ? 512 : 256);
   const int st = stream_policy<R>(n, tune);
   if (T < 11 || sizeof(R) == 8 || (cap < 512 && tune.round_bits < 5))
     return launch_lds_cfg<R, T, REV, 256, 4>(a, n, start, len, lo, hi, sign, scale, st, s);
@@ -607,6 +623,7 @@ hipError_t launch_pass(R* a, int n, int start, int len, const QftPass& ps, int s
         case 6: return launch_col<R, 6, REV>(a, n, start, len, ps.lo, sign, scale, tune, s);
         case 7: return launch_col<R, 7, REV>(a, n, start, len, ps.lo, sign, scale, tune, s);
         case 8: return launch_col<R, 8, REV>(a, n, start, len, ps.lo, sign, scale, tune, s);
+        case 9: return launch_col<R, 9, REV>(a, n, start, len, ps.lo, sign, scale, tune, s);
         default: return hipErrorInvalidValue;
       }
     case QftPass::REG:
@@ -645,7 +662,7 @@ template <typename R>
 int qft_plan(int n, int start, int len, bool rev, const QftTuning& tune, QftPass* out,
              int max_passes) {
   const bool use_reg = tune.high_kind == 1;
-  const int wmax = use_reg ? kRegMax : (tune.col_max == 8 ? kColMax8 : kColMax);
+  int wmax = use_reg ? kRegMax : (tune.col_max == 8 ? kColMax8 : kColMax);
   const int top = start + len;
   // passes of the plan with a contiguous tile of t bits
   auto pass_count = [&](int t) {
@@ -667,7 +684,7 @@ int qft_plan(int n, int start, int len, bool rev, const QftTuning& tune, QftPass
   // complex64 9 or 12). The 12-bit one leaves CUs idle below 20 qubits and
   // holds few waves for its LDS above. A transform and its inverse with 12
   // bits and with these: complex64 20.5 -> 17.3 us at 13 qubits, 24.2 -> 18.8 at
-  // 16, 71 -> 69 at 21 (23 qubits would be slower, 160 -> 190: two 7-bit strided
+  // 16 (23 qubits would be slower, 160 -> 190: two 7-bit strided
   // passes); complex128 25.8 -> 18.4 at 14, 44.3 -> 40.8 at 19, 101 -> 84 at 21,
   // 617 -> 568 at 24, 1307 -> 1203 at 25.
   if (tune.lds_bits == 0 && !use_reg && n <= (sizeof(R) == 4 ? 22 : 25))
@@ -676,6 +693,19 @@ int qft_plan(int n, int start, int len, bool rev, const QftTuning& tune, QftPass
         T = t;
         break;
       }
+  // complex64 states that fit the L2s (32 MiB): 13-bit tiles and strided passes
+  // of up to 9 bits where these leave a pass out: 68.7 -> 54.7 us at 21 qubits,
+  // 93-95 -> 84 at 22, bits 5 to 21 of 22 90 -> 69. Larger states lose by them
+  // (23 qubits 162 -> 200, 27 2410 -> 3610: two such tiles per CU leave the memory
+  // idle while they compute), complex128 ones gain nothing (21 qubits 82.7, 82.4).
+  if (tune.lds_bits == 0 && tune.col_max == 8 && !use_reg && sizeof(R) == 4 && n <= 22) {
+    const int now = pass_count(T);
+    wmax = kColMax9;
+    if (pass_count(13) < now)
+      T = 13;
+    else
+      wmax = kColMax8;
+  }
   if (T > n) T = n;
   int reg_lo = start > T ? start : T;
   if (!use_reg && reg_lo < col_bits<R>()) reg_lo = col_bits<R>();

@@ -440,7 +440,8 @@ struct QftTuning {
   int high_kind = 0;  // passes above the tile: 0 strided LDS tiles, 1 registers
   int threads = 0;    // thread cap of the LDS tile launches: 256, 512, or 0 = by pass width
   int round_bits = 4; // widest register round inside an LDS tile (4 or 5)
-  int col_max = 8;    // most bits of a strided LDS pass: 7 (512-byte rows) or 8 (256-byte)
+  int col_max = 8;    // most bits of a strided LDS pass: 7 (512-byte rows) or 8 (256-byte;
+                      // 9, 128-byte, on small complex64 states, see qft_plan)
   int col_rows = 0;   // 1: 7-bit strided passes with 256-byte rows (32 KiB tiles);
                       // 2: also 8-bit ones with 128-byte rows (complex64)
   int stream = 0;     // streaming (non-temporal) accesses of the LDS tile passes:
