@@ -6,13 +6,14 @@
 // default, 256-byte rows and 32 KiB tiles, 4 or 6 by knob; complex128: C = 4,
 // 256-byte rows, 32 KiB). The tile is staged
 // in LDS and transformed round by round, each round acting on 4 tile bits.
-// Three forms of rounds: two two-qubit gates on the FP32 matrix cores
-// (k_tile_pair, complex64 circuits of one- and two-qubit gates); a dense
-// 4-qubit block on the matrix cores (k_tile_mfma, complex64 circuits with
-// gates of three or four qubits), each complex product as three real ones
-// (Re U X_r, Im U X_i and (Re U + Im U)(X_r + X_i), 16 x 16 x 4 MFMAs: 3/4 of
-// the flops of the 32 x 32 real embedding); one- and two-qubit gates one by
-// one in registers (k_tile_pass, complex128).
+// Three forms of rounds: two two-qubit gates in fixed places (k_tile_pair;
+// complex64 circuits of one- and two-qubit gates on the FP32 matrix cores, all
+// complex128 circuits with FP64 FMAs); a dense 4-qubit block on the matrix
+// cores (k_tile_mfma, complex64 circuits with gates of three or four qubits),
+// each complex product as three real ones (Re U X_r, Im U X_i and (Re U + Im
+// U)(X_r + X_i), 16 x 16 x 4 MFMAs: 3/4 of the flops of the 32 x 32 real
+// embedding); one- and two-qubit gates one by one in registers (k_tile_pass:
+// runs of one-qubit gates on factorized kets, and complex64 with tile.mfma 0).
 #include "qs_internal.h"
 
 namespace qs {
