@@ -26,14 +26,45 @@ struct Block6 {
   int k;
   int q[6];       // bit of row/column bit j
   int sorted[6];  // the same bits ascending
+  int p0;         // bit 0 of the state is row/column bit p0 of the matrix (-1: none);
+                  // q then has rows p0 and 0 exchanged, so that q[0] = 0
 };
 
-template <typename R, int K, bool NT>
+// Row or column of the matrix for index x of a block with rows p0 and 0
+// exchanged.
+__host__ __device__ constexpr int unswap(int x, int p0) {
+  if (p0 <= 0) return x;
+  const int d = (x ^ (x >> p0)) & 1;
+  return x ^ (d | (d << p0));
+}
+
+// The 2^K amplitudes of a group; PAIR: bit 0 is the block's first, and
+// amplitudes c and c + 1 are loaded and stored as one 16-byte vector.
+template <typename R, int K, bool NT, bool PAIR>
+__device__ __forceinline__ void load_group(const R* __restrict__ a, const uint64_t (&off)[1 << K],
+                                           Cx<R> (&v)[1 << K]) {
+  if constexpr (PAIR) {
+#pragma unroll
+    for (int c = 0; c < (1 << K); c += 2) {
+      const float4 t = ld16<NT>(reinterpret_cast<const float4*>(a + 2 * off[c]));
+      v[c] = {t.x, t.y};
+      v[c + 1] = {t.z, t.w};
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < (1 << K); ++c) ld_amp<NT>(a + 2 * off[c], &v[c].r, &v[c].i);
+  }
+}
+
+template <typename R, int K, bool NT, bool PAIR>
 __global__ void __launch_bounds__(kBlock) k_fused_vec(R* __restrict__ a, uint64_t groups, Block6 b,
                                                       const R* __restrict__ mat) {
   constexpr int D = 1 << K;
   __shared__ Cx<R> M[D * D];
-  for (int e = threadIdx.x; e < D * D; e += kBlock) M[e] = {mat[2 * e], mat[2 * e + 1]};
+  for (int e = threadIdx.x; e < D * D; e += kBlock) {
+    const int f = PAIR ? unswap(e / D, b.p0) * D + unswap(e % D, b.p0) : e;
+    M[e] = {mat[2 * f], mat[2 * f + 1]};
+  }
   __syncthreads();
   for (uint64_t g = uint64_t(blockIdx.x) * kBlock + threadIdx.x; g < groups;
        g += uint64_t(gridDim.x) * kBlock) {
@@ -48,8 +79,9 @@ __global__ void __launch_bounds__(kBlock) k_fused_vec(R* __restrict__ a, uint64_
 #pragma unroll
       for (int j = 0; j < K; ++j) o |= uint64_t((c >> j) & 1) << b.q[j];
       off[c] = base | o;
-      ld_amp<NT>(a + 2 * off[c], &v[c].r, &v[c].i);
     }
+    load_group<R, K, NT, PAIR>(a, off, v);
+    R lr = 0, li = 0;  // the even row of a pair
 #pragma unroll
     for (int r = 0; r < D; ++r) {
       // complex128: read the matrix row by row (left to itself the compiler
@@ -62,29 +94,35 @@ __global__ void __launch_bounds__(kBlock) k_fused_vec(R* __restrict__ a, uint64_
         yr = fmadd(m.r, v[c].r, fmadd(-m.i, v[c].i, yr));
         yi = fmadd(m.r, v[c].i, fmadd(m.i, v[c].r, yi));
       }
-      st_amp<NT>(a + 2 * off[r], yr, yi);
+      if constexpr (PAIR) {
+        if (r & 1)
+          st16<NT>(reinterpret_cast<float4*>(a + 2 * off[r & ~1]), float4{lr, li, yr, yi});
+        lr = yr;
+        li = yi;
+      } else {
+        st_amp<NT>(a + 2 * off[r], yr, yi);
+      }
     }
   }
 }
 
 // Blocks of one to three qubits with the matrix passed by value: the same
-// arithmetic as k_fused_vec, the matrix read from the kernel arguments (by way
-// of LDS for three qubits). A call on 10 to 18 qubits, bound by the host:
+// arithmetic as k_fused_vec, the matrix from the kernel arguments by way of LDS
+// (read from there directly, states above the last-level cache lose: 27 qubits
+// 352 -> 362 us for one qubit, 365 -> 393 for two). A call on 10 to 18 qubits, bound by the host:
 // 9.5-10.4 us with an upload of the matrix, 6.7-7.8 us so.
 template <typename R, int K>
 struct MatArg {
   R v[2 << (2 * K)];
 };
 
-template <typename R, int K, bool NT>
+template <typename R, int K, bool NT, bool PAIR>
 __global__ void __launch_bounds__(kBlock) k_fused_arg(R* __restrict__ a, uint64_t groups, Block6 b,
                                                       MatArg<R, K> mat) {
   constexpr int D = 1 << K;
-  __shared__ Cx<R> M[K == 3 ? D * D : 1];
-  if constexpr (K == 3) {
-    if (threadIdx.x < D * D) M[threadIdx.x] = {mat.v[2 * threadIdx.x], mat.v[2 * threadIdx.x + 1]};
-    __syncthreads();
-  }
+  __shared__ Cx<R> M[D * D];
+  if (threadIdx.x < D * D) M[threadIdx.x] = {mat.v[2 * threadIdx.x], mat.v[2 * threadIdx.x + 1]};
+  __syncthreads();
   for (uint64_t g = uint64_t(blockIdx.x) * kBlock + threadIdx.x; g < groups;
        g += uint64_t(gridDim.x) * kBlock) {
     uint64_t base = g;
@@ -98,23 +136,27 @@ __global__ void __launch_bounds__(kBlock) k_fused_arg(R* __restrict__ a, uint64_
 #pragma unroll
       for (int j = 0; j < K; ++j) o |= uint64_t((c >> j) & 1) << b.q[j];
       off[c] = base | o;
-      ld_amp<NT>(a + 2 * off[c], &v[c].r, &v[c].i);
     }
+    load_group<R, K, NT, PAIR>(a, off, v);
+    R lr = 0, li = 0;  // the even row of a pair
 #pragma unroll
     for (int r = 0; r < D; ++r) {
-      if constexpr (K == 3 && sizeof(R) == 8) asm volatile("" ::: "memory");  // as above
+      if constexpr (sizeof(R) == 8) asm volatile("" ::: "memory");  // as above
       R yr = 0, yi = 0;
 #pragma unroll
       for (int c = 0; c < D; ++c) {
-        Cx<R> m;
-        if constexpr (K == 3)
-          m = M[r * D + c];
-        else
-          m = {mat.v[2 * (r * D + c)], mat.v[2 * (r * D + c) + 1]};
+        const Cx<R> m = M[r * D + c];
         yr = fmadd(m.r, v[c].r, fmadd(-m.i, v[c].i, yr));
         yi = fmadd(m.r, v[c].i, fmadd(m.i, v[c].r, yi));
       }
-      st_amp<NT>(a + 2 * off[r], yr, yi);
+      if constexpr (PAIR) {
+        if (r & 1)
+          st16<NT>(reinterpret_cast<float4*>(a + 2 * off[r & ~1]), float4{lr, li, yr, yi});
+        lr = yr;
+        li = yi;
+      } else {
+        st_amp<NT>(a + 2 * off[r], yr, yi);
+      }
     }
   }
 }
@@ -179,44 +221,59 @@ unsigned fused_grid(uint64_t groups) {
   return static_cast<unsigned>(want < cap ? (want > 0 ? want : 1) : cap);
 }
 
-Block6 make_block(const int* qubits, int k) {
+// pair (complex64): where amplitudes are swept in pairs, rows are exchanged so
+// that bit 0 comes first. That is blocks of one or three qubits with bit 0, and
+// of two on bits 0 and 1: 24 qubits k = 2 52-55 -> 38 us, k = 3 on bits 0-2 92 ->
+// 55, 27 qubits 431 -> 377 and 716 -> 449; k = 2 with bit 0 and a higher one
+// loses above the last-level cache (27 qubits 362 -> 390 us).
+Block6 make_block(const int* qubits, int k, bool pair) {
   Block6 b{};
   b.k = k;
-  for (int j = 0; j < k; ++j) b.q[j] = b.sorted[j] = qubits[j];
+  b.p0 = -1;
+  for (int j = 0; j < k; ++j) {
+    b.q[j] = b.sorted[j] = qubits[j];
+    if (qubits[j] == 0) b.p0 = j;
+  }
   for (int i = 1; i < k; ++i)
     for (int j = i; j > 0 && b.sorted[j - 1] > b.sorted[j]; --j) {
       const int t = b.sorted[j];
       b.sorted[j] = b.sorted[j - 1];
       b.sorted[j - 1] = t;
     }
+  if (!pair || k > 3 || (k == 2 && b.sorted[1] != 1)) b.p0 = -1;
+  if (b.p0 > 0) {
+    b.q[b.p0] = b.q[0];
+    b.q[0] = 0;
+  }
   return b;
 }
 
 template <typename R, int K>
 hipError_t launch_arg(R* a, int n, const Block6& b, const double* m, hipStream_t s) {
   MatArg<R, K> mat;
-  for (int i = 0; i < (2 << (2 * K)); ++i) mat.v[i] = static_cast<R>(m[i]);
+  constexpr int D = 1 << K;
+  for (int e = 0; e < D * D; ++e) {
+    const int f = unswap(e / D, b.p0) * D + unswap(e % D, b.p0);
+    mat.v[2 * e] = static_cast<R>(m[2 * f]);
+    mat.v[2 * e + 1] = static_cast<R>(m[2 * f + 1]);
+  }
   const uint64_t groups = uint64_t(1) << (n - K);
-  if (stream_sweep(n, 2 * sizeof(R), b.sorted[0]))
-    hipLaunchKernelGGL((k_fused_arg<R, K, true>), dim3(fused_grid(groups)), dim3(kBlock), 0, s, a,
-                       groups, b, mat);
-  else
-    hipLaunchKernelGGL((k_fused_arg<R, K, false>), dim3(fused_grid(groups)), dim3(kBlock), 0, s, a,
-                       groups, b, mat);
+  const bool nt = stream_sweep(n, 2 * sizeof(R), b.sorted[0]);
+  auto kern = nt ? k_fused_arg<R, K, true, false> : k_fused_arg<R, K, false, false>;
+  if constexpr (sizeof(R) == 4)
+    if (b.p0 >= 0) kern = nt ? k_fused_arg<R, K, true, true> : k_fused_arg<R, K, false, true>;
+  hipLaunchKernelGGL(kern, dim3(fused_grid(groups)), dim3(kBlock), 0, s, a, groups, b, mat);
   return hipGetLastError();
 }
 
 template <typename R, int K>
 hipError_t launch_k(R* a, int n, const Block6& b, const R* mat, hipStream_t s) {
   const uint64_t groups = uint64_t(1) << (n - K);
-  const uint64_t want = (groups + kBlock - 1) / kBlock, cap = uint64_t(1) << 20;
-  const unsigned grid = static_cast<unsigned>(want < cap ? want : cap);
-  if (stream_sweep(n, 2 * sizeof(R), b.sorted[0]))
-    hipLaunchKernelGGL((k_fused_vec<R, K, true>), dim3(grid), dim3(kBlock), 0, s, a, groups, b,
-                       mat);
-  else
-    hipLaunchKernelGGL((k_fused_vec<R, K, false>), dim3(grid), dim3(kBlock), 0, s, a, groups, b,
-                       mat);
+  const bool nt = stream_sweep(n, 2 * sizeof(R), b.sorted[0]);
+  auto kern = nt ? k_fused_vec<R, K, true, false> : k_fused_vec<R, K, false, false>;
+  if constexpr (sizeof(R) == 4 && K <= 3)
+    if (b.p0 >= 0) kern = nt ? k_fused_vec<R, K, true, true> : k_fused_vec<R, K, false, true>;
+  hipLaunchKernelGGL(kern, dim3(fused_grid(groups)), dim3(kBlock), 0, s, a, groups, b, mat);
   return hipGetLastError();
 }
 
@@ -225,7 +282,7 @@ hipError_t launch_k(R* a, int n, const Block6& b, const R* mat, hipStream_t s) {
 template <typename R>
 hipError_t launch_apply_small(R* a, int n, const int* qubits, int k, const double* host_mat,
                               hipStream_t s) {
-  const Block6 b = make_block(qubits, k);
+  const Block6 b = make_block(qubits, k, sizeof(R) == 4);
   switch (k) {
     case 1: return launch_arg<R, 1>(a, n, b, host_mat, s);
     case 2: return launch_arg<R, 2>(a, n, b, host_mat, s);
@@ -237,7 +294,7 @@ hipError_t launch_apply_small(R* a, int n, const int* qubits, int k, const doubl
 template <typename R>
 hipError_t launch_apply_fused(R* a, int n, const int* qubits, int k, const R* mat,
                               hipStream_t s) {
-  const Block6 b = make_block(qubits, k);
+  const Block6 b = make_block(qubits, k, sizeof(R) == 4);
   if (k >= 4 && n <= 11) switch (k) {
       case 4: return launch_small_state<R, 4>(a, n, b, mat, s);
       case 5: return launch_small_state<R, 5>(a, n, b, mat, s);

@@ -61,3 +61,27 @@ def test_blocks_on_small_states(qs_lib, n, k, dtype):
             st.set_amplitudes(a)
             st.apply_fused(bits, m)
             assert_parity(st.amplitudes(), dense.apply_matrix(a, n, bits, m), dtype, f"{bits}")
+
+
+@pytest.mark.parametrize("k", [1, 2, 3])
+@pytest.mark.parametrize("n", [3, 9, 14])
+def test_blocks_on_bit_zero(qs_lib, n, k):
+    """complex64 blocks that hold bit 0, at every row of the matrix: the sweeps
+    of pairs, applied by themselves and as the blocks of a circuit."""
+    a = workloads.gaussian_state(n, n)
+    rng = np.random.default_rng(n * k)
+    for row in range(k):
+        bits = [1 + int(x) for x in rng.choice(n - 1, size=k - 1, replace=False)]
+        bits.insert(row, 0)
+        m = haar(2 ** k, 7 * row + k)
+        want = dense.apply_matrix(a, n, bits, m)
+        with qs_lib.State(n, C64) as st:
+            st.set_amplitudes(a)
+            st.apply_fused(bits, m)
+            assert_parity(st.amplitudes(), want, C64, f"{bits}")
+            st.set_amplitudes(a)
+            c = qs_lib.Circuit(n).add_gates([("mat", tuple(bits), m)])
+            c.plan(3)
+            st.run(c)
+            assert_parity(st.amplitudes(), want, C64, f"circuit {bits}")
+            c.free()
