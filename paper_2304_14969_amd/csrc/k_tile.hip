@@ -321,16 +321,20 @@ struct PairRounds {
     }
     __syncthreads();
   }
-  __device__ __forceinline__ void run(float* re, float* im) {
+  template <typename Step>
+  __device__ __forceinline__ void run(Step step) {
     for (int r = 0; r < nrounds; r += 2) {  // two by two: the rows need no copies
       const Round rb = load_round(next);
       next = entry(r + 2);
-      step(ra, re, im);
+      step(ra);
       if (r + 1 == nrounds) break;
       ra = load_round(next);
       next = entry(r + 3);
-      step(rb, re, im);
+      step(rb);
     }
+  }
+  __device__ __forceinline__ void run(float* re, float* im) {
+    run([this, re, im](const Round& rd) { step(rd, re, im); });
   }
 };
 
@@ -500,17 +504,55 @@ __attribute__((amdgpu_waves_per_eu(kPairWaves<R>)))
 }
 
 // ---- states that fit one tile with room to spare
-// A state of n <= TB qubits whole in the LDS of one workgroup, every round of
+// A state of n <= TB qubits whole in the LDS of one workgroup, every gate of
 // the circuit in one launch; indices from 2^n on are zeros that no gate moves.
-// Fused blocks, one launch each, are the alternative: a pair round takes about
-// 0.85 us here, a launch about 4 (8 layers at 11 qubits: 23 against 112 us in
-// 14 blocks; at 6 qubits 14 against 48; complex128 at 10 and 6 qubits 47
-// against 81 and 25 against 44).
+// Fused blocks, one launch each, are the alternative (8 layers at 11 qubits 112
+// us in 14 blocks). One workgroup leaves nothing to hide latency with, so a
+// thread owns the four amplitudes of one gate's group and not the 16 of a
+// round's: four times the wavefronts, each with a quarter of the chain, for one
+// more barrier per round. The products and their order are those of the pair
+// rounds. 8 layers with 16 amplitudes per thread and with four: complex64 at 6,
+// 8, 10 and 11 qubits 13.8, 16.8, 23.8, 23.3 -> 10.9, 13.0, 17.9, 19.7 us,
+// complex128 at 6, 8 and 10 21.5, 26.9, 38.2 -> 15.1, 19.8, 27.0.
+struct QuadPos {  // LDS offsets of thread x's group of a gate on tile bits b0, b1
+  int px, d0, d1;
+  template <typename Pos>
+  __device__ __forceinline__ QuadPos(int b0, int b1, Pos pos) {
+    const int x0 = insert_zero32(insert_zero32(threadIdx.x, min(b0, b1)), max(b0, b1));
+    px = pos(x0);
+    d0 = pos(1 << b0);
+    d1 = pos(1 << b1);
+  }
+  __device__ __forceinline__ int operator()(int m) const {
+    return px + ((m & 1) ? d0 : 0) + ((m & 2) ? d1 : 0);
+  }
+};
+
+__device__ __forceinline__ void quad_gate(const float4 (&u)[2], int b0, int b1, float* re,
+                                          float* im) {
+  const QuadPos at(b0, b1, [](int x) { return plane_pos(x); });
+  const float ur[4] = {u[0].x, u[0].z, u[1].x, u[1].z}, ui[4] = {u[0].y, u[0].w, u[1].y, u[1].w};
+  float2 v[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v[c] = make_float2(re[at(c)], im[at(c)]);
+  f32x4 yr{}, yi{};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    yr = __builtin_amdgcn_mfma_f32_4x4x1f32(ur[c], v[c].x, yr, 0, 0, 0);
+    yi = __builtin_amdgcn_mfma_f32_4x4x1f32(ur[c], v[c].y, yi, 0, 0, 0);
+    yr = __builtin_amdgcn_mfma_f32_4x4x1f32(-ui[c], v[c].y, yr, 0, 0, 0);
+    yi = __builtin_amdgcn_mfma_f32_4x4x1f32(ui[c], v[c].x, yi, 0, 0, 0);
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) re[at(c)] = yr[c], im[at(c)] = yi[c];
+  __syncthreads();
+}
+
 template <int TB>
-__global__ void __launch_bounds__(1 << (TB - kW)) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(1 << (TB - 2))
     k_whole_pair(float* __restrict__ a, int n, const int4* __restrict__ rounds, int nrounds,
                  const float* __restrict__ mats) {
-  constexpr int NT = 1 << (TB - kW), NV = (1 << TB) / 2 / NT;
+  constexpr int NT = 1 << (TB - 2), NV = (1 << TB) / 2 / NT;
   extern __shared__ unsigned char smraw[];
   float* re = reinterpret_cast<float*>(smraw);
   float* im = re + kPlane<TB>;
@@ -527,7 +569,10 @@ __global__ void __launch_bounds__(1 << (TB - kW)) __attribute__((amdgpu_waves_pe
     im[l + 1] = b.w;
   }
   __syncthreads();
-  rr.run(re, im);
+  rr.run([re, im](const PairRounds::Round& rd) {
+    quad_gate(rd.m1, rd.bits & 255, (rd.bits >> 8) & 255, re, im);
+    if (rd.flags & 1) quad_gate(rd.m2, (rd.bits >> 16) & 255, (rd.bits >> 24) & 255, re, im);
+  });
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT, l = plane_pos(2 * e);
@@ -535,11 +580,28 @@ __global__ void __launch_bounds__(1 << (TB - kW)) __attribute__((amdgpu_waves_pe
   }
 }
 
+__device__ __forceinline__ void quad_gate_f64(Cx<double>* sm, int b0, int b1,
+                                              const double* __restrict__ u) {
+  const QuadPos at(b0, b1, [](int x) { return wide_pos(x); });
+  Cx<double> in[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) in[c] = sm[at(c)];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    Cx<double> y{0, 0};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      y = cmac(y, Cx<double>{u[2 * (4 * r + c)], u[2 * (4 * r + c) + 1]}, in[c]);
+    sm[at(r)] = y;
+  }
+  __syncthreads();
+}
+
 template <int TB>
-__global__ void __launch_bounds__(1 << (TB - kW))
+__global__ void __launch_bounds__(1 << (TB - 2))
     k_whole_pair(double* __restrict__ a, int n, const int4* __restrict__ rounds, int nrounds,
                  const double* __restrict__ num) {
-  constexpr int NT = 1 << (TB - kW), NV = (1 << TB) / NT;
+  constexpr int NT = 1 << (TB - 2), NV = (1 << TB) / NT;
   extern __shared__ unsigned char smraw[];
   Cx<double>* sm = reinterpret_cast<Cx<double>*>(smraw);
   double2* p2 = reinterpret_cast<double2*>(a);
@@ -551,7 +613,14 @@ __global__ void __launch_bounds__(1 << (TB - kW))
     sm[wide_pos(e)] = {b.x, b.y};
   }
   __syncthreads();
-  pair_rounds_f64(sm, rounds, nrounds, num);
+  int4 e = rounds[0];
+  for (int r = 0; r < nrounds; ++r) {
+    const int4 next = rounds[r + 1 < nrounds ? r + 1 : r];
+    const double* __restrict__ u = num + e.z;
+    quad_gate_f64(sm, e.x & 255, (e.x >> 8) & 255, u);
+    if (e.w & 1) quad_gate_f64(sm, (e.x >> 16) & 255, (e.x >> 24) & 255, u + 32);
+    e = next;
+  }
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT;
@@ -823,7 +892,7 @@ template <typename R, int TB>
 hipError_t launch_whole_tb(R* a, int n, const void* rounds, int nrounds, const R* num,
                            hipStream_t s) {
   void (*kern)(R*, int, const int4*, int, const R*) = k_whole_pair<TB>;
-  hipLaunchKernelGGL(kern, dim3(1), dim3(1 << (TB - kW)), (pair_lds<R, TB>()), s, a, n,
+  hipLaunchKernelGGL(kern, dim3(1), dim3(1 << (TB - 2)), (pair_lds<R, TB>()), s, a, n,
                      static_cast<const int4*>(rounds), nrounds, num);
   return hipGetLastError();
 }
