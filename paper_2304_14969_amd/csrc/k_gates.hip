@@ -6,6 +6,7 @@
 // partner at distance 2^t sits in the same thread, so each byte is read and
 // written once per gate. Grids are capped and threads stride through the
 // work, so a launch never exceeds the 2^32 threads of one grid dimension.
+#include "bit_pairs.h"
 #include "qs_internal.h"
 
 namespace qs {
@@ -254,33 +255,13 @@ __global__ void __launch_bounds__(kBlock) k_bitswap_scalar(R* __restrict__ a, ui
 // at 24 qubits 0.14 against 0.61 ms. Tiles of 2^9 or 2^10 amplitudes are even,
 // 2^11 took half as long again. A single pair keeps its own sweep
 // (k_bitswap), which touches only the half that moves.
-constexpr int kSwapTileMax = 11;
-struct BitPairs {
-  int n, low, tile;       // pairs; contiguous tile bits; tile bits (ascending)
-  int a[32], b[32];       // the pairs outside the tile
-  int bit[kSwapTileMax];  // the tile's bits
-  int to[kSwapTileMax];   // tile bit -> its image among the tile's bits
-  int moves;              // whether the exchange moves anything inside a tile
-};
-
 template <typename R, bool NT>
-__global__ void __launch_bounds__(kBlock) k_bit_pairs(R* __restrict__ a, BitPairs g) {
+__global__ void __launch_bounds__(kBlock) k_bit_pairs(R* __restrict__ a, uint64_t tiles, BitPairs g) {
   using V = typename Vec16<R>::T;
   constexpr int AP = Vec16<R>::AMPS;
   extern __shared__ unsigned char swap_lds[];
   V* sm = reinterpret_cast<V*>(swap_lds);
-  uint64_t base = blockIdx.x;
-  for (int j = 0; j < g.tile; ++j) base = insert_zero(base, g.bit[j]);
-  uint64_t image = base;
-  for (int j = 0; j < g.n; ++j) {
-    const uint64_t d = ((image >> g.a[j]) ^ (image >> g.b[j])) & 1;
-    image ^= (d << g.a[j]) | (d << g.b[j]);
-  }
-  const bool one = image == base;
-  if (image < base || (one && !g.moves)) return;
   const int vecs = (1 << g.tile) / AP, rowbits = g.low - (AP - 1);  // log2 vectors per row
-  V* from = reinterpret_cast<V*>(a + 2 * base);
-  V* to = reinterpret_cast<V*>(a + 2 * image);
   const int second = vecs + (vecs >> 4) + 1;  // LDS place of the image
   auto spread = [&](int e) {  // offset of a tile's vector e
     uint64_t x = uint64_t(e & ((1 << rowbits) - 1)) * AP;
@@ -288,33 +269,47 @@ __global__ void __launch_bounds__(kBlock) k_bit_pairs(R* __restrict__ a, BitPair
     for (int j = g.low; j < g.tile; ++j) x |= uint64_t((row >> (j - g.low)) & 1) << g.bit[j];
     return x / AP;
   };
-  for (int e = threadIdx.x; e < vecs; e += kBlock) {
-    const uint64_t x = spread(e);
-    const V v = ld16<NT>(from + x);
-    if (!one) sm[second + e + (e >> 4)] = ld16<NT>(to + x);
-    sm[e + (e >> 4)] = v;
-  }
-  __syncthreads();
   const int next = 1 << g.to[0];  // where the tile's odd entries come from
   auto amp = [&](int at, int t) {  // amplitude t of the tile staged at `at`
     const int e = t / AP;
     return reinterpret_cast<const R*>(sm + at + e + (e >> 4)) + 2 * (t % AP);
   };
-  for (int e = threadIdx.x; e < vecs; e += kBlock) {
-    const uint64_t x = spread(e);
-    int src = 0;
-    for (int j = AP - 1; j < g.tile; ++j) src |= ((e >> (j - (AP - 1))) & 1) << g.to[j];
-    auto moved = [&](int at) {
-      const R* p = amp(at, src);
-      if constexpr (AP == 2) {
-        const R* q = amp(at, src | next);
-        return V{p[0], p[1], q[0], q[1]};
-      } else {
-        return V{p[0], p[1]};
-      }
-    };
-    st16<NT>(to + x, moved(0));
-    if (!one) st16<NT>(from + x, moved(second));
+  for (uint64_t w = blockIdx.x; w < tiles; w += gridDim.x) {
+    uint64_t base = w;
+    for (int j = 0; j < g.tile; ++j) base = insert_zero(base, g.bit[j]);
+    uint64_t image = base;
+    for (int j = 0; j < g.n; ++j) {
+      const uint64_t d = ((image >> g.a[j]) ^ (image >> g.b[j])) & 1;
+      image ^= (d << g.a[j]) | (d << g.b[j]);
+    }
+    const bool one = image == base;
+    if (image < base || (one && !g.moves)) continue;
+    V* from = reinterpret_cast<V*>(a + 2 * base);
+    V* to = reinterpret_cast<V*>(a + 2 * image);
+    for (int e = threadIdx.x; e < vecs; e += kBlock) {
+      const uint64_t x = spread(e);
+      const V v = ld16<NT>(from + x);
+      if (!one) sm[second + e + (e >> 4)] = ld16<NT>(to + x);
+      sm[e + (e >> 4)] = v;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < vecs; e += kBlock) {
+      const uint64_t x = spread(e);
+      int src = 0;
+      for (int j = AP - 1; j < g.tile; ++j) src |= ((e >> (j - (AP - 1))) & 1) << g.to[j];
+      auto moved = [&](int at) {
+        const R* p = amp(at, src);
+        if constexpr (AP == 2) {
+          const R* q = amp(at, src | next);
+          return V{p[0], p[1], q[0], q[1]};
+        } else {
+          return V{p[0], p[1]};
+        }
+      };
+      st16<NT>(to + x, moved(0));
+      if (!one) st16<NT>(from + x, moved(second));
+    }
+    __syncthreads();  // the next tile takes this one's place
   }
 }
 
@@ -508,41 +503,15 @@ hipError_t launch_bitswap(R* a, int n, int qa, int qb, hipStream_t s) {
 
 template <typename R>
 hipError_t launch_bit_pairs(R* a, int n, const int* image, hipStream_t s) {
-  // tile bits: the lowest bits with their images, as many as fit
-  constexpr int kWant = 10;
-  BitPairs g{};
-  uint64_t tile = 0;
-  for (int q = 0; q < n; ++q) {
-    const uint64_t with = tile | (uint64_t(1) << q) | (uint64_t(1) << image[q]);
-    if (__builtin_popcountll(with) > kSwapTileMax) break;
-    tile = with;
-    g.low = q + 1;
-    if (__builtin_popcountll(tile) >= kWant) break;
-  }
-  while (g.low < n && ((tile >> g.low) & 1)) ++g.low;
-  int rank[64];
-  for (int q = 0; q < n; ++q)
-    if ((tile >> q) & 1) {
-      rank[q] = g.tile;
-      g.bit[g.tile++] = q;
-    }
+  const BitPairs g = plan_bit_pairs(n, image);
   if (g.low < log_amps<R>()) return hipErrorInvalidValue;
-  for (int j = 0; j < g.tile; ++j) {
-    g.to[j] = rank[image[g.bit[j]]];
-    g.moves |= g.to[j] != j;
-  }
-  for (int q = 0; q < n; ++q)
-    if (!((tile >> q) & 1) && image[q] > q) {
-      g.a[g.n] = q;
-      g.b[g.n++] = image[q];
-    }
   const int vecs = (1 << g.tile) / Vec16<R>::AMPS;
   const size_t bytes = size_t(2 * (vecs + (vecs >> 4) + 1)) * 16;
   auto kern = stream_sweep(n, 2 * sizeof(R), g.low) ? k_bit_pairs<R, true> : k_bit_pairs<R, false>;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
-  hipLaunchKernelGGL(kern, dim3(unsigned(uint64_t(1) << (n - g.tile))), dim3(kBlock), bytes, s, a,
-                     g);
+  hipLaunchKernelGGL(kern, dim3(bit_pairs_grid(n, g)), dim3(kBlock), bytes, s, a,
+                     uint64_t(1) << (n - g.tile), g);
   return hipGetLastError();
 }
 
