@@ -7,6 +7,7 @@
 // work tables and block matrices of a run are uploaded once; the launches can
 // be captured into a HIP graph and replayed.
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -106,20 +107,50 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
   const bool c64 = b->dtype == QS_C64;
   constexpr int H = qs::kTileRowBits;
   const int C = qs::batch_tile_low(b->dtype);
+  auto plan = [&](qs_circuit* c, int bits, qs::TileForms forms) {
+    const qs::TilePlan& have = c->bplan;
+    if (c->bplan_ok && have.C == C) {
+      bool fits = have.forms == forms;
+      if (have.forms == qs::TileForms::kPairsDense && !fits) {  // all its passes may be of the form
+        const qs::TileMode want =
+            forms == qs::TileForms::kPairs ? qs::TileMode::kPairs : qs::TileMode::kDense;
+        fits = true;
+        for (const auto& st : have.steps) fits = fits && !st.block && st.mode == want;
+      }
+      if (fits) return;
+    }
+    c->bplan = qs::plan_tiles(c->gates, bits, C, H, 4, forms);
+    c->bplan_ok = true;
+  };
+  // One form of rounds for every ket that could take pairs or dense ones, by
+  // their sums: kets with passes of both forms run as two launches a pass, one
+  // after the other (64 circuits of 12 to 16 qubits, 2 layers: 35 us in pairs,
+  // 40 with a form per ket).
+  double pair_cost = 0, dense_cost = 0;
+  for (int i = 0; c64 && i < b->count; ++i) {
+    qs_circuit* c = circs[i];
+    if (b->n[i] < C + H || c->gates.empty() || !qs::narrow_gates(c->gates)) continue;
+    if (!c->bcost_ok) {
+      plan(c, b->n[i], qs::TileForms::kPairsDense);
+      c->bcost[0] = c->bplan.pair_cost;
+      c->bcost[1] = c->bplan.group_cost;
+      c->bcost_ok = true;
+    }
+    pair_cost += std::ldexp(c->bcost[0], b->n[i]);
+    dense_cost += std::ldexp(c->bcost[1], b->n[i]);
+  }
+  const qs::TileForms full =
+      c64 && dense_cost < pair_cost ? qs::TileForms::kDense : qs::TileForms::kPairs;
   std::vector<const qs::TilePlan*> plans(b->count, nullptr);
   size_t maxp = 0;
   for (int i = 0; i < b->count; ++i) {
     qs_circuit* c = circs[i];
     if (c->gates.empty()) continue;
-    const qs::TileMode pairs = qs::TileMode::kPairs;
-    const qs::TileMode mode = c64 ? qs::matrix_tile_mode(c->gates) : pairs;
     // a ket smaller than a tile is planned on the tile's bits (one pass)
     const int bits = std::max(b->n[i], C + H);
-    if (bits > b->n[i] && mode != pairs) continue;
-    if (!c->bplan_ok || c->bplan.C != C || c->bplan.mode != mode) {
-      c->bplan = qs::plan_tiles(c->gates, bits, C, H, 4, mode);
-      c->bplan_ok = true;
-    }
+    const bool small = bits > b->n[i], narrow = qs::narrow_gates(c->gates);
+    if (small && !narrow) continue;
+    plan(c, bits, small ? qs::TileForms::kPairs : c64 && !narrow ? qs::TileForms::kDense : full);
     plans[i] = &c->bplan;
     bool ok = true;
     for (const auto& st : plans[i]->steps) ok = ok && !st.block;
@@ -141,7 +172,7 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
     const size_t m0 = mats.size();
     mats.insert(mats.end(), pl.reals.begin(), pl.reals.end());
     for (const auto& r : pl.rounds) {
-      if (pl.mode == qs::TileMode::kPairs) {
+      if (r.mode == qs::TileMode::kPairs) {
         int32_t row[4];
         qs::pair_round_entry(r, m0, row);
         rtab.insert(rtab.end(), row, row + 4);
@@ -162,8 +193,9 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
     for (const qs::TileMode mode : {qs::TileMode::kPairs, qs::TileMode::kDense}) {
       Launch L{items.size(), 0, 0, 0, true, mode};
       for (int i = 0; i < b->count; ++i) {
-        if (!(*use_tile)[i] || plans[i]->mode != mode || p >= plans[i]->steps.size()) continue;
+        if (!(*use_tile)[i] || p >= plans[i]->steps.size()) continue;
         const qs::TileStep& st = plans[i]->steps[p];
+        if (st.mode != mode) continue;
         qs::TileItem it{};
         it.amp_off = b->off[i];
         it.first_tile = L.tiles;

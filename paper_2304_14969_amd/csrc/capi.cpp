@@ -350,7 +350,7 @@ void circuit_invalidate(qs_circuit* c) {
   c->planned = false;
   c->due = false;
   c->blocks.clear();
-  c->bplan_ok = false;
+  c->bplan_ok = c->bcost_ok = false;
   c->bplan = qs::TilePlan();
   c->generation = next_generation();
 }
@@ -982,7 +982,7 @@ bool runs_whole(const qs_state* st, const qs_circuit* c) {
       st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits)
     return false;
   if (st->dtype == QS_C64 && !g_tile_mfma) return false;
-  return qs::matrix_tile_mode(c->gates) == qs::TileMode::kPairs;
+  return qs::narrow_gates(c->gates);
 }
 
 // The tile plan of circuit c for the state's precision and current labelling
@@ -994,11 +994,11 @@ int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   const int bits = whole ? qs::whole_bits(st->n) : st->n;
   const int low = whole ? bits - qs::kTileRowBits : qs::tile_low_bits(st->dtype);
   std::vector<int> key(st->perm, st->perm + st->n);
-  const qs::TileMode mode = st->dtype == QS_C128 ? qs::TileMode::kPairs
-                            : g_tile_mfma        ? qs::matrix_tile_mode(c->gates)
-                                                 : qs::TileMode::kSparse;
-  if (tc.dev && tc.key == key && tc.plan.mode == mode &&
-      tc.plan.C == low) {
+  const qs::TileForms forms = whole                  ? qs::TileForms::kPairs
+                              : st->dtype == QS_C128 ? qs::TileForms::kPairsSparse
+                              : g_tile_mfma          ? qs::TileForms::kPairsDense
+                                                     : qs::TileForms::kSparse;
+  if (tc.dev && tc.key == key && tc.plan.forms == forms && tc.plan.C == low) {
     *out = &tc;
     return QS_OK;
   }
@@ -1010,10 +1010,10 @@ int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   std::vector<qs::Gate> phys = c->gates;
   for (auto& g : phys)
     for (int j = 0; j < g.k; ++j) g.q[j] = st->perm[g.q[j]];
-  tc.plan = qs::plan_tiles(phys, bits, low, qs::kTileRowBits, 4, mode);
+  tc.plan = qs::plan_tiles(phys, bits, low, qs::kTileRowBits, 4, forms);
   std::vector<unsigned char> host;
-  size_t gates_at = 0, mats_at = 0, emb_at = 0;
-  qs::tile_tables(tc.plan, prec == 0, &host, &gates_at, &mats_at, &emb_at);
+  qs::TileOffsets at;
+  qs::tile_tables(tc.plan, prec == 0, &host, &at);
   const size_t total = host.size();
   void* d = dev_alloc(std::max<size_t>(total, 256));
   if (!d) return fail(QS_E_NOMEM, "allocating %zu bytes of tile tables", total);
@@ -1024,9 +1024,7 @@ int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   }
   tc.dev = d;
   tc.key = key;
-  tc.gates_off = gates_at;
-  tc.mats_off = mats_at;  // block-step matrices (and sparse-round matrices)
-  tc.emb_off = emb_at;
+  tc.at = at;
   *out = &tc;
   return QS_OK;
 }
@@ -1038,7 +1036,7 @@ int run_tiles(qs_state* st, qs_circuit* c) {
   const double bytes = 2.0 * std::ldexp(1.0, st->n) * ab(st);
   if (runs_whole(st, c)) {  // one step with every round
     ProfScope ps(st, "circuit_lds", bytes);
-    const void* num = base + tc->gates_off;
+    const void* num = base + tc->at.reals;
     const int nr = int(tc->plan.rounds.size());
     const hipError_t e =
         st->dtype == QS_C64 ? qs::launch_whole(static_cast<float*>(st->amps), st->n, base, nr,
@@ -1050,30 +1048,31 @@ int run_tiles(qs_state* st, qs_circuit* c) {
   for (const auto& stp : tc->plan.steps) {
     hipError_t e;
     if (stp.block) {
-      const void* dm = base + tc->mats_off + 2 * stp.mat * (st->dtype == QS_C64 ? 4 : 8);
+      const void* dm = base + tc->at.mats + 2 * stp.mat * (st->dtype == QS_C64 ? 4 : 8);
       e = launch_block(st, stp.blk.q, stp.blk.k, dm);
     } else {
       qs::TileRows rows;
       for (int j = 0; j < qs::kTileRowBits; ++j) rows.b[j] = stp.hb[j];
       const void* rd = base + size_t(stp.r0) * 4 * sizeof(int32_t);
-      const void* gt = base + tc->gates_off;
-      if (tc->plan.mode == qs::TileMode::kPairs) {
-        ProfScope ps(st, st->dtype == QS_C64 ? "tile_mfma" : "tile_pass", bytes);
-        e = st->dtype == QS_C64
-                ? qs::launch_tile_pair(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd,
-                                       stp.nr, static_cast<const float*>(gt), st->stream)
+      const bool c64 = st->dtype == QS_C64;
+      ProfScope ps(st, c64 && stp.mode != qs::TileMode::kSparse ? "tile_mfma" : "tile_pass", bytes);
+      if (stp.mode == qs::TileMode::kPairs) {
+        const void* num = base + tc->at.reals;
+        e = c64 ? qs::launch_tile_pair(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd,
+                                       stp.nr, static_cast<const float*>(num), st->stream)
                 : qs::launch_tile_pair(static_cast<double*>(st->amps), st->n, tc->plan.C, rows, rd,
-                                       stp.nr, static_cast<const double*>(gt), st->stream);
-      } else if (tc->plan.mode == qs::TileMode::kDense) {
-        ProfScope ps(st, "tile_mfma", bytes);
+                                       stp.nr, static_cast<const double*>(num), st->stream);
+      } else if (stp.mode == qs::TileMode::kDense) {
         e = qs::launch_tile_mfma(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd,
-                                 stp.nr, reinterpret_cast<const float*>(base + tc->emb_off),
+                                 stp.nr, reinterpret_cast<const float*>(base + tc->at.ops),
                                  st->stream);
       } else {
-        ProfScope ps(st, "tile_pass", bytes);
-        e = qs::launch_tile_pass(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd, stp.nr,
-                                 gt, reinterpret_cast<const float*>(base + tc->mats_off),
-                                 st->stream);
+        const void* gt = base + tc->at.gates;
+        const void* mt = base + tc->at.mats;
+        e = c64 ? qs::launch_tile_pass(static_cast<float*>(st->amps), st->n, tc->plan.C, rows, rd,
+                                       stp.nr, gt, static_cast<const float*>(mt), st->stream)
+                : qs::launch_tile_pass(static_cast<double*>(st->amps), st->n, tc->plan.C, rows, rd,
+                                       stp.nr, gt, static_cast<const double*>(mt), st->stream);
       }
     }
     if (int rc = device_error(st, e, "tile pass")) return rc;

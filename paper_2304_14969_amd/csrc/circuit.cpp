@@ -93,27 +93,37 @@ bool gate_matrix(int kind, int nq, const double* p, std::vector<cd>* m, int* k_o
 namespace {
 
 // m <- g m, where g acts on the block-local bits lp[0..gk) of a k-bit block.
+// (Rows as planes of real and imaginary parts, so that the columns' sums run in
+// vectors; std::complex's products would look for infinities and NaN each time.)
 void left_apply(std::vector<cd>& m, int k, const std::vector<cd>& g, int gk, const int* lp) {
+  constexpr int D = 1 << QS_MAX_FUSED;
   const int d = 1 << k, gd = 1 << gk;
-  int mask = 0;
+  int mask = 0, off[D];
   for (int j = 0; j < gk; ++j) mask |= 1 << lp[j];
-  std::vector<cd> in(gd), out(gd);
-  std::vector<int> idx(gd);
-  for (int col = 0; col < d; ++col) {
-    for (int base = 0; base < d; ++base) {
-      if (base & mask) continue;
+  for (int s = 0; s < gd; ++s) {
+    off[s] = 0;
+    for (int j = 0; j < gk; ++j) off[s] |= ((s >> j) & 1) << lp[j];
+  }
+  double xr[D * D], xi[D * D], yr[D], yi[D];
+  for (int base = 0; base < d; ++base) {
+    if (base & mask) continue;
+    for (int s = 0; s < gd; ++s)
+      for (int col = 0; col < d; ++col) {
+        const cd v = m[size_t(base | off[s]) * d + col];
+        xr[s * d + col] = v.real();
+        xi[s * d + col] = v.imag();
+      }
+    for (int r = 0; r < gd; ++r) {
+      for (int col = 0; col < d; ++col) yr[col] = yi[col] = 0;
       for (int s = 0; s < gd; ++s) {
-        int x = base;
-        for (int j = 0; j < gk; ++j) x |= ((s >> j) & 1) << lp[j];
-        idx[s] = x;
-        in[s] = m[size_t(x) * d + col];
+        const double gr = g[size_t(r) * gd + s].real(), gi = g[size_t(r) * gd + s].imag();
+        const double *pr = xr + s * d, *pi = xi + s * d;
+        for (int col = 0; col < d; ++col) {
+          yr[col] += gr * pr[col] - gi * pi[col];
+          yi[col] += gr * pi[col] + gi * pr[col];
+        }
       }
-      for (int r = 0; r < gd; ++r) {
-        cd acc = 0.0;
-        for (int s = 0; s < gd; ++s) acc += g[size_t(r) * gd + s] * in[s];
-        out[r] = acc;
-      }
-      for (int s = 0; s < gd; ++s) m[size_t(idx[s]) * d + col] = out[s];
+      for (int col = 0; col < d; ++col) m[size_t(base | off[r]) * d + col] = cd(yr[col], yi[col]);
     }
   }
 }
@@ -188,69 +198,6 @@ std::vector<Block> fuse(const std::vector<Gate>& gates, int n, int kmax) {
     if (open[b].live) emit(b);
   return out;
 }
-
-namespace {
-
-// The gates of a list (`qb`: the qubits of each) in the dependence order:
-// front() are those whose earlier gates on the same qubits are taken.
-struct DagCursor {
-  const std::vector<std::vector<int>>* qb = nullptr;
-  std::vector<std::vector<int>> per_qubit;  // gate positions (into sel) per qubit
-  std::vector<size_t> next;                 // per qubit: index into per_qubit
-  std::vector<char> done;
-  size_t remaining = 0;
-
-  DagCursor(const std::vector<std::vector<int>>& q, int nq) : qb(&q), per_qubit(nq), next(nq, 0) {
-    for (size_t i = 0; i < q.size(); ++i)
-      for (int x : q[i]) per_qubit[x].push_back(int(i));
-    done.assign(q.size(), 0);
-    remaining = q.size();
-  }
-  bool at_front(int i) const {
-    for (int x : (*qb)[i])
-      if (next[x] >= per_qubit[x].size() || per_qubit[x][next[x]] != i) return false;
-    return true;
-  }
-  void take(int i) {
-    done[i] = 1;
-    --remaining;
-    for (int x : (*qb)[i]) ++next[x];
-  }
-  // the front in circuit order
-  std::vector<int> front() const {
-    std::vector<int> f;
-    for (size_t x = 0; x < per_qubit.size(); ++x)
-      if (next[x] < per_qubit[x].size()) {
-        const int i = per_qubit[x][next[x]];
-        if (at_front(i) && std::find(f.begin(), f.end(), i) == f.end()) f.push_back(i);
-      }
-    std::sort(f.begin(), f.end());
-    return f;
-  }
-};
-
-// Greedy group: front gates (circuit order) whose qubits, with those already
-// chosen, fit in `budget`.
-std::vector<int> take_group(DagCursor& dag, int budget, std::vector<int>* chosen) {
-  std::vector<int> out;
-  bool progress = true;
-  while (progress) {
-    progress = false;
-    for (int i : dag.front()) {
-      std::vector<int> need;
-      for (int x : (*dag.qb)[i])
-        if (std::find(chosen->begin(), chosen->end(), x) == chosen->end()) need.push_back(x);
-      if (int(chosen->size() + need.size()) > budget) continue;
-      chosen->insert(chosen->end(), need.begin(), need.end());
-      dag.take(i);
-      out.push_back(i);
-      progress = true;
-    }
-  }
-  return out;
-}
-
-}  // namespace
 
 namespace {
 
@@ -406,10 +353,10 @@ struct PassPicker {
 
 }  // namespace
 
-TileMode matrix_tile_mode(const std::vector<Gate>& gates) {
+bool narrow_gates(const std::vector<Gate>& gates) {
   for (const auto& g : gates)
-    if (g.k > 2) return TileMode::kDense;
-  return TileMode::kPairs;
+    if (g.k > 2) return false;
+  return true;
 }
 
 namespace {
@@ -453,6 +400,7 @@ void pair_rounds(TilePlan* plan, const std::vector<Gate>& gates, const std::vect
     if (!need[i]) ready.push_back(int(i));
   auto emit = [&](const Op* o1, const Op* o2) {
     TileRound r;
+    r.mode = TileMode::kPairs;
     r.mat = plan->reals.size();
     r.ng = o2 ? 2 : 1;
     int nb = 0;
@@ -507,14 +455,178 @@ void pair_rounds(TilePlan* plan, const std::vector<Gate>& gates, const std::vect
 
 }  // namespace
 
-TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W, TileMode mode) {
+namespace {
+
+// What the rounds of a pass cost, in us per round (and gate of a sparse one):
+// fits to whole runs of fourteen kinds of circuits (layers of random pairs, of
+// neighbours, chains, rings, stars, gates on a few qubits only) in each form.
+// A pair round holds two gates and a dense or sparse one all that four bits
+// allow, so circuits that stay on few qubits, or go along a chain or a ring,
+// need up to hundreds of times the rounds in pairs: 10 layers of a ring on 27
+// qubits complex64 17.2 ms in dense rounds and 21.5 in pairs, of random pairs
+// 12.0 and 8.0; 250 gates on four of 20 qubits 5.8 and 140 us. The ratios hardly
+// depend on the size in complex64 (24 qubits; 12 qubits 0.80, 1.05, 1.73).
+// Complex128 rounds wait for LDS and barriers while a CU has one tile (12
+// qubits), where pairs do better, and are bound by the FMAs and the LDS
+// bandwidth when it has four or more (24 qubits): 8 layers of neighbours on 12
+// qubits 59 us in pairs and 65 in sparse rounds, 10 layers of a ring on 27 50.8
+// and 36 ms.
+struct RoundCost {
+  double pair[2];          // a pair round of one gate, of two
+  double group;            // a dense or a sparse round
+  double gate[2];          // a sparse round's gates on one qubit, on two
+};
+constexpr RoundCost kCost64{{6.7, 10.2}, 16.2, {0, 0}};
+constexpr RoundCost kCost128One{{1.23, 1.77}, 0.79, {0.47, 0.81}};  // up to 19 qubits
+constexpr RoundCost kCost128Two{{1.84, 2.67}, 0.75, {0.65, 1.12}};  // 20 qubits
+constexpr RoundCost kCost128{{22.6, 28.4}, 8.3, {5.7, 9.6}};
+
+// The rounds of a pass as groups of its gates: of the gates whose earlier ones
+// are taken, those that fit W tile bits, in circuit order, until none does;
+// `bits` are ascending, filled up with the lowest unused ones. Returns their
+// number; out may be NULL.
+struct Group {
+  std::vector<int> bits, gates;
+};
+int greedy_groups(const std::vector<std::vector<int>>& tq, int tile_bits, int W,
+                  std::vector<Group>* out) {
+  int at[33] = {};  // gates of each bit, in order: list[at[x] .. at[x + 1])
+  std::vector<uint32_t> mask(tq.size(), 0);
+  for (size_t i = 0; i < tq.size(); ++i)
+    for (int x : tq[i]) {
+      mask[i] |= uint32_t(1) << x;
+      ++at[x + 1];
+    }
+  for (int x = 0; x < tile_bits; ++x) at[x + 1] += at[x];
+  std::vector<int> list(mask.size() ? at[tile_bits] : 0);
+  int next[32];
+  std::copy(at, at + tile_bits, next);
+  for (size_t i = 0; i < tq.size(); ++i)
+    for (int x : tq[i]) list[next[x]++] = int(i);
+  std::copy(at, at + tile_bits, next);
+  auto front = [&](int x) { return next[x] < at[x + 1] ? list[next[x]] : -1; };
+  int count = 0;
+  for (size_t left = tq.size(); left; ++count) {
+    if (out) out->emplace_back();
+    uint32_t set = 0;
+    for (bool progress = true; progress;) {
+      progress = false;
+      int ready[32], nready = 0;
+      for (int x = 0; x < tile_bits; ++x) {
+        const int i = front(x);
+        if (i < 0 || (mask[i] & ((uint32_t(1) << x) - 1))) continue;  // seen at its lowest bit
+        bool first = true;
+        for (int y : tq[i]) first = first && front(y) == i;
+        if (first) ready[nready++] = i;
+      }
+      std::sort(ready, ready + nready);
+      for (int r = 0; r < nready; ++r) {
+        const int i = ready[r];
+        if (__builtin_popcount(set | mask[i]) > W) continue;
+        set |= mask[i];
+        for (int y : tq[i]) ++next[y];
+        if (out) out->back().gates.push_back(i);
+        --left;
+        progress = true;
+      }
+    }
+    if (!out) continue;
+    for (int b = 0; __builtin_popcount(set) < W; ++b) set |= uint32_t(1) << b;
+    for (int b = 0; b < tile_bits; ++b)
+      if ((set >> b) & 1) out->back().bits.push_back(b);
+  }
+  return count;
+}
+
+// Emits a group's round: the product of its gates (dense) or the gates one by
+// one (sparse).
+void group_round(TilePlan* plan, const std::vector<Gate>& gates, const std::vector<int>& pass,
+                 const std::vector<std::vector<int>>& tq, const Group& group, int W, bool dense) {
+  const std::vector<int>& rb = group.bits;
+  TileRound r;
+  r.mode = dense ? TileMode::kDense : TileMode::kSparse;
+  for (int j = 0; j < W; ++j) r.bits[j] = rb[j];
+  r.g0 = int(plan->gates.size());
+  r.ng = int(group.gates.size());
+  if (dense) {
+    // the product of the round's gates on its W bits (local bit j = rb[j])
+    std::vector<cd> u = eye(W);
+    for (int gi : group.gates) {
+      const Gate& g = gates[pass[gi]];
+      int lp[QS_MAX_FUSED];
+      for (int j = 0; j < g.k; ++j)
+        lp[j] = int(std::find(rb.begin(), rb.end(), tq[gi][j]) - rb.begin());
+      left_apply(u, W, g.m, g.k, lp);
+    }
+    r.mat = plan->mats.size();
+    plan->mats.insert(plan->mats.end(), u.begin(), u.end());
+  } else {
+    // one-qubit gates folded into the round's two-qubit gates: into the
+    // last two-qubit gate on their bit (from the left) when there is one,
+    // else into the next (from the right); one-qubit products on bits no
+    // two-qubit gate of the round touches stay one-qubit gates (they
+    // commute with the rest of the round)
+    struct Out { int kind, j1, j2; std::vector<cd> m; };
+    std::vector<Out> outg;
+    std::vector<int> last(W, -1);            // per round bit: its last two-qubit gate
+    std::vector<std::vector<cd>> pend(W);    // per round bit: pending one-qubit product
+    for (int gi : group.gates) {
+      const Gate& g = gates[pass[gi]];
+      const int j1 = int(std::find(rb.begin(), rb.end(), tq[gi][0]) - rb.begin());
+      if (g.k == 1) {
+        if (last[j1] >= 0) {
+          Out& o = outg[size_t(last[j1])];
+          const int at = o.j1 == j1 ? 0 : 1;
+          left_apply(o.m, 2, g.m, 1, &at);
+        } else {
+          if (pend[j1].empty()) pend[j1] = eye(1);
+          const int at = 0;
+          left_apply(pend[j1], 1, g.m, 1, &at);
+        }
+        continue;
+      }
+      const int j2 = int(std::find(rb.begin(), rb.end(), tq[gi][1]) - rb.begin());
+      std::vector<cd> m = eye(2);
+      const int bit0 = 0, bit1 = 1, both[2] = {0, 1};
+      if (!pend[j1].empty()) left_apply(m, 2, pend[j1], 1, &bit0);
+      if (!pend[j2].empty()) left_apply(m, 2, pend[j2], 1, &bit1);
+      left_apply(m, 2, g.m, 2, both);
+      pend[j1].clear();
+      pend[j2].clear();
+      last[j1] = last[j2] = int(outg.size());
+      outg.push_back({2, j1, j2, std::move(m)});
+    }
+    for (int j = 0; j < W; ++j)
+      if (!pend[j].empty()) outg.push_back({1, j, 0, std::move(pend[j])});
+    r.ng = int(outg.size());
+    for (Out& o : outg) {
+      TileGate tg;
+      tg.kind = o.kind;
+      tg.j1 = o.j1;
+      tg.j2 = o.j2;
+      tg.mat = plan->mats.size();
+      plan->mats.insert(plan->mats.end(), o.m.begin(), o.m.end());
+      plan->gates.push_back(tg);
+    }
+  }
+  plan->rounds.push_back(r);
+}
+
+}  // namespace
+
+TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W,
+                    TileForms forms) {
   const std::vector<Gate> gates = merge_gates(circuit, n);
   TilePlan plan;
   plan.C = C;
   plan.H = H;
   plan.W = W;
-  plan.mode = mode;
-  const bool dense = mode == TileMode::kDense;
+  plan.forms = forms;
+  const bool dense = forms == TileForms::kPairsDense || forms == TileForms::kDense;
+  const RoundCost& cost = dense     ? kCost64
+                          : n <= 19 ? kCost128One
+                          : n == 20 ? kCost128Two
+                                    : kCost128;
   std::vector<std::vector<int>> qb(gates.size());
   for (size_t i = 0; i < gates.size(); ++i) qb[i].assign(gates[i].q, gates[i].q + gates[i].k);
   PassPicker picker(gates, n, dense ? W : 2);
@@ -556,89 +668,40 @@ TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W
     for (int j = 0; j < H; ++j) st.hb[j] = hi[j];
     st.r0 = int(plan.rounds.size());
     st.ngates = int(pass.size());
-    // rounds: the same greedy grouping on tile bits, W bits each
     std::vector<std::vector<int>> tq(pass.size());
     for (size_t i = 0; i < pass.size(); ++i)
       for (int x : qb[pass[i]]) tq[i].push_back(tbit[x]);
-    if (mode == TileMode::kPairs) {
+    // the rounds, in the cheaper of the two forms the plan may use
+    bool narrow = true;
+    for (int i : pass) narrow = narrow && gates[i].k <= 2;
+    const bool pairs = narrow && forms != TileForms::kSparse && forms != TileForms::kDense;
+    const bool groups = !pairs || forms != TileForms::kPairs;
+    const size_t reals0 = plan.reals.size();
+    double pair_cost = 0, group_cost = 0;
+    if (pairs) {
       pair_rounds(&plan, gates, pass, tq, C + H);
-      st.nr = int(plan.rounds.size()) - st.r0;
-      plan.steps.push_back(st);
-      continue;
+      st.mode = TileMode::kPairs;
+      for (size_t r = size_t(st.r0); r < plan.rounds.size(); ++r)
+        pair_cost += cost.pair[plan.rounds[r].ng - 1];
     }
-    DagCursor rd(tq, C + H);
-    while (rd.remaining) {
-      std::vector<int> rb;
-      const std::vector<int> grp = take_group(rd, W, &rb);
-      for (int b = 0; b < C + H && int(rb.size()) < W; ++b)
-        if (std::find(rb.begin(), rb.end(), b) == rb.end()) rb.push_back(b);
-      std::sort(rb.begin(), rb.end());
-      TileRound r;
-      for (int j = 0; j < W; ++j) r.bits[j] = rb[j];
-      r.g0 = int(plan.gates.size());
-      r.ng = int(grp.size());
-      if (dense) {
-        // the product of the round's gates on its W bits (local bit j = rb[j])
-        std::vector<cd> u = eye(W);
-        for (int gi : grp) {
-          const Gate& g = gates[pass[gi]];
-          int lp[QS_MAX_FUSED];
-          for (int j = 0; j < g.k; ++j)
-            lp[j] = int(std::find(rb.begin(), rb.end(), tq[gi][j]) - rb.begin());
-          left_apply(u, W, g.m, g.k, lp);
-        }
-        r.mat = plan.mats.size();
-        plan.mats.insert(plan.mats.end(), u.begin(), u.end());
-      } else {
-        // one-qubit gates folded into the round's two-qubit gates: into the
-        // last two-qubit gate on their bit (from the left) when there is one,
-        // else into the next (from the right); one-qubit products on bits no
-        // two-qubit gate of the round touches stay one-qubit gates (they
-        // commute with the rest of the round)
-        struct Out { int kind, j1, j2; std::vector<cd> m; };
-        std::vector<Out> outg;
-        std::vector<int> last(W, -1);            // per round bit: its last two-qubit gate
-        std::vector<std::vector<cd>> pend(W);    // per round bit: pending one-qubit product
-        for (int gi : grp) {
-          const Gate& g = gates[pass[gi]];
-          const int j1 = int(std::find(rb.begin(), rb.end(), tq[gi][0]) - rb.begin());
-          if (g.k == 1) {
-            if (last[j1] >= 0) {
-              Out& o = outg[size_t(last[j1])];
-              const int at = o.j1 == j1 ? 0 : 1;
-              left_apply(o.m, 2, g.m, 1, &at);
-            } else {
-              if (pend[j1].empty()) pend[j1] = eye(1);
-              const int at = 0;
-              left_apply(pend[j1], 1, g.m, 1, &at);
-            }
-            continue;
-          }
-          const int j2 = int(std::find(rb.begin(), rb.end(), tq[gi][1]) - rb.begin());
-          std::vector<cd> m = eye(2);
-          const int bit0 = 0, bit1 = 1, both[2] = {0, 1};
-          if (!pend[j1].empty()) left_apply(m, 2, pend[j1], 1, &bit0);
-          if (!pend[j2].empty()) left_apply(m, 2, pend[j2], 1, &bit1);
-          left_apply(m, 2, g.m, 2, both);
-          pend[j1].clear();
-          pend[j2].clear();
-          last[j1] = last[j2] = int(outg.size());
-          outg.push_back({2, j1, j2, std::move(m)});
-        }
-        for (int j = 0; j < W; ++j)
-          if (!pend[j].empty()) outg.push_back({1, j, 0, std::move(pend[j])});
-        r.ng = int(outg.size());
-        for (Out& o : outg) {
-          TileGate tg;
-          tg.kind = o.kind;
-          tg.j1 = o.j1;
-          tg.j2 = o.j2;
-          tg.mat = plan.mats.size();
-          plan.mats.insert(plan.mats.end(), o.m.begin(), o.m.end());
-          plan.gates.push_back(tg);
-        }
+    if (groups) {
+      if (pairs) {
+        group_cost = cost.group * greedy_groups(tq, C + H, W, nullptr);
+        if (!dense)
+          for (int i : pass) group_cost += cost.gate[gates[i].k - 1];
       }
-      plan.rounds.push_back(r);
+      if (!pairs || group_cost < pair_cost) {
+        plan.rounds.resize(size_t(st.r0));
+        plan.reals.resize(reals0);
+        st.mode = dense ? TileMode::kDense : TileMode::kSparse;
+        std::vector<Group> grp;
+        greedy_groups(tq, C + H, W, &grp);
+        for (const Group& g : grp) group_round(&plan, gates, pass, tq, g, W, dense);
+      }
+    }
+    if (pairs && groups) {
+      plan.pair_cost += pair_cost;
+      plan.group_cost += group_cost;
     }
     st.nr = int(plan.rounds.size()) - st.r0;
     plan.steps.push_back(st);
@@ -656,68 +719,47 @@ void pair_round_entry(const TileRound& r, size_t base, int32_t row[4]) {
   row[3] = r.ng > 1 ? 1 : 0;
 }
 
-void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, size_t* gates_off,
-                 size_t* mats_off, size_t* emb_off) {
-  const bool dense = pl.mode == TileMode::kDense;
-  const bool pairs = pl.mode == TileMode::kPairs;
+void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, TileOffsets* at) {
   std::vector<int32_t> tab;
-  for (size_t ri = 0; ri < pl.rounds.size(); ++ri) {
-    const auto& r = pl.rounds[ri];
-    if (pairs) {
-      int32_t row[4];
+  std::vector<float> ops;  // dense rounds
+  for (const TileRound& r : pl.rounds) {
+    int32_t row[4] = {r.bits[0] | (r.bits[1] << 8) | (r.bits[2] << 16) | (r.bits[3] << 24), r.g0,
+                      r.ng, 0};
+    if (r.mode == TileMode::kPairs) {
       pair_round_entry(r, 0, row);
-      tab.insert(tab.end(), row, row + 4);
-      continue;
+    } else if (r.mode == TileMode::kDense) {
+      row[1] = int32_t(ops.size());
+      ops.resize(ops.size() + kRoundOperands);
+      embed_round(pl.mats.data() + r.mat, ops.data() + row[1]);
     }
-    tab.push_back(r.bits[0] | (r.bits[1] << 8) | (r.bits[2] << 16) | (r.bits[3] << 24));
-    tab.push_back(dense ? int32_t(ri * kRoundOperands) : r.g0);
-    tab.push_back(r.ng);
-    tab.push_back(0);
+    tab.insert(tab.end(), row, row + 4);
   }
-  const size_t gates_at = tab.size() * sizeof(int32_t);
-  if (!dense)
-    for (const auto& g : pl.gates) {
-      tab.push_back(g.kind | (g.j1 << 4) | (g.j2 << 8));
-      tab.push_back(int32_t(2 * g.mat));
-    }
+  auto up256 = [](size_t x) { return (x + 255) / 256 * 256; };
+  at->gates = tab.size() * sizeof(int32_t);
+  for (const auto& g : pl.gates) {
+    tab.push_back(g.kind | (g.j1 << 4) | (g.j2 << 8));
+    tab.push_back(int32_t(2 * g.mat));
+  }
   const size_t esz = c64 ? sizeof(float) : sizeof(double);
-  const size_t emb_at = (tab.size() * sizeof(int32_t) + 255) / 256 * 256;
-  // dense rounds: each round's matrix-core operands in lane order, then the
-  // matrices of the block steps; sparse rounds: every matrix as is
-  const size_t emb = dense ? pl.rounds.size() * kRoundOperands * sizeof(float) : 0;
-  const size_t real_at = emb_at + emb + 2 * pl.mats.size() * esz;
-  const size_t total = real_at + pl.reals.size() * esz;
-  out->assign(total, 0);
+  at->ops = up256(tab.size() * sizeof(int32_t));
+  at->mats = up256(at->ops + ops.size() * sizeof(float));
+  at->reals = up256(at->mats + 2 * pl.mats.size() * esz);
+  out->assign(at->reals + pl.reals.size() * esz, 0);
   unsigned char* host = out->data();
   std::memcpy(host, tab.data(), tab.size() * sizeof(int32_t));
-  if (dense) {
-    std::vector<float> A(kRoundOperands);
-    for (size_t ri = 0; ri < pl.rounds.size(); ++ri) {
-      embed_round(pl.mats.data() + pl.rounds[ri].mat, A.data());
-      std::memcpy(host + emb_at + ri * kRoundOperands * sizeof(float), A.data(),
-                  kRoundOperands * sizeof(float));
-    }
-  }
+  if (!ops.empty()) std::memcpy(host + at->ops, ops.data(), ops.size() * sizeof(float));
+  auto put = [&](unsigned char* to, double v) {
+    const float f = float(v);
+    if (c64)
+      std::memcpy(to, &f, sizeof f);
+    else
+      std::memcpy(to, &v, sizeof v);
+  };
   for (size_t i = 0; i < pl.mats.size(); ++i) {
-    if (c64) {
-      const float v[2] = {float(pl.mats[i].real()), float(pl.mats[i].imag())};
-      std::memcpy(host + emb_at + emb + 2 * i * esz, v, sizeof v);
-    } else {
-      const double v[2] = {pl.mats[i].real(), pl.mats[i].imag()};
-      std::memcpy(host + emb_at + emb + 2 * i * esz, v, sizeof v);
-    }
+    put(host + at->mats + 2 * i * esz, pl.mats[i].real());
+    put(host + at->mats + (2 * i + 1) * esz, pl.mats[i].imag());
   }
-  for (size_t i = 0; i < pl.reals.size(); ++i) {
-    if (c64) {
-      const float v = float(pl.reals[i]);
-      std::memcpy(host + real_at + i * esz, &v, sizeof v);
-    } else {
-      std::memcpy(host + real_at + i * esz, &pl.reals[i], sizeof(double));
-    }
-  }
-  *gates_off = pairs ? real_at : gates_at;
-  *emb_off = emb_at;
-  *mats_off = emb_at + emb;
+  for (size_t i = 0; i < pl.reals.size(); ++i) put(host + at->reals + i * esz, pl.reals[i]);
 }
 
 void embed_round(const cd* u, float* out) {
@@ -874,9 +916,9 @@ int qs_circuit_tile_info(const qs_circuit* c, int dtype, int* passes, int* block
   if (dtype != QS_C64 && dtype != QS_C128) return cfail(QS_E_INVAL, "unknown dtype %d", dtype);
   const int C = qs::tile_low_bits(dtype);
   if (c->n < C + 7) return cfail(QS_E_UNSUPPORTED, "%d qubits: fewer than one tile (%d)", c->n, C + 7);
-  const qs::TilePlan pl =
-      qs::plan_tiles(c->gates, c->n, C, 7, 4,
-                     dtype == QS_C64 ? qs::matrix_tile_mode(c->gates) : qs::TileMode::kPairs);
+  const qs::TilePlan pl = qs::plan_tiles(
+      c->gates, c->n, C, 7, 4,
+      dtype == QS_C64 ? qs::TileForms::kPairsDense : qs::TileForms::kPairsSparse);
   if (passes) *passes = pl.passes();
   if (blocks) *blocks = int(pl.steps.size()) - pl.passes();
   if (rounds) *rounds = int(pl.rounds.size());

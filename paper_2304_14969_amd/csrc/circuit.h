@@ -47,7 +47,22 @@ struct TileGate {
   int j1 = 0, j2 = 0;
   size_t mat = 0;    // offset of the matrix in TilePlan::mats (complex entries)
 };
+// What the rounds of a pass hold: gates of one or two qubits on any of the
+// round's bits (kSparse); one or two gates on disjoint pairs, the first on the
+// round's bits 0 and 1, the second on 2 and 3 (kPairs); one dense product of
+// gates of at most W qubits (kDense). A pair round's numbers (TilePlan::reals)
+// are its gates' 4 x 4 complex matrices (32 reals each, row-major).
+enum class TileMode { kSparse, kPairs, kDense };
+// The forms a plan may use; where there are two, each pass takes the cheaper.
+enum class TileForms {
+  kSparse,       // complex64 off the matrix cores; runs of one-qubit gates
+  kPairs,        // states below a tile, batches
+  kDense,        // complex64 batches
+  kPairsDense,   // complex64 on the matrix cores
+  kPairsSparse,  // complex128
+};
 struct TileRound {
+  TileMode mode = TileMode::kSparse;
   int bits[4] = {0, 0, 0, 0};  // tile bits of the round, ascending (pairs: the
                                // first gate's two, then the second's)
   int g0 = 0, ng = 0;          // its gates in TilePlan::gates (sparse); pairs: 1 or 2 gates
@@ -55,26 +70,24 @@ struct TileRound {
 };
 struct TileStep {
   bool block = false;  // a dense block (a gate on more than two qubits), not a pass
-  int hb[8] = {0};     // pass: the H row bits (physical, ascending)
-  int r0 = 0, nr = 0;  // pass: its rounds
-  int ngates = 0;
+  TileMode mode = TileMode::kSparse;  // pass: of its rounds
+  int hb[7] = {0, 0, 0, 0, 0, 0, 0};  // pass: tile row bits, ascending
+  int r0 = 0, nr = 0;  // pass: its rounds in TilePlan::rounds
+  int ngates = 0;      // pass: gates applied; block: 1
   Block blk;           // block step, on physical bits
   size_t mat = 0;      // block step: offset of its matrix
 };
-// What the rounds of a plan hold: gates of one or two qubits on any of the
-// round's bits (kSparse); one or two gates on disjoint pairs, the first on the
-// round's bits 0 and 1, the second on 2 and 3 (kPairs); one dense product of
-// gates of at most W qubits (kDense). A pair round's numbers (TilePlan::reals)
-// are its gates' 4 x 4 complex matrices (32 reals each, row-major).
-enum class TileMode { kSparse, kPairs, kDense };
 struct TilePlan {
   int C = 0, H = 0, W = 0;
-  TileMode mode = TileMode::kSparse;
+  TileForms forms = TileForms::kSparse;
   std::vector<TileStep> steps;
   std::vector<TileRound> rounds;
   std::vector<TileGate> gates;
   std::vector<cd> mats;
   std::vector<double> reals;  // pair rounds
+  // forms of two kinds: what the passes that could take either cost in pair
+  // rounds and in the other form (the same units, per tile)
+  double pair_cost = 0, group_cost = 0;
   int passes() const {
     int p = 0;
     for (const auto& s : steps) p += s.block ? 0 : 1;
@@ -88,26 +101,26 @@ struct TilePlan {
 // the low bits plus at most H other bits, which are chosen to let many gates
 // run (PassPicker in circuit.cpp). Within a pass, sparse and dense rounds are
 // formed greedily, W bits each; pair rounds take the two ready gates with the
-// longest chains of gates behind them. Gates too wide for a round (more than
+// longest chains of gates behind them; a pass takes the form whose rounds cost
+// less (RoundCost in circuit.cpp). Gates too wide for a round (more than
 // two qubits, or more than W for dense rounds) run as blocks between passes.
-TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, TileMode mode);
+TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, TileForms forms);
 
-// Rounds of complex64 passes: pairs, or dense products when the circuit has
-// gates of more than two qubits (so that they still join the passes).
-// (Complex128 passes always have pairs.)
-TileMode matrix_tile_mode(const std::vector<Gate>& gates);
+// Whether every gate has one or two qubits.
+bool narrow_gates(const std::vector<Gate>& gates);
 
 // The device tables of a plan, as one byte image: per round an int4 {bits
-// packed by byte, first gate (sparse) or embedding offset in floats (dense),
+// packed by byte, first gate (sparse) or operand offset in floats (dense),
 // gate count, 0}, or for pairs {bits packed by byte, the same bits ascending,
-// offset of its numbers, 1 if it has a second gate}; per gate
-// (sparse) an int2 {kind | j1 << 4 | j2 << 8, offset
-// of its matrix in reals}; at emb_off (dense) the rounds' 32 x 32 embeddings
-// in lane order (float); at mats_off the plan's matrices (float or double
-// pairs); for pairs, at gates_off their numbers. Offsets are bytes from the
-// start.
-void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, size_t* gates_off,
-                 size_t* mats_off, size_t* emb_off);
+// offset of its numbers, 1 if it has a second gate}; at `gates` per gate
+// (sparse) an int2 {kind | j1 << 4 | j2 << 8, offset of its matrix in reals};
+// at `ops` the dense rounds' matrix-core operands (embed_round); at `mats` the
+// plan's matrices (float or double pairs); at `reals` the pair rounds' numbers.
+// Offsets are bytes from the start.
+struct TileOffsets {
+  size_t gates = 0, ops = 0, mats = 0, reals = 0;
+};
+void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, TileOffsets* at);
 
 // A pair round's table entry (int4 as above), its numbers moved by `base`.
 void pair_round_entry(const TileRound& r, size_t base, int32_t row[4]);
@@ -150,10 +163,12 @@ struct qs_circuit {
     std::vector<int> key;  // physical bit of every virtual position
     qs::TilePlan plan;
     void* dev = nullptr;   // rounds, gates, matrices (owned)
-    size_t gates_off = 0, mats_off = 0, emb_off = 0;  // byte offsets in dev
+    qs::TileOffsets at;
   } tcache[2];
-  // host plan for batched runs (identity labelling, dense rounds); cleared
-  // with the other plans when the circuit changes
-  bool bplan_ok = false;
+  // host plan for batched runs (identity labelling), and what its passes cost
+  // in pair and in dense rounds once that was asked for; cleared with the other
+  // plans when the circuit changes
+  bool bplan_ok = false, bcost_ok = false;
   qs::TilePlan bplan;
+  double bcost[2] = {0, 0};
 };

@@ -1705,10 +1705,10 @@ int large_1q_run(FactorState* f, int si, const int* qubits, const double* m,
       for (int e = 0; e < 4; ++e)
         g.m[e] = cd(m[8 * list[i] + 2 * e], m[8 * list[i] + 2 * e + 1]);
     }
-    const TilePlan pl = plan_tiles(gl, S.nq, kLow, kTileRowBits, 4, TileMode::kSparse);
+    const TilePlan pl = plan_tiles(gl, S.nq, kLow, kTileRowBits, 4, TileForms::kSparse);
     std::vector<unsigned char> tab;
-    size_t goff = 0, moff = 0, eoff = 0;
-    tile_tables(pl, sizeof(R) == 4, &tab, &goff, &moff, &eoff);
+    TileOffsets at;
+    tile_tables(pl, sizeof(R) == 4, &tab, &at);
     if (tab.size() <= FactorState::kSlotBytes) {
       if (tab.size() > f->tile_cap) {
         if (int rc = dev_err(hipStreamSynchronize(f->stream), "tile tables")) return rc;
@@ -1736,7 +1736,7 @@ int large_1q_run(FactorState* f, int si, const int* qubits, const double* m,
         TileRows rows;
         for (int j = 0; j < kTileRowBits; ++j) rows.b[j] = st.hb[j];
         e = launch_tile_pass(amps, S.nq, kLow, rows, base + size_t(st.r0) * 4 * sizeof(int32_t),
-                             st.nr, base + goff, reinterpret_cast<const R*>(base + moff),
+                             st.nr, base + at.gates, reinterpret_cast<const R*>(base + at.mats),
                              f->stream);
       }
       return dev_err(e, "one-qubit tile passes");
