@@ -475,11 +475,12 @@ struct RoundCost {
   double pair[2];          // a pair round of one gate, of two
   double group;            // a dense or a sparse round
   double gate[2];          // a sparse round's gates on one qubit, on two
+  double pass;             // a pass of these over one of pair rounds, without the rounds
 };
-constexpr RoundCost kCost64{{6.7, 10.2}, 16.2, {0, 0}};
-constexpr RoundCost kCost128One{{1.23, 1.77}, 0.79, {0.47, 0.81}};  // up to 19 qubits
-constexpr RoundCost kCost128Two{{1.84, 2.67}, 0.75, {0.65, 1.12}};  // 20 qubits
-constexpr RoundCost kCost128{{22.6, 28.4}, 8.3, {5.7, 9.6}};
+constexpr RoundCost kCost64{{6.7, 10.2}, 16.2, {0, 0}, -5};
+constexpr RoundCost kCost128One{{1.23, 1.77}, 0.79, {0.47, 0.81}, 0.5};  // up to 19 qubits
+constexpr RoundCost kCost128Two{{1.84, 2.67}, 0.75, {0.65, 1.12}, 0.5};  // 20 qubits
+constexpr RoundCost kCost128{{22.6, 28.4}, 8.3, {5.7, 9.6}, 14};
 
 // The rounds of a pass as groups of its gates: of the gates whose earlier ones
 // are taken, those that fit W tile bits, in circuit order, until none does;
@@ -686,7 +687,7 @@ TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W
     }
     if (groups) {
       if (pairs) {
-        group_cost = cost.group * greedy_groups(tq, C + H, W, nullptr);
+        group_cost = cost.pass + cost.group * greedy_groups(tq, C + H, W, nullptr);
         if (!dense)
           for (int i : pass) group_cost += cost.gate[gates[i].k - 1];
       }
