@@ -404,10 +404,12 @@ int qs_circuit_plan(qs_circuit* c, int kmax);
  * the state's labelling differs). Gates too wide for a round (more than 4
  * qubits with "tile.mfma" on, more than 2 otherwise or for complex128) run
  * as dense blocks between passes. States with fewer qubits than a tile (its
- * low bits + 7) run whole in the LDS of one workgroup, the circuit in one
- * launch, when every gate has at most two qubits ("tile.mfma" on for
- * complex64), and as fused blocks otherwise. Same results as the block path
- * up to float rounding order. */
+ * low bits + 7), of at most 11 qubits in complex64 and 10 in complex128, run a
+ * circuit whose gates have at most two qubits ("tile.mfma" on for complex64)
+ * in one launch in the LDS of one workgroup, or as fused blocks where these
+ * are estimated to be faster (many gates on few qubits); other states below a
+ * tile, and other circuits on them, as fused blocks. Same results as the block
+ * path up to float rounding order. */
 int qs_circuit_use_tiles(qs_circuit* c, int on);
 /* Tile plan of the circuit for a state in the identity labelling (current
  * "tile.*" knobs): passes,

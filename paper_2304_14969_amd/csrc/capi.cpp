@@ -337,7 +337,9 @@ uint64_t next_generation() {
 
 void circuit_invalidate(qs_circuit* c) {
   // launches already queued may still read the matrices
-  if (c->dmat[0] || c->dmat[1] || c->tcache[0].dev || c->tcache[1].dev) (void)hipDeviceSynchronize();
+  if (c->dmat[0] || c->dmat[1] || c->tcache[0].dev || c->tcache[1].dev || c->whole[0].dev ||
+      c->whole[1].dev)
+    (void)hipDeviceSynchronize();
   for (int p = 0; p < 2; ++p) {
     if (c->dmat[p]) dev_free(c->dmat[p]);
     c->dmat[p] = nullptr;
@@ -346,6 +348,8 @@ void circuit_invalidate(qs_circuit* c) {
     c->tcache[p].dev = nullptr;
     c->tcache[p].key.clear();
     c->tcache[p].plan = qs::TilePlan();
+    if (c->whole[p].dev) dev_free(c->whole[p].dev);
+    c->whole[p] = qs_circuit::WholeCache();
   }
   c->planned = false;
   c->due = false;
@@ -974,15 +978,100 @@ int qs_circuit_free(qs_circuit* c) {
 
 namespace {
 
-// A state smaller than a tile whose circuit has only one- and two-qubit gates
-// runs whole in the LDS of one workgroup (on the matrix cores in complex64,
-// so not with "tile.mfma" off).
-bool runs_whole(const qs_state* st, const qs_circuit* c) {
-  if (st->n > (st->dtype == QS_C64 ? 11 : 10) ||
-      st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits)
-    return false;
-  if (st->dtype == QS_C64 && !g_tile_mfma) return false;
-  return qs::narrow_gates(c->gates);
+// How a state smaller than a tile runs a circuit of one- and two-qubit gates
+// (on the matrix cores in complex64, so not with "tile.mfma" off): gate after
+// gate in the LDS of one workgroup, as one matrix on all of up to 5 qubits, or
+// as blocks, which do better where many gates stay on few qubits. In us per
+// run: a gate in LDS 0.36 (11 qubits 0.44; complex128 0.58) besides 1.7; a
+// block, a launch of its own, 2.8 and on five of 9 to 11 qubits 3.0, 3.7, 5.3
+// (complex128 3.4, 4.4), on six 1.6 times that; the matrix 3.4. Gates are
+// counted as they merge. 200 gates on four of 10 qubits: 56 us in LDS, 3.8 as a
+// block; 40 layers on 5 qubits complex128 37 us in LDS, 3.9 as one matrix.
+// Blocks have to promise 4/5 of the time: the estimates are no closer.
+qs_circuit::WholeForm whole_form(const qs_state* st, qs_circuit* c) {
+  const bool c64 = st->dtype == QS_C64;
+  if (st->n > (c64 ? 11 : 10) || st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits ||
+      (c64 && !g_tile_mfma))
+    return qs_circuit::kBlocks;
+  qs_circuit::WholeCache& w = c->whole[c64 ? 0 : 1];
+  if (w.form != qs_circuit::kUndecided && w.kmax == c->kmax) return w.form;
+  qs_circuit::WholeForm form = qs_circuit::kBlocks;
+  if (qs::narrow_gates(c->gates)) {
+    const double rounds =
+        1.7 + qs::merged_gates(c->gates, c->n) * (!c64 ? 0.58 : st->n < 11 ? 0.36 : 0.44);
+    form = qs_circuit::kRounds;
+    if (st->n <= 5) {
+      if (rounds > 3.4) form = qs_circuit::kMatrix;
+    } else {
+      int count[QS_MAX_FUSED + 1];
+      qs::block_widths(c->gates, c->n, c->kmax, count);
+      const double k5 = st->n < 9 ? 2.8 : c64 ? (st->n == 9 ? 3.0 : st->n == 10 ? 3.7 : 5.3)
+                                              : (st->n == 9 ? 3.4 : 4.4);
+      double blocks = 1.6 * k5 * count[6] + k5 * count[5];
+      for (int k = 1; k <= 4; ++k) blocks += 2.8 * count[k];
+      if (blocks < 0.8 * rounds) form = qs_circuit::kBlocks;
+    }
+  }
+  if (w.form != form && w.dev) {
+    (void)hipDeviceSynchronize();
+    dev_free(w.dev);
+    w.dev = nullptr;
+  }
+  w.form = form;
+  w.kmax = c->kmax;
+  return form;
+}
+
+// Runs the circuit in one launch (kRounds or kMatrix). The tables are made for
+// virtual positions and uploaded once per precision.
+int run_whole(qs_state* st, qs_circuit* c, qs_circuit::WholeForm form) {
+  const bool c64 = st->dtype == QS_C64;
+  qs_circuit::WholeCache& w = c->whole[c64 ? 0 : 1];
+  if (!w.dev) {
+    std::vector<unsigned char> host;
+    if (form == qs_circuit::kRounds) {
+      const int bits = qs::whole_bits(st->n);
+      const qs::TilePlan pl = qs::plan_tiles(c->gates, bits, bits - qs::kTileRowBits,
+                                             qs::kTileRowBits, 4, qs::TileForms::kPairs);
+      qs::TileOffsets at;
+      qs::tile_tables(pl, c64, &host, &at);
+      w.nrounds = int(pl.rounds.size());
+      w.num = at.reals;
+    } else {
+      const qs::Block b = qs::whole_block(c->gates, st->n);
+      const double* m = reinterpret_cast<const double*>(b.m.data());
+      host.resize(2 * b.m.size() * (c64 ? sizeof(float) : sizeof(double)));
+      for (size_t i = 0; i < 2 * b.m.size(); ++i) {
+        if (c64)
+          reinterpret_cast<float*>(host.data())[i] = float(m[i]);
+        else
+          reinterpret_cast<double*>(host.data())[i] = m[i];
+      }
+    }
+    void* d = dev_alloc(std::max<size_t>(host.size(), 256));
+    if (!d) return fail(QS_E_NOMEM, "allocating %zu bytes of circuit tables", host.size());
+    const hipError_t e = hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      dev_free(d);
+      return device_error(st, e, "uploading circuit tables");
+    }
+    w.dev = d;
+  }
+  ProfScope ps(st, "circuit_lds", 2.0 * std::ldexp(1.0, st->n) * ab(st));
+  hipError_t e;
+  if (form == qs_circuit::kMatrix) {
+    e = c64 ? qs::launch_small_block(static_cast<float*>(st->amps), st->n, st->perm, st->n,
+                                     static_cast<const float*>(w.dev), st->stream)
+            : qs::launch_small_block(static_cast<double*>(st->amps), st->n, st->perm, st->n,
+                                     static_cast<const double*>(w.dev), st->stream);
+  } else {
+    const void* num = static_cast<const char*>(w.dev) + w.num;
+    e = c64 ? qs::launch_whole(static_cast<float*>(st->amps), st->n, st->perm, w.dev, w.nrounds,
+                               static_cast<const float*>(num), st->stream)
+            : qs::launch_whole(static_cast<double*>(st->amps), st->n, st->perm, w.dev, w.nrounds,
+                               static_cast<const double*>(num), st->stream);
+  }
+  return device_error(st, e, "circuit in LDS");
 }
 
 // The tile plan of circuit c for the state's precision and current labelling
@@ -990,14 +1079,11 @@ bool runs_whole(const qs_state* st, const qs_circuit* c) {
 int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   const int prec = st->dtype == QS_C64 ? 0 : 1;
   qs_circuit::TileCache& tc = c->tcache[prec];
-  const bool whole = runs_whole(st, c);
-  const int bits = whole ? qs::whole_bits(st->n) : st->n;
-  const int low = whole ? bits - qs::kTileRowBits : qs::tile_low_bits(st->dtype);
+  const int low = qs::tile_low_bits(st->dtype);
   std::vector<int> key(st->perm, st->perm + st->n);
-  const qs::TileForms forms = whole                  ? qs::TileForms::kPairs
-                              : st->dtype == QS_C128 ? qs::TileForms::kPairsSparse
-                              : g_tile_mfma          ? qs::TileForms::kPairsDense
-                                                     : qs::TileForms::kSparse;
+  const qs::TileForms forms = st->dtype == QS_C128 ? qs::TileForms::kPairsSparse
+                              : g_tile_mfma        ? qs::TileForms::kPairsDense
+                                                   : qs::TileForms::kSparse;
   if (tc.dev && tc.key == key && tc.plan.forms == forms && tc.plan.C == low) {
     *out = &tc;
     return QS_OK;
@@ -1010,7 +1096,7 @@ int tile_plan_for(qs_state* st, qs_circuit* c, qs_circuit::TileCache** out) {
   std::vector<qs::Gate> phys = c->gates;
   for (auto& g : phys)
     for (int j = 0; j < g.k; ++j) g.q[j] = st->perm[g.q[j]];
-  tc.plan = qs::plan_tiles(phys, bits, low, qs::kTileRowBits, 4, forms);
+  tc.plan = qs::plan_tiles(phys, st->n, low, qs::kTileRowBits, 4, forms);
   std::vector<unsigned char> host;
   qs::TileOffsets at;
   qs::tile_tables(tc.plan, prec == 0, &host, &at);
@@ -1034,17 +1120,6 @@ int run_tiles(qs_state* st, qs_circuit* c) {
   if (int rc = tile_plan_for(st, c, &tc)) return rc;
   const char* base = static_cast<const char*>(tc->dev);
   const double bytes = 2.0 * std::ldexp(1.0, st->n) * ab(st);
-  if (runs_whole(st, c)) {  // one step with every round
-    ProfScope ps(st, "circuit_lds", bytes);
-    const void* num = base + tc->at.reals;
-    const int nr = int(tc->plan.rounds.size());
-    const hipError_t e =
-        st->dtype == QS_C64 ? qs::launch_whole(static_cast<float*>(st->amps), st->n, base, nr,
-                                               static_cast<const float*>(num), st->stream)
-                            : qs::launch_whole(static_cast<double*>(st->amps), st->n, base, nr,
-                                               static_cast<const double*>(num), st->stream);
-    return device_error(st, e, "circuit in LDS");
-  }
   for (const auto& stp : tc->plan.steps) {
     hipError_t e;
     if (stp.block) {
@@ -1324,9 +1399,15 @@ int qs_run(qs_state* st, qs_circuit* c) {
     if (int rc = fact_rc(st, qs::fact_end_run(f, apply_all_or_prefix()))) return rc;
     return fact_rc(st, qs::fact_relabel(f, c->pos.data()));
   }
-  if (c->tiles != 0 && !c->gates.empty() &&
-      (runs_whole(st, c) || st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits)) {
-    if (int rc = run_tiles(st, c)) return rc;
+  const bool tiles = c->tiles != 0 && !c->gates.empty();
+  const qs_circuit::WholeForm form = tiles ? whole_form(st, c) : qs_circuit::kBlocks;
+  if (form != qs_circuit::kBlocks ||
+      (tiles && st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits)) {
+    if (form != qs_circuit::kBlocks) {
+      if (int rc = run_whole(st, c, form)) return rc;
+    } else if (int rc = run_tiles(st, c)) {
+      return rc;
+    }
     int np[64];
     for (int q = 0; q < st->n; ++q) np[q] = st->perm[c->pos[q]];
     for (int q = 0; q < st->n; ++q) st->perm[q] = np[q];

@@ -455,6 +455,56 @@ void pair_rounds(TilePlan* plan, const std::vector<Gate>& gates, const std::vect
 
 }  // namespace
 
+double merged_gates(const std::vector<Gate>& gates, int n) {
+  std::vector<int> last(n, -1);
+  std::vector<char> one(n, 0);
+  int count = 0;
+  double singles = 0;
+  for (const Gate& g : gates) {
+    if (g.k == 1) {
+      one[g.q[0]] = 1;
+      continue;
+    }
+    if (last[g.q[0]] >= 0 && last[g.q[0]] == last[g.q[1]]) continue;
+    last[g.q[0]] = last[g.q[1]] = count++;
+  }
+  for (int q = 0; q < n; ++q) singles += one[q] && last[q] < 0;
+  return count + singles / 2;
+}
+
+void block_widths(const std::vector<Gate>& gates, int n, int kmax, int count[QS_MAX_FUSED + 1]) {
+  std::vector<uint64_t> owner(n, 0);  // per qubit: the qubits of its open block
+  std::fill(count, count + QS_MAX_FUSED + 1, 0);
+  auto close = [&](uint64_t b) {
+    ++count[__builtin_popcountll(b)];
+    for (; b; b &= b - 1) owner[__builtin_ctzll(b)] = 0;
+  };
+  for (const Gate& g : gates) {
+    uint64_t mine = 0, all = 0;
+    for (int j = 0; j < g.k; ++j) {
+      mine |= uint64_t(1) << g.q[j];
+      all |= owner[g.q[j]];
+    }
+    all |= mine;
+    if (__builtin_popcountll(all) > kmax) {
+      for (int j = 0; j < g.k; ++j)
+        if (owner[g.q[j]]) close(owner[g.q[j]]);
+      all = mine;
+    }
+    for (uint64_t b = all; b; b &= b - 1) owner[__builtin_ctzll(b)] = all;
+  }
+  for (int q = 0; q < n; ++q)
+    if (owner[q]) close(owner[q]);
+}
+
+Block whole_block(const std::vector<Gate>& gates, int n) {
+  const std::vector<Gate> merged = merge_gates(gates, n);
+  Open o;
+  for (int q = 0; q < n; ++q) o.qubits.push_back(q);
+  for (size_t i = 0; i < merged.size(); ++i) o.gates.push_back(int(i));
+  return build_block(o, merged);
+}
+
 namespace {
 
 // What the rounds of a pass cost, in us per round (and gate of a sparse one):

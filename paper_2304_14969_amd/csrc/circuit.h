@@ -108,6 +108,13 @@ TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, 
 
 // Whether every gate has one or two qubits.
 bool narrow_gates(const std::vector<Gate>& gates);
+// Of a list of such gates: how many are left when merged as plan_tiles does
+// (one-qubit gates that stay count half), and how many blocks of each width
+// fuse() makes of them. Both without any matrix.
+double merged_gates(const std::vector<Gate>& gates, int n);
+void block_widths(const std::vector<Gate>& gates, int n, int kmax, int count[QS_MAX_FUSED + 1]);
+// The product of all gates as one block on qubits 0 .. n - 1 (n <= QS_MAX_FUSED).
+Block whole_block(const std::vector<Gate>& gates, int n);
 
 // The device tables of a plan, as one byte image: per round an int4 {bits
 // packed by byte, first gate (sparse) or operand offset in floats (dense),
@@ -165,6 +172,16 @@ struct qs_circuit {
     void* dev = nullptr;   // rounds, gates, matrices (owned)
     qs::TileOffsets at;
   } tcache[2];
+  // runs on states below a tile: how (decided once per precision and block
+  // width) and the tables, on virtual positions, whatever the state's labels
+  enum WholeForm { kUndecided, kBlocks, kRounds, kMatrix };
+  struct WholeCache {
+    WholeForm form = kUndecided;
+    int kmax = 0;          // block width the decision was made for
+    void* dev = nullptr;   // rounds and their numbers, or the matrix (owned)
+    int nrounds = 0;
+    size_t num = 0;        // byte offset of the rounds' numbers
+  } whole[2];
   // host plan for batched runs (identity labelling), and what its passes cost
   // in pair and in dense rounds once that was asked for; cleared with the other
   // plans when the circuit changes

@@ -292,14 +292,25 @@ hipError_t launch_apply_small(R* a, int n, const int* qubits, int k, const doubl
 }
 
 template <typename R>
+hipError_t launch_small_block(R* a, int n, const int* qubits, int k, const R* mat, hipStream_t s) {
+  if (n > 11 || k > n) return hipErrorInvalidValue;
+  const Block6 b = make_block(qubits, k, false);
+  switch (k) {
+    case 1: return launch_small_state<R, 1>(a, n, b, mat, s);
+    case 2: return launch_small_state<R, 2>(a, n, b, mat, s);
+    case 3: return launch_small_state<R, 3>(a, n, b, mat, s);
+    case 4: return launch_small_state<R, 4>(a, n, b, mat, s);
+    case 5: return launch_small_state<R, 5>(a, n, b, mat, s);
+    case 6: return launch_small_state<R, 6>(a, n, b, mat, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename R>
 hipError_t launch_apply_fused(R* a, int n, const int* qubits, int k, const R* mat,
                               hipStream_t s) {
+  if (k >= 4 && n <= 11) return launch_small_block(a, n, qubits, k, mat, s);
   const Block6 b = make_block(qubits, k, sizeof(R) == 4);
-  if (k >= 4 && n <= 11) switch (k) {
-      case 4: return launch_small_state<R, 4>(a, n, b, mat, s);
-      case 5: return launch_small_state<R, 5>(a, n, b, mat, s);
-      case 6: return launch_small_state<R, 6>(a, n, b, mat, s);
-    }
   switch (k) {
     case 1: return launch_k<R, 1>(a, n, b, mat, s);
     case 2: return launch_k<R, 2>(a, n, b, mat, s);
@@ -311,6 +322,10 @@ hipError_t launch_apply_fused(R* a, int n, const int* qubits, int k, const R* ma
   }
 }
 
+template hipError_t launch_small_block<float>(float*, int, const int*, int, const float*,
+                                              hipStream_t);
+template hipError_t launch_small_block<double>(double*, int, const int*, int, const double*,
+                                               hipStream_t);
 template hipError_t launch_apply_fused<float>(float*, int, const int*, int, const float*,
                                               hipStream_t);
 template hipError_t launch_apply_small<float>(float*, int, const int*, int, const double*,

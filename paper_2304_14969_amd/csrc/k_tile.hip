@@ -548,10 +548,26 @@ __device__ __forceinline__ void quad_gate(const float4 (&u)[2], int b0, int b1, 
   __syncthreads();
 }
 
+// Bit q of a circuit's positions is bit (bits >> 4 q) & 15 of the state's index,
+// and bit 0 of the latter is bit `first` of the former. (Packed: an array would
+// be read bit by bit through the scalar cache.)
+struct WholePerm {
+  uint64_t bits;
+  int first;
+};
+// The tile index of a state's index i.
+template <int TB>
+__device__ __forceinline__ int whole_pos(int i, const WholePerm& perm) {
+  int x = 0;
+#pragma unroll
+  for (int q = 0; q < TB; ++q) x |= ((i >> int((perm.bits >> (4 * q)) & 15)) & 1) << q;
+  return x;
+}
+
 template <int TB>
 __global__ void __launch_bounds__(1 << (TB - 2))
-    k_whole_pair(float* __restrict__ a, int n, const int4* __restrict__ rounds, int nrounds,
-                 const float* __restrict__ mats) {
+    k_whole_pair(float* __restrict__ a, int n, WholePerm perm, const int4* __restrict__ rounds,
+                 int nrounds, const float* __restrict__ mats) {
   constexpr int NT = 1 << (TB - 2), NV = (1 << TB) / 2 / NT;
   extern __shared__ unsigned char smraw[];
   float* re = reinterpret_cast<float*>(smraw);
@@ -559,14 +575,18 @@ __global__ void __launch_bounds__(1 << (TB - 2))
   float4* p4 = reinterpret_cast<float4*>(a);
   const int vecs = 1 << (n - 1);
   PairRounds rr(rounds, nrounds, mats);
+  int at[NV][2];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    const int e = threadIdx.x + k * NT, l = plane_pos(2 * e);
+    const int e = threadIdx.x + k * NT;
     const float4 b = e < vecs ? p4[e] : make_float4(0.f, 0.f, 0.f, 0.f);
-    re[l] = b.x;
-    im[l] = b.y;
-    re[l + 1] = b.z;
-    im[l + 1] = b.w;
+    const int x = whole_pos<TB>(2 * e, perm);
+    at[k][0] = plane_pos(x);
+    at[k][1] = plane_pos(x | (1 << perm.first));
+    re[at[k][0]] = b.x;
+    im[at[k][0]] = b.y;
+    re[at[k][1]] = b.z;
+    im[at[k][1]] = b.w;
   }
   __syncthreads();
   rr.run([re, im](const PairRounds::Round& rd) {
@@ -575,8 +595,8 @@ __global__ void __launch_bounds__(1 << (TB - 2))
   });
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    const int e = threadIdx.x + k * NT, l = plane_pos(2 * e);
-    if (e < vecs) p4[e] = make_float4(re[l], im[l], re[l + 1], im[l + 1]);
+    const int e = threadIdx.x + k * NT, l = at[k][0], m = at[k][1];
+    if (e < vecs) p4[e] = make_float4(re[l], im[l], re[m], im[m]);
   }
 }
 
@@ -599,18 +619,20 @@ __device__ __forceinline__ void quad_gate_f64(Cx<double>* sm, int b0, int b1,
 
 template <int TB>
 __global__ void __launch_bounds__(1 << (TB - 2))
-    k_whole_pair(double* __restrict__ a, int n, const int4* __restrict__ rounds, int nrounds,
-                 const double* __restrict__ num) {
+    k_whole_pair(double* __restrict__ a, int n, WholePerm perm, const int4* __restrict__ rounds,
+                 int nrounds, const double* __restrict__ num) {
   constexpr int NT = 1 << (TB - 2), NV = (1 << TB) / NT;
   extern __shared__ unsigned char smraw[];
   Cx<double>* sm = reinterpret_cast<Cx<double>*>(smraw);
   double2* p2 = reinterpret_cast<double2*>(a);
   const int amps = 1 << n;
+  int at[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT;
     const double2 b = e < amps ? p2[e] : make_double2(0.0, 0.0);
-    sm[wide_pos(e)] = {b.x, b.y};
+    at[k] = wide_pos(whole_pos<TB>(e, perm));
+    sm[at[k]] = {b.x, b.y};
   }
   __syncthreads();
   int4 e = rounds[0];
@@ -624,7 +646,7 @@ __global__ void __launch_bounds__(1 << (TB - 2))
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int e = threadIdx.x + k * NT;
-    if (e < amps) p2[e] = make_double2(sm[wide_pos(e)].r, sm[wide_pos(e)].i);
+    if (e < amps) p2[e] = make_double2(sm[at[k]].r, sm[at[k]].i);
   }
 }
 
@@ -889,26 +911,33 @@ hipError_t launch_tile_mfma(float* a, int n, int low_bits, const TileRows& rows,
 
 namespace {
 template <typename R, int TB>
-hipError_t launch_whole_tb(R* a, int n, const void* rounds, int nrounds, const R* num,
-                           hipStream_t s) {
-  void (*kern)(R*, int, const int4*, int, const R*) = k_whole_pair<TB>;
-  hipLaunchKernelGGL(kern, dim3(1), dim3(1 << (TB - 2)), (pair_lds<R, TB>()), s, a, n,
+hipError_t launch_whole_tb(R* a, int n, const WholePerm& perm, const void* rounds, int nrounds,
+                           const R* num, hipStream_t s) {
+  void (*kern)(R*, int, WholePerm, const int4*, int, const R*) = k_whole_pair<TB>;
+  hipLaunchKernelGGL(kern, dim3(1), dim3(1 << (TB - 2)), (pair_lds<R, TB>()), s, a, n, perm,
                      static_cast<const int4*>(rounds), nrounds, num);
   return hipGetLastError();
 }
 }  // namespace
 
 template <typename R>
-hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const R* num,
+hipError_t launch_whole(R* a, int n, const int* perm, const void* rounds, int nrounds, const R* num,
                         hipStream_t s) {
-  if (n < 1 || nrounds < 1) return hipErrorInvalidValue;
-  if (whole_bits(n) == 10) return launch_whole_tb<R, 10>(a, n, rounds, nrounds, num, s);
+  if (n < 1 || n > 11 || nrounds < 1) return hipErrorInvalidValue;
+  WholePerm w{};
+  for (int q = 0; q < 11; ++q) {  // (bits from n on keep their place)
+    const int p = q < n ? perm[q] : q;
+    w.bits |= uint64_t(p) << (4 * q);
+    if (p == 0) w.first = q;
+  }
+  if (whole_bits(n) == 10) return launch_whole_tb<R, 10>(a, n, w, rounds, nrounds, num, s);
   if constexpr (sizeof(R) == 4)
-    if (whole_bits(n) == 11) return launch_whole_tb<R, 11>(a, n, rounds, nrounds, num, s);
+    if (whole_bits(n) == 11) return launch_whole_tb<R, 11>(a, n, w, rounds, nrounds, num, s);
   return hipErrorInvalidValue;
 }
-template hipError_t launch_whole<float>(float*, int, const void*, int, const float*, hipStream_t);
-template hipError_t launch_whole<double>(double*, int, const void*, int, const double*,
+template hipError_t launch_whole<float>(float*, int, const int*, const void*, int, const float*,
+                                        hipStream_t);
+template hipError_t launch_whole<double>(double*, int, const int*, const void*, int, const double*,
                                          hipStream_t);
 
 // complex64 (dtype 1): rows of 2^g_tile_low_c64 amplitudes (4: 128 bytes, 5:

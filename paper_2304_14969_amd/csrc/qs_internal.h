@@ -163,6 +163,10 @@ hipError_t launch_bit_pairs(R* amps, int n, const int* image, hipStream_t s);
 template <typename R>
 hipError_t launch_apply_fused(R* amps, int n, const int* qubits, int k, const R* mat,
                               hipStream_t s);
+// The same on a state of at most 11 qubits, in the LDS of one workgroup.
+template <typename R>
+hipError_t launch_small_block(R* amps, int n, const int* qubits, int k, const R* mat,
+                              hipStream_t s);
 // The same for k <= 3 with the host matrix (FP64, interleaved, row-major)
 // cast to R and passed in the kernel arguments: no device copy of it.
 template <typename R>
@@ -386,10 +390,11 @@ hipError_t launch_tile_pair(R* a, int n, int low_bits, const TileRows& rows, con
                             int nrounds, const R* num, hipStream_t s);
 // A state of n <= 11 (complex64) or 10 (complex128) qubits and every round of
 // a circuit of one- and two-qubit gates in one launch of one workgroup; tables
-// of a one-pass plan of pair rounds on whole_bits(n) bits.
+// of a one-pass plan of pair rounds on whole_bits(n) bits; bit q of the plan is
+// bit perm[q] of the state.
 inline int whole_bits(int n) { return n < 10 ? 10 : n; }
 template <typename R>
-hipError_t launch_whole(R* a, int n, const void* rounds, int nrounds, const R* num,
+hipError_t launch_whole(R* a, int n, const int* perm, const void* rounds, int nrounds, const R* num,
                         hipStream_t s);
 // Batched tile passes: one item = one pass of one ket of an arena; items sorted
 // by first_tile, the tiles of item i are [first_tile_i, first_tile_{i+1}); its
