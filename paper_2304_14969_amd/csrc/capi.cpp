@@ -1404,6 +1404,7 @@ int qs_run(qs_state* st, qs_circuit* c) {
   if (form != qs_circuit::kBlocks ||
       (tiles && st->n >= qs::tile_low_bits(st->dtype) + qs::kTileRowBits)) {
     if (form != qs_circuit::kBlocks) {
+      qs::circuit_plan_blocks_later(c, c->kmax);  // answers for its blocks as if run in them
       if (int rc = run_whole(st, c, form)) return rc;
     } else if (int rc = run_tiles(st, c)) {
       return rc;

@@ -83,3 +83,21 @@ def test_every_labelling_uses_the_same_tables(qs_lib, dtype, n):
             a = dense.run_circuit(a, n, gates)
         assert_parity(st.amplitudes(), a, dtype, f"n={n}")
     c.free()
+
+
+@pytest.mark.parametrize("dtype", [C64, C128])
+def test_blocks_are_known_after_a_run(qs_lib, dtype):
+    """A run on a state below a tile leaves the circuit planned in blocks."""
+    n = 8
+    gates = workloads.random_circuit(n, 4, 3)
+    c, ref = qs_lib.Circuit(n).add_gates(gates), qs_lib.Circuit(n).add_gates(gates).plan(5)
+    assert c.info()["blocks"] == -1
+    with qs_lib.State(n, dtype) as st:
+        st.run(c)
+        assert c.info() == ref.info()
+        assert c.block(0)[0] == ref.block(0)[0]
+        st.run(c)
+        want = dense.run_circuit(dense.zero_state(n), n, gates + gates)
+        assert_parity(st.amplitudes(), want, dtype)
+    c.free()
+    ref.free()
