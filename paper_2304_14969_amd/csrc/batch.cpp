@@ -11,6 +11,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <vector>
 
 #include "circuit.h"
@@ -98,10 +99,45 @@ void drop_run(qs_batch* b) {
   b->built_from.clear();
 }
 
+// Kets that can only take pair rounds (those below a tile, all in complex128)
+// are better off as blocks where many gates stay on few qubits: 200 gates on
+// four qubits of 4 to 11, 200 kets: one block 18 us, 160 rounds 130 (complex128
+// 18 and 235). A batch waits for its longest ket in every launch, and those of
+// passes and of blocks run one after the other, so that kets move from passes to
+// blocks together or not at all. Estimates in us: a pass lasts as long as its
+// longest ket (a round of one gate, of two) or as its tiles' rounds on a full
+// chip, a launch of blocks as long as its amplitudes take.
+struct BatchTime {
+  bool c64;
+  std::vector<double> longest, sum;  // per pass: rounds of its longest ket; of all tiles
+  std::map<std::pair<size_t, int>, double> amps;  // per block index and width
+  void add_passes(const qs::TilePlan& pl, uint64_t tiles) {
+    for (size_t p = 0; p < pl.steps.size(); ++p) {
+      double t = 0;
+      for (int r = pl.steps[p].r0; r < pl.steps[p].r0 + pl.steps[p].nr; ++r)
+        t += pl.rounds[size_t(r)].ng > 1 ? 1.4 : 1.0;
+      if (p >= longest.size()) longest.push_back(0), sum.push_back(0);
+      longest[p] = std::max(longest[p], t);
+      sum[p] += t * double(tiles);
+    }
+  }
+  void add_blocks(const std::vector<int>& widths, int n) {
+    for (size_t i = 0; i < widths.size(); ++i)
+      amps[{i, widths[i]}] += std::ldexp(1.0, n + widths[i] - 4);
+  }
+  double us() const {
+    double t = 0;
+    for (size_t p = 0; p < longest.size(); ++p)
+      t += 2.4 + std::max(longest[p] * (c64 ? 0.8 : 1.25), sum[p] * (c64 ? 1.6e-3 : 2.8e-3));
+    for (const auto& a : amps) t += std::max(a.first.second < 5 ? 6.0 : 20.0, a.second * 1.6e-5);
+    return t;
+  }
+};
+
 // Tile passes for the kets that take them: one launch per pass index and kind
 // of rounds over every ket that has that pass. Fills use_tile; false if
 // nothing to do.
-int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_tile) {
+int prepare_tiles(qs_batch* b, qs_circuit* const* circs, int kmax, std::vector<char>* use_tile) {
   use_tile->assign(b->count, 0);
   if (!b->tiles) return QS_OK;
   const bool c64 = b->dtype == QS_C64;
@@ -156,8 +192,29 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, std::vector<char>* use_
     for (const auto& st : plans[i]->steps) ok = ok && !st.block;
     if (!ok) continue;
     (*use_tile)[i] = 1;
-    maxp = std::max(maxp, plans[i]->steps.size());
   }
+  BatchTime passes{c64}, both{c64};
+  std::vector<int> moved;
+  for (int i = 0; i < b->count; ++i) {
+    if (!(*use_tile)[i]) continue;
+    const uint64_t tiles = uint64_t(1) << std::max(0, b->n[i] - C - H);
+    passes.add_passes(*plans[i], tiles);
+    double rounds = 0;  // a block is a launch, worth about 8 rounds
+    for (const auto& r : plans[i]->rounds) rounds += r.mode != qs::TileMode::kPairs ? 0 : r.ng > 1 ? 1.4 : 1.0;
+    if (rounds > 8 && (!c64 || b->n[i] < C + H)) {
+      const std::vector<int> widths = qs::block_widths(circs[i]->gates, b->n[i], kmax);
+      if (8.0 * double(widths.size()) < rounds) {
+        moved.push_back(i);
+        both.add_blocks(widths, b->n[i]);
+        continue;
+      }
+    }
+    both.add_passes(*plans[i], tiles);
+  }
+  if (!moved.empty() && both.us() < 0.8 * passes.us())
+    for (int i : moved) (*use_tile)[i] = 0;
+  for (int i = 0; i < b->count; ++i)
+    if ((*use_tile)[i]) maxp = std::max(maxp, plans[i]->steps.size());
   if (!maxp) return QS_OK;
   // rounds of every ket, in ket order; round_base[i] = first round of ket i
   std::vector<int32_t> rtab;
@@ -252,7 +309,7 @@ int prepare(qs_batch* b, qs_circuit* const* circs, int kmax) {
   }
   drop_run(b);
   std::vector<char> use_tile;
-  if (int rc = prepare_tiles(b, circs, &use_tile)) {
+  if (int rc = prepare_tiles(b, circs, kmax, &use_tile)) {
     drop_run(b);
     return rc;
   }

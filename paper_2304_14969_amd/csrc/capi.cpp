@@ -1003,12 +1003,11 @@ qs_circuit::WholeForm whole_form(const qs_state* st, qs_circuit* c) {
     if (st->n <= 5) {
       if (rounds > 3.4) form = qs_circuit::kMatrix;
     } else {
-      int count[QS_MAX_FUSED + 1];
-      qs::block_widths(c->gates, c->n, c->kmax, count);
       const double k5 = st->n < 9 ? 2.8 : c64 ? (st->n == 9 ? 3.0 : st->n == 10 ? 3.7 : 5.3)
                                               : (st->n == 9 ? 3.4 : 4.4);
-      double blocks = 1.6 * k5 * count[6] + k5 * count[5];
-      for (int k = 1; k <= 4; ++k) blocks += 2.8 * count[k];
+      double blocks = 0;
+      for (int k : qs::block_widths(c->gates, c->n, c->kmax))
+        blocks += k < 5 ? 2.8 : k == 5 ? k5 : 1.6 * k5;
       if (blocks < 0.8 * rounds) form = qs_circuit::kBlocks;
     }
   }

@@ -472,11 +472,11 @@ double merged_gates(const std::vector<Gate>& gates, int n) {
   return count + singles / 2;
 }
 
-void block_widths(const std::vector<Gate>& gates, int n, int kmax, int count[QS_MAX_FUSED + 1]) {
+std::vector<int> block_widths(const std::vector<Gate>& gates, int n, int kmax) {
+  std::vector<int> out;
   std::vector<uint64_t> owner(n, 0);  // per qubit: the qubits of its open block
-  std::fill(count, count + QS_MAX_FUSED + 1, 0);
   auto close = [&](uint64_t b) {
-    ++count[__builtin_popcountll(b)];
+    out.push_back(__builtin_popcountll(b));
     for (; b; b &= b - 1) owner[__builtin_ctzll(b)] = 0;
   };
   for (const Gate& g : gates) {
@@ -495,6 +495,7 @@ void block_widths(const std::vector<Gate>& gates, int n, int kmax, int count[QS_
   }
   for (int q = 0; q < n; ++q)
     if (owner[q]) close(owner[q]);
+  return out;
 }
 
 Block whole_block(const std::vector<Gate>& gates, int n) {

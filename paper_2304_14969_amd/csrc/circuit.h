@@ -109,10 +109,11 @@ TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, 
 // Whether every gate has one or two qubits.
 bool narrow_gates(const std::vector<Gate>& gates);
 // Of a list of such gates: how many are left when merged as plan_tiles does
-// (one-qubit gates that stay count half), and how many blocks of each width
-// fuse() makes of them. Both without any matrix.
+// (one-qubit gates that stay count half). Without any matrix.
 double merged_gates(const std::vector<Gate>& gates, int n);
-void block_widths(const std::vector<Gate>& gates, int n, int kmax, int count[QS_MAX_FUSED + 1]);
+// The widths of the blocks that fuse() makes, about in their order. Without any
+// matrix.
+std::vector<int> block_widths(const std::vector<Gate>& gates, int n, int kmax);
 // The product of all gates as one block on qubits 0 .. n - 1 (n <= QS_MAX_FUSED).
 Block whole_block(const std::vector<Gate>& gates, int n);
 
