@@ -254,53 +254,75 @@ int phys_swap(qs_state* st, int pa, int pb) {
   return device_error(st, e, "bit swap");
 }
 
-// Moves amplitudes so that logical qubit q sits at physical bit q again: one
-// exchange for a single pair of bits; otherwise the moves physical bit ->
-// logical qubit as one in-place sweep if they are disjoint pairs (a
-// transform's bit reversal), else as two such sweeps (a cycle p_0 -> p_1 -> ...
-// is the exchange of p_i and p_-i followed by that of p_i and p_1-i).
+// Moves amplitudes so that logical qubit q sits at physical bit q again: the
+// moves physical bit -> logical qubit by exchanges of two bits, a sweep each,
+// or as one in-place sweep if they are disjoint pairs (a transform's bit
+// reversal), else as two such sweeps (a cycle p_0 -> p_1 -> ... is the exchange
+// of p_i and p_-i followed by that of p_i and p_1-i). An exchange moves half of
+// the state, so that few of them beat the sweeps: three bits in a cycle at the
+// top of 24 qubits complex64 47 us by exchanges and 73 by sweeps, 94 and 131 in
+// complex128, with two of them below bit 4 108 and 86; two pairs at the top of
+// 20 qubits complex128 18 and 24; states of 13 to 19 qubits wait for launches and
+// the latency of an exchange within a tile (14 qubits complex128, two cycles of
+// three: 21 and 27).
 int materialize(qs_state* st) {
-  int to[64], moved = 0;
-  for (int q = 0; q < st->n; ++q) {
+  const int n = st->n;
+  int to[64], moved = 0, low = 0, lowest = 64;
+  for (int q = 0; q < n; ++q) {
     to[st->perm[q]] = q;
-    moved += st->perm[q] != q;
+    if (st->perm[q] == q) continue;
+    ++moved;
+    low += q < 4;
+    lowest = std::min(lowest, q);
   }
   if (!moved) return QS_OK;
-  if (moved == 2) {
-    for (int q = 0; q < st->n; ++q)
-      if (to[q] > q)
-        if (int rc = phys_swap(st, q, to[q])) return rc;
-  } else {
-    int step[2][64];
-    bool used[2] = {false, false};
-    for (int q = 0; q < st->n; ++q) step[0][q] = step[1][q] = q;
-    uint64_t seen = 0;
-    for (int q = 0; q < st->n; ++q) {
-      int cyc[64], k = 0;
-      for (int p = q; !((seen >> p) & 1); p = to[p]) {
-        seen |= uint64_t(1) << p;
-        cyc[k++] = p;
-      }
-      if (k < 2) continue;
-      // two bits: one exchange (in the first sweep)
-      for (int i = 0; i < k; ++i) {
-        step[0][cyc[i]] = k == 2 ? cyc[1 - i] : cyc[(k - i) % k];
-        if (k > 2) step[1][cyc[i]] = cyc[(k + 1 - i) % k];
-      }
-      used[0] = true;
-      used[1] = used[1] || k > 2;
+  int step[2][64], exchanges = 0;
+  bool used[2] = {false, false};
+  for (int q = 0; q < n; ++q) step[0][q] = step[1][q] = q;
+  uint64_t seen = 0;
+  for (int q = 0; q < n; ++q) {
+    int cyc[64], k = 0;
+    for (int p = q; !((seen >> p) & 1); p = to[p]) {
+      seen |= uint64_t(1) << p;
+      cyc[k++] = p;
     }
-    for (int i = 0; i < 2; ++i) {
-      if (!used[i]) continue;
-      ProfScope ps(st, "bitswap", 2.0 * std::ldexp(1.0, st->n) * ab(st));
-      const hipError_t e =
-          st->dtype == QS_C64
-              ? qs::launch_bit_pairs(static_cast<float*>(st->amps), st->n, step[i], st->stream)
-              : qs::launch_bit_pairs(static_cast<double*>(st->amps), st->n, step[i], st->stream);
-      if (int rc = device_error(st, e, "bit exchange")) return rc;
+    if (k < 2) continue;
+    exchanges += k - 1;
+    // two bits: one exchange (in the first sweep)
+    for (int i = 0; i < k; ++i) {
+      step[0][cyc[i]] = k == 2 ? cyc[1 - i] : cyc[(k - i) % k];
+      if (k > 2) step[1][cyc[i]] = cyc[(k + 1 - i) % k];
     }
+    used[0] = true;
+    used[1] = used[1] || k > 2;
   }
-  for (int q = 0; q < st->n; ++q) st->perm[q] = q;
+  bool single = exchanges == 1;
+  if (exchanges == 2 && !used[1]) single = lowest >= 6 && n < 22;
+  if (exchanges == 2 && used[1]) single = low < 2 || n < (st->dtype == QS_C64 ? 20 : 23);
+  if (exchanges > 2 && used[1]) single = exchanges <= 4 && n > 12 && n < 20;
+  if (single) {
+    for (int q = 0; q < n; ++q) {
+      if (st->perm[q] == q) continue;
+      int q2 = -1;  // logical qubit currently at physical bit q
+      for (int k = 0; k < n; ++k)
+        if (st->perm[k] == q) q2 = k;
+      const int p = st->perm[q];
+      if (int rc = phys_swap(st, p, q)) return rc;
+      st->perm[q] = q;
+      st->perm[q2] = p;
+    }
+    return QS_OK;
+  }
+  for (int i = 0; i < 2; ++i) {
+    if (!used[i]) continue;
+    ProfScope ps(st, "bitswap", 2.0 * std::ldexp(1.0, n) * ab(st));
+    const hipError_t e =
+        st->dtype == QS_C64
+            ? qs::launch_bit_pairs(static_cast<float*>(st->amps), n, step[i], st->stream)
+            : qs::launch_bit_pairs(static_cast<double*>(st->amps), n, step[i], st->stream);
+    if (int rc = device_error(st, e, "bit exchange")) return rc;
+  }
+  for (int q = 0; q < n; ++q) st->perm[q] = q;
   return QS_OK;
 }
 
