@@ -262,7 +262,7 @@ int phys_swap(qs_state* st, int pa, int pb) {
 // the state, so that few of them beat the sweeps: three bits in a cycle at the
 // top of 24 qubits complex64 47 us by exchanges and 73 by sweeps, 94 and 131 in
 // complex128, with two of them below bit 4 108 and 86; two pairs at the top of
-// 20 qubits complex128 18 and 24; states of 13 to 19 qubits wait for launches and
+// 20 qubits complex128 18 and 24; states of 10 to 19 qubits wait for launches and
 // the latency of an exchange within a tile (14 qubits complex128, two cycles of
 // three: 21 and 27).
 int materialize(qs_state* st) {
@@ -299,7 +299,7 @@ int materialize(qs_state* st) {
   bool single = exchanges == 1;
   if (exchanges == 2 && !used[1]) single = lowest >= 6 && n < 22;
   if (exchanges == 2 && used[1]) single = low < 2 || n < (st->dtype == QS_C64 ? 20 : 23);
-  if (exchanges > 2 && used[1]) single = exchanges <= 4 && n > 12 && n < 20;
+  if (exchanges > 2 && used[1]) single = exchanges <= 4 && n > (exchanges < 4 ? 9 : 12) && n < 20;
   if (single) {
     for (int q = 0; q < n; ++q) {
       if (st->perm[q] == q) continue;
