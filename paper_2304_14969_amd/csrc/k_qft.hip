@@ -479,8 +479,8 @@ hipError_t launch_col_cfg(R* a, int n, int start, int len, int lo, int sign, R s
   if (lo < C || n < lo + G) return hipErrorInvalidValue;
   constexpr int NT =
       tile_threads(G + C, (1 << (G + C)) / Vec16<R>::AMPS, round_width(G, WMAX), CAP);
-  const size_t bytes =
-      ((size_t(1) << (G + C)) + (col_pad<R>(C) ? size_t(1) << (G + C - 4) : 0)) * 2 * sizeof(R);
+  constexpr size_t tile = size_t(1) << (G + C);
+  const size_t bytes = (tile + (col_pad<R>(C) ? tile >> 4 : 0)) * 2 * sizeof(R);
   auto kern = k_qft_col<R, G, C, REV, NT, WMAX>;
   allow_lds(kern, bytes);
   const unsigned grid = static_cast<unsigned>(uint64_t(1) << (n - G - C));
