@@ -891,15 +891,16 @@ int qft_passes(qs_state* st, void* amps, int nq, int start, int len, bool revers
                      : qs::qft_plan<double>(nq, start, len, reversed, g_qft_tune, plan, 64);
   if (np < 0) return fail(QS_E_UNSUPPORTED, "QFT pass plan failed");
   const int sign = inverse ? -1 : 1;
-  static const char* kind_names[3][9] = {
+  constexpr int kWidths = 10;
+  static const char* const kind_names[3][kWidths] = {
       {"qft_lds", "qft_lds", "qft_lds", "qft_lds", "qft_lds", "qft_lds", "qft_lds", "qft_lds",
-       "qft_lds"},
+       "qft_lds", "qft_lds"},
       {"", "qft_col1", "qft_col2", "qft_col3", "qft_col4", "qft_col5", "qft_col6", "qft_col7",
-       "qft_col8"},
-      {"", "qft_reg1", "qft_reg2", "qft_reg3", "qft_reg4", "qft_reg5", "", "", ""}};
+       "qft_col8", "qft_col9"},
+      {"", "qft_reg1", "qft_reg2", "qft_reg3", "qft_reg4", "qft_reg5", "", "", "", ""}};
   for (int k = 0; k < np; ++k) {
     const int g = plan[k].kind == qs::QftPass::LDS ? 0 : plan[k].hi - plan[k].lo;
-    ProfScope ps(st, kind_names[plan[k].kind][g <= 8 ? g : 0],
+    ProfScope ps(st, kind_names[plan[k].kind][g < kWidths ? g : 0],
                  2.0 * std::ldexp(1.0, nq) * ab(st));
     hipError_t e =
         st->dtype == QS_C64
