@@ -515,10 +515,18 @@ int qs_check(qs_state* st, double tol);
  *   "qft.lds_bits"   bits of the contiguous LDS tile of the QFT's low pass:
  *                    1 to 13 for complex64 / 12 for complex128 (larger
  *                    values are clamped to that); 0 (default): 12, or 11
- *                    for complex64 states above 256 MiB, 9 for those up to
- *                    22 qubits, and 9 to 11 for complex128 ones up to 25,
- *                    each when that adds no pass; 13 for complex64 states up
- *                    to 22 qubits where that saves one;
+ *                    for states above 256 MiB (complex64: when that adds no
+ *                    pass).
+ *                    While this knob, qft.high_pass, col_max, col_rows,
+ *                    threads and round_bits are all at their defaults, small
+ *                    states have plans of their own: complex64 ones up to 22
+ *                    qubits take 9 bits, complex128 ones up to 25 take 9 to
+ *                    11, each when that adds no pass; complex64 ones up to 22
+ *                    take 13 bits and strided passes of up to 9 (128-byte
+ *                    rows) where that saves a pass; strided passes have rows
+ *                    of 256 down to 64 bytes where wider ones would leave
+ *                    CUs without a workgroup; and contiguous tiles of 12 and
+ *                    13 bits take 512 threads where there are at most 256;
  *   "qft.stream"     global accesses of the LDS tile passes: 0 (default)
  *                    streaming (non-temporal) for states above 256 MiB, plain
  *                    below (such states partly stay in the last-level
@@ -543,18 +551,16 @@ int qs_check(qs_state* st, double tol);
  *   "qft.high_pass"  passes above that tile: 0 = strided LDS tiles, 1 =
  *                    register passes of up to 5 bits;
  *   "qft.col_max"    most bits of one strided LDS pass: 8 (default; 256-byte
- *                    rows; with qft.lds_bits 0 also 9 for complex64 states
- *                    up to 22 qubits where that saves a pass) or 7 (512-byte
- *                    rows), all 64 KiB tiles; a 7-bit
- *                    complex64 pass always has 512-byte rows unless
- *                    qft.col_rows = 1 (complex128 ones have 256-byte rows);
+ *                    rows) or 7 (512-byte rows), both 64 KiB tiles; a 7-bit
+ *                    complex64 pass has 512-byte rows unless qft.col_rows = 1
+ *                    (complex128 ones have 256-byte rows);
  *   "qft.col_rows"   1: strided passes of 7 bits use 256-byte rows (32 KiB
  *                    tiles); 2: also complex64 passes of 8 bits use 128-byte
  *                    rows (32 KiB); 0 (default): 512-byte rows for 7 bits
  *                    (complex128: 256), 256-byte rows for 8;
  *   "qft.threads"    thread cap of the LDS tile launches: 256, 512, or 0
- *                    (default: 512 for strided passes of 8 bits, 256 for
- *                    the others);
+ *                    (default: 512 for strided passes of 8 and 9 bits, 256
+ *                    for the others);
  *   "qft.round_bits" widest in-register round inside an LDS tile: 4 (default)
  *                    or 5 (complex64 only);
  *   "tile.low_bits"  contiguous low bits of a complex64 tile: 5 (default,

@@ -502,6 +502,14 @@ hipError_t launch_lds_cfg(R* a, int n, int start, int len, int lo, int hi, int s
   return hipGetLastError();
 }
 
+// Whether every knob of the pass shapes is at its default: only then do small
+// states get plans of their own.
+bool default_shapes(const QftTuning& t) {
+  const QftTuning d;
+  return t.lds_bits == d.lds_bits && t.high_kind == d.high_kind && t.threads == d.threads &&
+         t.round_bits == d.round_bits && t.col_max == d.col_max && t.col_rows == d.col_rows;
+}
+
 // Launch configurations selectable by the tuning knobs: thread cap 256 or
 // 512, round width 4 or 5 (tiles of at least 2^11 entries / 2^5 rows); smaller
 // tiles always use cap 256 and rounds of 4.
@@ -545,7 +553,7 @@ hipError_t launch_col(R* a, int n, int start, int len, int lo, int sign, R scale
   if constexpr (G == 9)  // 128-byte rows
     return launch_col_cfg<R, G, CB - 2, REV, 512, 4>(a, n, start, len, lo, sign, scale,
                                                      stream_policy<R>(n, tune), s);
-  if (tune.col_rows == 0 && tune.threads == 0 && tune.round_bits == 4) {
+  if (default_shapes(tune)) {
     const int st = stream_policy<R>(n, tune);
     const int rows = small_col_bits<R>(n, G);
     if (rows == CB - 1)  // (8 bits: a 64 KiB tile per CU, 512 threads for its latency)
@@ -576,7 +584,8 @@ hipError_t launch_lds_t(R* a, int n, int start, int len, int lo, int hi, int sig
   // a large tile or less per CU: 512 threads (a transform and its inverse on
   // 21 qubits complex64, 66 -> 54.5 us; with two tiles per CU, 22 qubits, 91
   // against 84)
-  const int cap = tune.threads > 0 ? tune.threads : (T >= 12 && n - T <= 8 ? 512 : 256);
+  const int cap = tune.threads > 0 ? tune.threads
+                  : default_shapes(tune) && T >= 12 && n - T <= 8 ? 512 : 256;
   const int st = stream_policy<R>(n, tune);
   if (T < 11 || sizeof(R) == 8 || (cap < 512 && tune.round_bits < 5))
     return launch_lds_cfg<R, T, REV, 256, 4>(a, n, start, len, lo, hi, sign, scale, st, s);
@@ -687,7 +696,8 @@ int qft_plan(int n, int start, int len, bool rev, const QftTuning& tune, QftPass
   // 16 (23 qubits would be slower, 160 -> 190: two 7-bit strided
   // passes); complex128 25.8 -> 18.4 at 14, 44.3 -> 40.8 at 19, 101 -> 84 at 21,
   // 617 -> 568 at 24, 1307 -> 1203 at 25.
-  if (tune.lds_bits == 0 && !use_reg && n <= (sizeof(R) == 4 ? 22 : 25))
+  const bool own = default_shapes(tune);
+  if (own && n <= (sizeof(R) == 4 ? 22 : 25))
     for (int t = 9; t < 12; t += sizeof(R) == 4 ? 3 : 1)
       if (pass_count(t) <= pass_count(12)) {
         T = t;
@@ -695,10 +705,11 @@ int qft_plan(int n, int start, int len, bool rev, const QftTuning& tune, QftPass
       }
   // complex64 states that fit the L2s (32 MiB): 13-bit tiles and strided passes
   // of up to 9 bits where these leave a pass out: 68.7 -> 54.7 us at 21 qubits,
-  // 93-95 -> 84 at 22, bits 5 to 21 of 22 90 -> 69. Larger states lose by them
-  // (23 qubits 162 -> 200, 27 2410 -> 3610: two such tiles per CU leave the memory
-  // idle while they compute), complex128 ones gain nothing (21 qubits 82.7, 82.4).
-  if (tune.lds_bits == 0 && tune.col_max == 8 && !use_reg && sizeof(R) == 4 && n <= 22) {
+  // 93-95 -> 84 at 22, bits 5 to 21 of 22 90 -> 69. From 23 qubits on the count
+  // stays at three passes with them, and such passes are slower each (23 qubits
+  // 162 -> 200, 27 2410 -> 3610); complex128 states gain nothing (21 qubits 82.7,
+  // 82.4).
+  if (own && sizeof(R) == 4 && n <= 22) {
     const int now = pass_count(T);
     wmax = kColMax9;
     if (pass_count(13) < now)
