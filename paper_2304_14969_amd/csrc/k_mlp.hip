@@ -26,7 +26,7 @@ constexpr int kBlock = 256;
 // the inner dimension; each workgroup keeps its 24 tiles in registers over all
 // the rows it takes and writes one partial gradient, and k_mlp_reduce adds the
 // partials in workgroup order (in float64). Its bound is latency: 16 rows pass
-// six barriers and 208 matrix steps, and a minibatch of 256 rows is 16
+// seven barriers and 64 matrix steps in each wavefront, and a minibatch of 256 rows is 16
 // workgroups (10.4 us, then 3.2 us for the sums and the Adam step). 40 steps
 // of 256 rows, then loss, gradient and scores of 20000 rows take 1.07 ms
 // (0.6 ms of it on the GPU, the rest copies of the rows) instead of 18.7 ms
@@ -64,7 +64,9 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
   double ls = 0;
   const int nblk = (rows + kRows - 1) / kRows;
   for (int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const int r0 = blk * kRows, left = rows - r0;  // rows past the end enter as zeros
+    // Rows past the end are zeros in every array, as products by a zero factor
+    // alone are NaN where a weight has grown infinite.
+    const int r0 = blk * kRows, left = rows - r0;
 #pragma unroll
     for (int e = threadIdx.x; e < kRows * kIn; e += kBlock) {
       const int r = e / kIn;
@@ -77,7 +79,7 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
       h1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sx[col * kPadX + 4 * s + q], w1[s], h1, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      h1[i] = tanhf(h1[i]);
+      h1[i] = 4 * q + i < left ? tanhf(h1[i]) : 0.0f;
       s1[(4 * q + i) * kPadH + j] = h1[i];
     }
     __syncthreads();
@@ -87,7 +89,7 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
       h2 = __builtin_amdgcn_mfma_f32_16x16x4f32(s1[col * kPadH + 4 * s + q], w2[s], h2, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      h2[i] = tanhf(h2[i]);
+      h2[i] = 4 * q + i < left ? tanhf(h2[i]) : 0.0f;
       float v = h2[i] * w3;  // summed over the wavefront's 16 units
 #pragma unroll
       for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
@@ -115,7 +117,7 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
         const int r = 4 * q + i;
         const float yr = r < left ? y[r0 + r] : 0.0f;
         d3[i] = r < left ? (1.0f / (1.0f + expf(-logit(r))) - yr) / float(rows) : 0.0f;
-        d2[i] = d3[i] * w3 * (1.0f - h2[i] * h2[i]);
+        d2[i] = r < left ? d3[i] * w3 * (1.0f - h2[i] * h2[i]) : 0.0f;
         s2[r * kPadH + j] = d2[i];
         gw3 += h2[i] * d3[i];
         gb2 += d2[i];
@@ -138,7 +140,7 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
       __syncthreads();  // D2 is read; its place takes D1
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        d1[i] *= 1.0f - h1[i] * h1[i];
+        d1[i] = 4 * q + i < left ? d1[i] * (1.0f - h1[i] * h1[i]) : 0.0f;
         s2[(4 * q + i) * kPadH + j] = d1[i];
         gb1 += d1[i];
       }
