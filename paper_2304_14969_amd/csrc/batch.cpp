@@ -227,7 +227,12 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, int kmax, std::vector<c
     const qs::TilePlan& pl = *plans[i];
     round_base[i] = nround;
     const size_t m0 = mats.size();
-    mats.insert(mats.end(), pl.reals.begin(), pl.reals.end());
+    if (c64) {
+      const std::vector<float> f = qs::float_pairs(pl);
+      mats.insert(mats.end(), f.begin(), f.end());
+    } else {
+      mats.insert(mats.end(), pl.reals.begin(), pl.reals.end());
+    }
     for (const auto& r : pl.rounds) {
       if (r.mode == qs::TileMode::kPairs) {
         int32_t row[4];

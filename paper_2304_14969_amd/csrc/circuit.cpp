@@ -761,6 +761,28 @@ TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W
   return plan;
 }
 
+std::vector<float> float_pairs(const TilePlan& pl) {
+  constexpr int kReals = 32;  // of a gate
+  std::vector<float> out(pl.reals.size());
+  double scale = 1.0;
+  for (const TileRound& r : pl.rounds) {
+    if (r.mode != TileMode::kPairs) continue;
+    for (int g = 0; g < r.ng; ++g) {
+      const double* m = pl.reals.data() + r.mat + g * kReals;
+      float* f = out.data() + r.mat + g * kReals;
+      double before = 0, after = 0;
+      for (int i = 0; i < kReals; ++i) {
+        f[i] = float(m[i] * scale);
+        before += m[i] * m[i];
+        after += double(f[i]) * double(f[i]);
+      }
+      scale *= std::sqrt(before / after);
+      if (!(std::abs(scale - 1.0) < 1e-6)) scale = 1.0;  // a zero matrix, numbers out of range
+    }
+  }
+  return out;
+}
+
 void pair_round_entry(const TileRound& r, size_t base, int32_t row[4]) {
   int asc[4];
   std::copy(r.bits, r.bits + 4, asc);
@@ -811,7 +833,12 @@ void tile_tables(const TilePlan& pl, bool c64, std::vector<unsigned char>* out, 
     put(host + at->mats + 2 * i * esz, pl.mats[i].real());
     put(host + at->mats + (2 * i + 1) * esz, pl.mats[i].imag());
   }
-  for (size_t i = 0; i < pl.reals.size(); ++i) put(host + at->reals + i * esz, pl.reals[i]);
+  if (c64) {
+    const std::vector<float> f = float_pairs(pl);
+    if (!f.empty()) std::memcpy(host + at->reals, f.data(), f.size() * sizeof(float));
+  } else if (!pl.reals.empty()) {
+    std::memcpy(host + at->reals, pl.reals.data(), pl.reals.size() * sizeof(double));
+  }
 }
 
 void embed_round(const cd* u, float* out) {
