@@ -568,10 +568,12 @@ int qs_check(qs_state* st, double tol);
  *                    6 (512-byte rows, 64 KiB) or 4 (128-byte rows, 16 KiB);
  *                    complex128 tiles always have 16-amplitude (256-byte)
  *                    rows, 32 KiB;
- *   "tile.mfma"      1 (default): complex64 tile passes run their rounds as
- *                    dense 4-qubit blocks on the matrix cores (any gate of at
- *                    most 4 qubits joins a pass); 0: one- and two-qubit gates
- *                    applied one by one in registers;
+ *   "tile.mfma"      1 (default): complex64 tile passes run on the matrix
+ *                    cores, each in rounds of two two-qubit gates or in dense
+ *                    4-qubit blocks, whichever cost less (any gate of at most
+ *                    4 qubits joins a pass); 0: one- and two-qubit gates
+ *                    applied one by one in registers, and states below a tile
+ *                    run circuits as blocks;
  *   "factor.multi_test" 1 (default): the plain separability schedule
  *                    measures the lowest dirty qubit together with the next
  *                    dirty qubits of its subsystem (up to 5, none skipped) in

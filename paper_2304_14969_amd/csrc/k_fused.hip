@@ -109,8 +109,10 @@ __global__ void __launch_bounds__(kBlock) k_fused_vec(R* __restrict__ a, uint64_
 // Blocks of one to three qubits with the matrix passed by value: the same
 // arithmetic as k_fused_vec, the matrix from the kernel arguments by way of LDS
 // (read from there directly, states above the last-level cache lose: 27 qubits
-// 352 -> 362 us for one qubit, 365 -> 393 for two). A call on 10 to 18 qubits, bound by the host:
-// 9.5-10.4 us with an upload of the matrix, 6.7-7.8 us so.
+// 352 -> 362 us for one qubit, 365 -> 393 for two). A call on 10 to 18 qubits,
+// bound by the host: 9.5-10.4 us with an upload of the matrix, 6.7-7.8 us so. (A
+// body shared with k_fused_vec makes that one's code for 4 and 5 qubits complex64
+// an eighth longer.)
 template <typename R, int K>
 struct MatArg {
   R v[2 << (2 * K)];

@@ -6,14 +6,15 @@
 // default, 256-byte rows and 32 KiB tiles, 4 or 6 by knob; complex128: C = 4,
 // 256-byte rows, 32 KiB). The tile is staged
 // in LDS and transformed round by round, each round acting on 4 tile bits.
-// Three forms of rounds: two two-qubit gates in fixed places (k_tile_pair;
-// complex64 circuits of one- and two-qubit gates on the FP32 matrix cores, all
-// complex128 circuits with FP64 FMAs); a dense 4-qubit block on the matrix
-// cores (k_tile_mfma, complex64 circuits with gates of three or four qubits),
-// each complex product as three real ones (Re U X_r, Im U X_i and (Re U + Im
-// U)(X_r + X_i), 16 x 16 x 4 MFMAs: 3/4 of the flops of the 32 x 32 real
-// embedding); one- and two-qubit gates one by one in registers (k_tile_pass:
-// runs of one-qubit gates on factorized kets, and complex64 with tile.mfma 0).
+// Three forms of rounds, of which a pass takes the one whose rounds cost less:
+// two two-qubit gates in fixed places (k_tile_pair; on the FP32 matrix cores in
+// complex64, with FP64 FMAs in complex128); a dense 4-qubit block on the matrix
+// cores (k_tile_mfma, complex64; passes with gates of three or four qubits, and
+// those whose gates stay on few qubits), each complex product as three real ones
+// (Re U X_r, Im U X_i and (Re U + Im U)(X_r + X_i), 16 x 16 x 4 MFMAs: 3/4 of the
+// flops of the 32 x 32 real embedding); one- and two-qubit gates one by one in
+// registers (k_tile_pass: complex128 passes whose gates stay on few qubits, runs
+// of one-qubit gates on factorized kets, and complex64 with tile.mfma 0).
 #include "qs_internal.h"
 
 namespace qs {
@@ -651,14 +652,14 @@ __global__ void __launch_bounds__(1 << (TB - 2))
 }
 
 // Complex64 passes whose rounds are dense 4-qubit blocks on the FP32 matrix
-// cores. A round multiplies the 16 amplitudes of every group (the other 9
-// tile bits) by the round's 16x16 complex matrix U, as a real GEMM on the
-// interleaved embedding [[Re U, -Im U], [Im U, Re U]] with
-// v_mfma_f32_32x32x2f32: a wavefront takes 32 groups at a time (lane % 32 =
-// group, lane / 32 = real or imaginary part), one K-step per input amplitude.
-// `amats` holds each round's embedding in lane order: entry ks * 64 + lane =
-// Uemb[lane % 32][2 ks + lane / 32].
-// matrix-core operands of a round per lane: Re U, Im U, Re U + Im U for 4 K-steps
+// cores. A round multiplies the 16 amplitudes of every group (the other tile
+// bits) by the round's 16 x 16 complex matrix U, as three real products on
+// v_mfma_f32_16x16x4f32 (Re U X_r, Im U X_i and (Re U + Im U)(X_r + X_i)): a
+// wavefront takes 16 groups at a time, lane (q, col) = (lane / 16, lane % 16)
+// supplies row col of the matrices and input 4 s + q of group col in step s, and
+// gets outputs 4 q + i of that group. `amats` holds each round's operands in that
+// order, 12 values a lane: entry (3 s + c) 64 + lane = W_c[lane % 16][4 s + lane /
+// 16] with W_0 = Re U, W_1 = Im U, W_2 = Re U + Im U.
 constexpr int kOps = 12;
 static_assert(kOps * 64 == kRoundOperands, "round operand layout");
 
