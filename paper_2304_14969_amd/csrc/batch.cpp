@@ -143,31 +143,23 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, int kmax, std::vector<c
   const bool c64 = b->dtype == QS_C64;
   constexpr int H = qs::kTileRowBits;
   const int C = qs::batch_tile_low(b->dtype);
-  auto plan = [&](qs_circuit* c, int bits, qs::TileForms forms) {
-    const qs::TilePlan& have = c->bplan;
-    if (c->bplan_ok && have.C == C) {
-      bool fits = have.forms == forms;
-      if (have.forms == qs::TileForms::kPairsDense && !fits) {  // all its passes may be of the form
-        const qs::TileMode want =
-            forms == qs::TileForms::kPairs ? qs::TileMode::kPairs : qs::TileMode::kDense;
-        fits = true;
-        for (const auto& st : have.steps) fits = fits && !st.block && st.mode == want;
-      }
-      if (fits) return;
-    }
-    c->bplan = qs::plan_tiles(c->gates, bits, C, H, 4, forms);
+  auto plan = [&](qs_circuit* c, int bits, qs::TileForms forms, bool price = false) {
+    if (c->bplan_ok && c->bplan.C == C && c->bplan.forms == forms && !(price && !c->bcost_ok))
+      return;
+    c->bplan = qs::plan_tiles(c->gates, bits, C, H, 4, forms, price);
     c->bplan_ok = true;
   };
   // One form of rounds for every ket that could take pairs or dense ones, by
   // their sums: kets with passes of both forms run as two launches a pass, one
   // after the other (64 circuits of 12 to 16 qubits, 2 layers: 35 us in pairs,
-  // 40 with a form per ket).
+  // 40 with a form per ket). Dense rounds, whose products make a first run two to
+  // four times as long to prepare, have to promise a clear gain.
   double pair_cost = 0, dense_cost = 0;
   for (int i = 0; c64 && i < b->count; ++i) {
     qs_circuit* c = circs[i];
     if (b->n[i] < C + H || c->gates.empty() || !qs::narrow_gates(c->gates)) continue;
     if (!c->bcost_ok) {
-      plan(c, b->n[i], qs::TileForms::kPairsDense);
+      plan(c, b->n[i], qs::TileForms::kPairs, true);
       c->bcost[0] = c->bplan.pair_cost;
       c->bcost[1] = c->bplan.group_cost;
       c->bcost_ok = true;
@@ -176,7 +168,7 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, int kmax, std::vector<c
     dense_cost += std::ldexp(c->bcost[1], b->n[i]);
   }
   const qs::TileForms full =
-      c64 && dense_cost < pair_cost ? qs::TileForms::kDense : qs::TileForms::kPairs;
+      c64 && dense_cost < 0.92 * pair_cost ? qs::TileForms::kDense : qs::TileForms::kPairs;
   std::vector<const qs::TilePlan*> plans(b->count, nullptr);
   size_t maxp = 0;
   for (int i = 0; i < b->count; ++i) {

@@ -262,8 +262,8 @@ std::vector<Gate> merge_gates(const std::vector<Gate>& gates, int n) {
 // the dependence order lets it run inside the set; the set is the low bits
 // plus at most H qubits, grown by the ready gate that lets the most gates run
 // per qubit it adds. (Taking front gates in circuit order while they fit,
-// the rule before, needed 24.2 passes for 10 layers at 28 qubits where this
-// one needs 16.8, and 11.4 against 7.6 for 8 layers at 20.)
+// the rule before, needed 24.3 passes for 10 layers at 28 qubits where this
+// one needs 16.8, and 11.3 against 7.9 for 8 layers at 20.)
 struct PassPicker {
   const std::vector<Gate>& g;
   int n, max_k;
@@ -667,7 +667,7 @@ void group_round(TilePlan* plan, const std::vector<Gate>& gates, const std::vect
 }  // namespace
 
 TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W,
-                    TileForms forms) {
+                    TileForms forms, bool dense_price) {
   const std::vector<Gate> gates = merge_gates(circuit, n);
   TilePlan plan;
   plan.C = C;
@@ -675,7 +675,7 @@ TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W
   plan.W = W;
   plan.forms = forms;
   const bool dense = forms == TileForms::kPairsDense || forms == TileForms::kDense;
-  const RoundCost& cost = dense     ? kCost64
+  const RoundCost& cost = dense || dense_price ? kCost64
                           : n <= 19 ? kCost128One
                           : n == 20 ? kCost128Two
                                     : kCost128;
@@ -736,24 +736,19 @@ TilePlan plan_tiles(const std::vector<Gate>& circuit, int n, int C, int H, int W
       for (size_t r = size_t(st.r0); r < plan.rounds.size(); ++r)
         pair_cost += cost.pair[plan.rounds[r].ng - 1];
     }
-    if (groups) {
-      if (pairs) {
-        group_cost = cost.pass + cost.group * greedy_groups(tq, C + H, W, nullptr);
-        if (!dense)
-          for (int i : pass) group_cost += cost.gate[gates[i].k - 1];
-      }
-      if (!pairs || group_cost < pair_cost) {
-        plan.rounds.resize(size_t(st.r0));
-        plan.reals.resize(reals0);
-        st.mode = dense ? TileMode::kDense : TileMode::kSparse;
-        std::vector<Group> grp;
-        greedy_groups(tq, C + H, W, &grp);
-        for (const Group& g : grp) group_round(&plan, gates, pass, tq, g, W, dense);
-      }
-    }
-    if (pairs && groups) {
+    if (pairs && (groups || dense_price)) {
+      group_cost = cost.pass + cost.group * greedy_groups(tq, C + H, W, nullptr);
+      for (int i : pass) group_cost += cost.gate[gates[i].k - 1];  // (none in dense rounds)
       plan.pair_cost += pair_cost;
       plan.group_cost += group_cost;
+    }
+    if (groups && (!pairs || group_cost < pair_cost)) {
+      plan.rounds.resize(size_t(st.r0));
+      plan.reals.resize(reals0);
+      st.mode = dense ? TileMode::kDense : TileMode::kSparse;
+      std::vector<Group> grp;
+      greedy_groups(tq, C + H, W, &grp);
+      for (const Group& g : grp) group_round(&plan, gates, pass, tq, g, W, dense);
     }
     st.nr = int(plan.rounds.size()) - st.r0;
     plan.steps.push_back(st);

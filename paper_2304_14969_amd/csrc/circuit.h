@@ -85,8 +85,8 @@ struct TilePlan {
   std::vector<TileGate> gates;
   std::vector<cd> mats;
   std::vector<double> reals;  // pair rounds
-  // forms of two kinds: what the passes that could take either cost in pair
-  // rounds and in the other form (the same units, per tile)
+  // what the passes that could take pair rounds cost so and in the other form
+  // (the same units, per tile), where both were asked for
   double pair_cost = 0, group_cost = 0;
   int passes() const {
     int p = 0;
@@ -104,7 +104,9 @@ struct TilePlan {
 // longest chains of gates behind them; a pass takes the form whose rounds cost
 // less (RoundCost in circuit.cpp). Gates too wide for a round (more than
 // two qubits, or more than W for dense rounds) run as blocks between passes.
-TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, TileForms forms);
+// dense_price: also what dense rounds would cost where forms is kPairs.
+TilePlan plan_tiles(const std::vector<Gate>& gates, int n, int C, int H, int W, TileForms forms,
+                    bool dense_price = false);
 
 // Whether every gate has one or two qubits.
 bool narrow_gates(const std::vector<Gate>& gates);

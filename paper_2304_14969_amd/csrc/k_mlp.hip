@@ -79,7 +79,8 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
       h1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sx[col * kPadX + 4 * s + q], w1[s], h1, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      h1[i] = 4 * q + i < left ? tanhf(h1[i]) : 0.0f;
+      h1[i] = tanhf(h1[i]);
+      if (left < kRows && 4 * q + i >= left) h1[i] = 0.0f;
       s1[(4 * q + i) * kPadH + j] = h1[i];
     }
     __syncthreads();
@@ -89,7 +90,8 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
       h2 = __builtin_amdgcn_mfma_f32_16x16x4f32(s1[col * kPadH + 4 * s + q], w2[s], h2, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      h2[i] = 4 * q + i < left ? tanhf(h2[i]) : 0.0f;
+      h2[i] = tanhf(h2[i]);
+      if (left < kRows && 4 * q + i >= left) h2[i] = 0.0f;
       float v = h2[i] * w3;  // summed over the wavefront's 16 units
 #pragma unroll
       for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
@@ -117,7 +119,8 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
         const int r = 4 * q + i;
         const float yr = r < left ? y[r0 + r] : 0.0f;
         d3[i] = r < left ? (1.0f / (1.0f + expf(-logit(r))) - yr) / float(rows) : 0.0f;
-        d2[i] = r < left ? d3[i] * w3 * (1.0f - h2[i] * h2[i]) : 0.0f;
+        d2[i] = d3[i] * w3 * (1.0f - h2[i] * h2[i]);
+        if (left < kRows && r >= left) d2[i] = 0.0f;
         s2[r * kPadH + j] = d2[i];
         gw3 += h2[i] * d3[i];
         gb2 += d2[i];
@@ -140,7 +143,8 @@ __global__ void __launch_bounds__(kBlock) k_mlp_rows(const float* __restrict__ P
       __syncthreads();  // D2 is read; its place takes D1
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        d1[i] = 4 * q + i < left ? d1[i] * (1.0f - h1[i] * h1[i]) : 0.0f;
+        d1[i] *= 1.0f - h1[i] * h1[i];
+        if (left < kRows && 4 * q + i >= left) d1[i] = 0.0f;
         s2[(4 * q + i) * kPadH + j] = d1[i];
         gb1 += d1[i];
       }
