@@ -32,8 +32,8 @@ HBM_PEAK_GBS = 8000.0
 # (`bench.py --calibrate-copy`: FETCH_SIZE reads 0.50002 of the bytes copied,
 # WRITE_SIZE 1.00000). Valid only for the kernel source they were taken on.
 TRAFFIC_SOURCE = os.path.join(ROOT, "paper_2304_14969_amd", "csrc", "k_qft.hip")
-TRAFFIC = {"sha256": "86034e83500f988c2b24b5bb9d839e624c0c36d081283c6a4c7b25e31a167d96",
-           "bytes_per_launch": {"qft_col8": 2147807433, "qft_lds": 2147610211}}
+TRAFFIC = {"sha256": "137d00952855b7cc9a4e87c30dc4953f3c99ecae943126b79e10a904eda8c29b",
+           "bytes_per_launch": {"qft_col8": 2147813833, "qft_lds": 2147610620}}
 
 
 def measured_traffic(kernel: str):
@@ -134,7 +134,7 @@ def bench_circuit(qs, workloads, torch, n: int = 32, layers: int = 10, seed: int
                   kmaxes=(4, 5)) -> dict:
     """Exact random circuit (U3 on every qubit, then CZ/iSWAP on a random
     matching, per layer): tile passes (several gates per HBM sweep, rounds of
-    dense 4-qubit blocks on the matrix cores), and for comparison one sweep
+    two two-qubit gates on the matrix cores), and for comparison one sweep
     per fused block of at most kmax qubits, for each kmax in kmaxes."""
     gates = workloads.random_circuit(n, layers, seed)
     st = qs.State(n, qs.C64)
@@ -161,8 +161,8 @@ def bench_circuit(qs, workloads, torch, n: int = 32, layers: int = 10, seed: int
         norm = st.norm()
         if mode == "tiles":
             def flops(name, rounds=ti["rounds"], passes=ti["passes"]):
-                # dense 16x16 complex blocks: 8 x 16 real flops per amplitude per round
-                return 8.0 * 16 * 2 ** n * rounds / passes if name == "tile_mfma" else 0.0
+                # two 4x4 complex gates a round: 8 x 4 real flops per amplitude each
+                return 8.0 * 8 * 2 ** n * rounds / passes if name == "tile_mfma" else 0.0
             out["tiles"] = {"s": round(dt, 4), "sweeps": ti["passes"], "rounds": ti["rounds"],
                             "norm_after": norm, "kernels": _kernel_rates(prof, flops)}
         else:

@@ -395,8 +395,8 @@ int qs_circuit_plan(qs_circuit* c, int kmax);
 
 /* Run this circuit on dense states as tile passes (on != 0) or as fused
  * blocks (on = 0). Without either call, or qs_circuit_plan before it, dense
- * runs use tile passes: on MI355X they took 0.49-0.92 of the blocks' time
- * for random circuits of 1 to 10 layers at 20 and 30 qubits, and 0.53 at 32
+ * runs use tile passes: on MI355X they take 0.28-0.54 of the blocks' time
+ * for random circuits of 1 to 10 layers at 20 and 30 qubits, and 0.36 at 32
  * qubits and 10 layers. A pass reads and writes the ket once for every one- and
  * two-qubit gate it holds: a tile is the contiguous low bits (complex64:
  * "tile.low_bits", 5 by default; complex128: 4) plus 7 bits chosen per pass, and the passes
@@ -465,7 +465,9 @@ int qs_batch_replay(qs_batch* b);
  * batched as one launch per pass index over every ket that has that pass; a
  * ket smaller than a tile is one pass. Kets with gates of more than two
  * qubits keep the block launches (in complex64 and at 12 qubits or more:
- * with gates of more than four). on = 0: blocks for every ket. Drops a
+ * with gates of more than four), and so do kets in complex128 or below 12
+ * qubits that have many gates on few qubits, when the run is estimated to end
+ * sooner that way. on = 0: blocks for every ket. Drops a
  * prepared run or graph; applies to the next run or capture. */
 int qs_batch_use_tiles(qs_batch* b, int on);
 /* Launches per run of the last prepared run and arena size in amplitudes. */

@@ -82,3 +82,26 @@ def test_batch_in_one_form(qs_lib, kinds):
                               f"ket {i} {kinds[i]}")
     one.free()
     two.free()
+
+
+@pytest.mark.parametrize("dtype,n", [(C64, 14), (C128, 13)])
+@pytest.mark.parametrize("kind", ["few", "layers, few, chain"])
+def test_streaming_and_plain_passes_agree(qs_lib, dtype, n, kind):
+    """Bit for bit, in every form."""
+    gates = KINDS[kind](n, np.random.default_rng(n))
+    a = workloads.gaussian_state(n, n)
+    c = qs_lib.Circuit(n).add_gates(gates)
+    saved = qs_lib.tune_get("sweep.stream")
+    got = []
+    try:
+        for stream in (1, 2):
+            qs_lib.tune_set("sweep.stream", stream)
+            with qs_lib.State(n, dtype) as st:
+                st.set_amplitudes(a)
+                st.run(c)
+                got.append(st.amplitudes())
+    finally:
+        qs_lib.tune_set("sweep.stream", saved)
+    np.testing.assert_array_equal(got[0], got[1])
+    assert_parity(got[0], run_oracle(a, n, gates), dtype, kind)
+    c.free()
