@@ -224,10 +224,12 @@ std::vector<Gate> merge_gates(const std::vector<Gate>& gates, int n) {
     for (int j = 1; j < g.k; ++j)
       if (last[g.q[j]] != prev) prev = -1;
     const bool onto = prev >= 0 && out[prev].k == g.k;
+    bool alone = !onto;
+    for (int j = 0; j < g.k; ++j) alone = alone && pend[g.q[j]].empty();
     Gate w;
     if (!onto) {
       w = g;
-      w.m = eye(g.k);
+      if (!alone) w.m = eye(g.k);
     }
     Gate& t = onto ? out[prev] : w;
     int lp[QS_MAX_FUSED];
@@ -237,7 +239,7 @@ std::vector<Gate> merge_gates(const std::vector<Gate>& gates, int n) {
       if (!u.empty()) left_apply(t.m, t.k, u, 1, &lp[j]);
       u.clear();
     }
-    left_apply(t.m, t.k, g.m, g.k, lp);
+    if (!alone) left_apply(t.m, t.k, g.m, g.k, lp);
     if (onto) continue;
     for (int j = 0; j < g.k; ++j) last[g.q[j]] = int(out.size());
     out.push_back(std::move(w));
