@@ -185,26 +185,31 @@ int prepare_tiles(qs_batch* b, qs_circuit* const* circs, int kmax, std::vector<c
     if (!ok) continue;
     (*use_tile)[i] = 1;
   }
-  BatchTime passes{c64}, both{c64};
-  std::vector<int> moved;
+  std::vector<std::pair<int, std::vector<int>>> few;  // kets to move, their blocks' widths
   for (int i = 0; i < b->count; ++i) {
-    if (!(*use_tile)[i]) continue;
-    const uint64_t tiles = uint64_t(1) << std::max(0, b->n[i] - C - H);
-    passes.add_passes(*plans[i], tiles);
+    if (!(*use_tile)[i] || (c64 && b->n[i] >= C + H)) continue;
     double rounds = 0;  // a block is a launch, worth about 8 rounds
-    for (const auto& r : plans[i]->rounds) rounds += r.mode != qs::TileMode::kPairs ? 0 : r.ng > 1 ? 1.4 : 1.0;
-    if (rounds > 8 && (!c64 || b->n[i] < C + H)) {
-      const std::vector<int> widths = qs::block_widths(circs[i]->gates, b->n[i], kmax);
-      if (8.0 * double(widths.size()) < rounds) {
-        moved.push_back(i);
-        both.add_blocks(widths, b->n[i]);
-        continue;
-      }
-    }
-    both.add_passes(*plans[i], tiles);
+    for (const auto& r : plans[i]->rounds) rounds += r.ng > 1 ? 1.4 : 1.0;
+    if (rounds <= 8) continue;
+    std::vector<int> widths = qs::block_widths(circs[i]->gates, b->n[i], kmax);
+    if (8.0 * double(widths.size()) < rounds) few.emplace_back(i, std::move(widths));
   }
-  if (!moved.empty() && both.us() < 0.8 * passes.us())
-    for (int i : moved) (*use_tile)[i] = 0;
+  if (!few.empty()) {
+    BatchTime passes{c64}, both{c64};
+    std::vector<char> moved(b->count, 0);
+    for (const auto& f : few) {
+      moved[f.first] = 1;
+      both.add_blocks(f.second, b->n[f.first]);
+    }
+    for (int i = 0; i < b->count; ++i) {
+      if (!(*use_tile)[i]) continue;
+      const uint64_t tiles = uint64_t(1) << std::max(0, b->n[i] - C - H);
+      passes.add_passes(*plans[i], tiles);
+      if (!moved[i]) both.add_passes(*plans[i], tiles);
+    }
+    if (both.us() < 0.8 * passes.us())
+      for (const auto& f : few) (*use_tile)[f.first] = 0;
+  }
   for (int i = 0; i < b->count; ++i)
     if ((*use_tile)[i]) maxp = std::max(maxp, plans[i]->steps.size());
   if (!maxp) return QS_OK;

@@ -767,12 +767,15 @@ std::vector<float> float_pairs(const TilePlan& pl) {
     for (int g = 0; g < r.ng; ++g) {
       const double* m = pl.reals.data() + r.mat + g * kReals;
       float* f = out.data() + r.mat + g * kReals;
+      double b[8] = {}, c[8] = {};  // squares before and after the cast, in 8 sums
+      for (int i = 0; i < kReals; i += 8)
+        for (int j = 0; j < 8; ++j) {
+          f[i + j] = float(m[i + j] * scale);
+          b[j] += m[i + j] * m[i + j];
+          c[j] += double(f[i + j]) * double(f[i + j]);
+        }
       double before = 0, after = 0;
-      for (int i = 0; i < kReals; ++i) {
-        f[i] = float(m[i] * scale);
-        before += m[i] * m[i];
-        after += double(f[i]) * double(f[i]);
-      }
+      for (int j = 0; j < 8; ++j) before += b[j], after += c[j];
       scale *= std::sqrt(before / after);
       if (!(std::abs(scale - 1.0) < 1e-6)) scale = 1.0;  // a zero matrix, numbers out of range
     }
