@@ -27,7 +27,8 @@ __device__ __forceinline__ uint64_t insert_zero(uint64_t x, int pos) {
 // and i + 128, then i and i + 64, ..., i and i + 1): all values go through LDS
 // once, wavefront w then owns rows w, w + 4, ... and folds them by shuffles. A
 // barrier per level for all rows cost more than the sums of a small subsystem;
-// an approximate run of 54 qubits, some 100 such sweeps in turn, 2410 -> 2230 us.
+// an approximate run on a 6 x 9 grid of 7 layers, p = 0.6, some 100 such sweeps in
+// turn, 2410 -> 2230 us (the approximate case of perf/cases.py at seed 1).
 template <int N>
 __device__ __forceinline__ void block_sum(double (&v)[N], double* sh) {
   static_assert(kBlock == 256, "four wavefronts");
